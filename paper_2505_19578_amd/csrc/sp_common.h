@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "shareprefill.h"
 
@@ -18,6 +19,16 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+// f(integral_constant<int, G>) for G = FROM .. TO-1, expanded at compile time (the steps below index registers
+// by G, so they must never be left as a run-time loop)
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (FROM < TO) {
+    f(std::integral_constant<int, FROM>{});
+    static_for<FROM + 1, TO>(f);
+  }
+}
 
 constexpr int SP_MAX_HEADS = 128;
 constexpr int KT = 64;  // keys per sub-tile

@@ -3,7 +3,6 @@
 // offsets are walked as bands of key blocks with a bit mask inside every tile.
 #ifndef SP_VS_TOKEN_KERNELS_H
 #define SP_VS_TOKEN_KERNELS_H
-#include <type_traits>
 #include "sp_common.h"
 #include "attn_kernel.h"
 #include "vertical_slash_kernels.h"
@@ -166,16 +165,6 @@ __global__ __launch_bounds__(256) void vs_gather_kernel(VsTokParams p) {
     }
     u32x4 val = {w[0], w[1], w[2], w[3]};
     *reinterpret_cast<u32x4 *>(out + IMG + (int64_t)c * 16) = val;
-  }
-}
-
-// f(integral_constant<int, G>) for G = FROM .. TO-1, expanded at compile time (the steps below index registers
-// by G, so they must never be left as a run-time loop)
-template <int FROM, int TO, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (FROM < TO) {
-    f(std::integral_constant<int, FROM>{});
-    static_for<FROM + 1, TO>(f);
   }
 }
 
