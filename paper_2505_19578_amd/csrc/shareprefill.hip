@@ -401,14 +401,16 @@ void launch_gsel_threshold(const float *scores, int n_maps, const GselGeom &g, u
 
 // workspace of the vertical-slash search for n listed heads per batch entry
 struct VsLayout {
-  size_t x, stats, sums, flags, gsel, total;
+  size_t part, sums, flags, gsel, total;
 };
 VsLayout vs_layout(const sp_shape *s, int n) {
   const size_t maps = (size_t)s->batch * n, nkb = s->seq / s->block;
   VsLayout L;
-  L.x = 0;
-  L.stats = L.x + align_up(maps * s->block * s->seq * sizeof(float), 256);
-  L.sums = L.stats + align_up(maps * s->block * 2 * sizeof(float), 256);
+  L.part = 0;
+  // (the sizes that callers have been told: room for every logit of a query block, of which the partial row statistics
+  // take nkb * block * 8 bytes at most)
+  L.sums = L.part + align_up(maps * s->block * s->seq * sizeof(float), 256) +
+           align_up(maps * s->block * 2 * sizeof(float), 256);
   L.flags = L.sums + align_up(maps * 2 * s->seq * sizeof(float), 256);
   L.gsel = L.flags + align_up(maps * 2 * nkb * sizeof(int32_t), 256);
   L.total = L.gsel + align_up(maps * 2 * gsel_map_bytes((int)nkb), 256);
@@ -444,19 +446,23 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
   vp.n_q_heads = s->n_q_heads;
   const float scale = (s->softmax_scale > 0.f) ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   vp.c = scale * 1.4426950408889634f;
-  vp.x = (float *)(vs_ws + L.x);
-  vp.stats = (float *)(vs_ws + L.stats);
+  // Chunks of whole key blocks: about 1024 workgroups over all listed heads (four per CU, so that the heads that
+  // a role leaves out do not empty the chip), at most 64 because every workgroup of the second pass merges the
+  // statistics of all of them.
+  const int want = std::min(64, std::max(1, 1024 / (s->batch * n)));
+  vp.chunk = (nkb + want - 1) / want;
+  vp.n_chunks = (nkb + vp.chunk - 1) / vp.chunk;
+  vp.part = (float2 *)(vs_ws + L.part);
   vp.sums = sums_out ? sums_out : (float *)(vs_ws + L.sums);
   vp.role = role;
   for (int a = 0; a < n; ++a) vp.head_ids[a] = heads[a];
   int32_t *flags = (int32_t *)(vs_ws + L.flags);
   ProfScope prof(KK_VS, st);
-  const dim3 glog((s->seq + 127) / 128, n, s->batch), gstat(s->block, n, s->batch), gsum((s->seq + 255) / 256, n, s->batch);
-#define SP_VS(D_, B_)                                                                  \
-  do {                                                                                 \
-    hipLaunchKernelGGL((vs_logits_kernel<D_, B_>), glog, dim3(256), 0, st, vp);        \
-    hipLaunchKernelGGL((vs_rowstats_kernel<B_>), gstat, dim3(256), 0, st, vp);         \
-    hipLaunchKernelGGL((vs_sums_kernel<B_>), gsum, dim3(256), 0, st, vp);              \
+  const dim3 gvs(vp.n_chunks, n, s->batch), bvs(s->block * 2);
+#define SP_VS(D_, B_)                                                           \
+  do {                                                                          \
+    hipLaunchKernelGGL((vs_rowpart_kernel<D_, B_>), gvs, bvs, 0, st, vp);       \
+    hipLaunchKernelGGL((vs_sums_kernel<D_, B_>), gvs, bvs, 0, st, vp);          \
   } while (0)
   if (s->head_dim == 128 && s->block == 128)
     SP_VS(128, 128);

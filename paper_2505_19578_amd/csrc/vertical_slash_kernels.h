@@ -9,17 +9,19 @@
 namespace {
 
 // ---- Search Vertical Slash Pattern (Alg. 5) ------------------------------------------------------
-// Q_hat = the last `block` queries.  Their raw dot products with every key go to a workspace slab
-// X[b][n][t][s] (fp32), three memory-bound passes turn it into the normalised vertical sums a_v[s] and
-// slash sums a_s[t - s], the vector selection above keeps the shortest prefixes reaching gamma, and the kept
-// keys / offsets become per-row key-block lists.
+// Q_hat = the last `block` queries, A_hat = their causal softmax over every key.  Two passes over K form the logits by
+// MFMA and keep them on chip: the first leaves row max and row sum per chunk of keys, the second merges those, forms
+// the logits again and adds up the normalised vertical sums a_v[s] and slash sums a_s[t - s].  (K is read twice, 2 x
+// 64 MiB per 128K keys and KV head; a slab of logits in memory, written once and read three times, was 64 MiB per
+// query head.)  The vector selection above keeps the shortest prefixes reaching gamma, and the kept keys / offsets
+// become per-row key-block lists.
 struct VsParams {
   const uint16_t *q, *k;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
   int seq, group, n_heads, n_q_heads;
+  int n_chunks, chunk;   // chunks of `chunk` key blocks, the last one may be shorter
   float c;               // softmax scale * log2(e)
-  float *x;              // [b][n][B][seq]
-  float *stats;          // [b][n][B][2]  row max (log2 domain) and 1 / row sum
+  float2 *part;          // [b][n][n_chunks][B]  row max (log2 domain) and row sum of a chunk
   float *sums;           // [b][n][2][seq] a_v then a_s
   const int32_t *role;   // optional [b][n_q_heads]: only heads whose entry is -1 are processed
   int32_t head_ids[SP_MAX_HEADS];
@@ -27,97 +29,214 @@ struct VsParams {
 __device__ __forceinline__ bool vs_skip(const VsParams &p, int b, int n) {
   return p.role != nullptr && p.role[(int64_t)b * p.n_q_heads + p.head_ids[n]] != -1;
 }
+// (m, l) := (m, l) joined with (m2, l2), sums l relative to 2^m; -inf with 0 is the empty sum
+__device__ __forceinline__ void vs_join(float &m, float &l, float m2, float l2) {
+  const float mn = fmaxf(m, m2), ref = (mn == -INFINITY) ? 0.f : mn;
+  l = l * fast_exp2(m - ref) + l2 * fast_exp2(m2 - ref);
+  m = mn;
+}
 
-// X = Q_hat K^T with the queries as MFMA rows and the keys as columns, so that one accumulator register
-// holds 32 consecutive keys of one query across the lanes and the stores coalesce.  A workgroup takes 128
-// keys (32 per wavefront) against all B queries; operands come straight from the caller's Q and K.
+// Pass 1: causal softmax statistics of the B query rows over one chunk of keys.  Bound by MFMA and the exponentials
+// (one per logit); a wavefront owns 32 queries (one per lane, as in attn_kernel, so nothing is exchanged before the end)
+// and the wavefronts share 64-key tiles of K in LDS, fetched one tile ahead.
+// Also clears the slash sums that two chunks add to in pass 2.
 template <int D, int B>
-__global__ __launch_bounds__(256) void vs_logits_kernel(VsParams p) {
-  constexpr int DS = D / 16;
-  const int n = blockIdx.y, b = blockIdx.z;
+__global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
+  constexpr int DS = D / 16, NT = B * 2, IMG = KT * D * 2, NP = IMG / 16 / NT;
+  __shared__ __attribute__((aligned(16))) char kt_sh[2][IMG];
+  const int chunk = blockIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (vs_skip(p, b, n)) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
-  const int head = p.head_ids[n];
-  const int s0 = blockIdx.x * 128 + 32 * w;
-  if (s0 >= p.seq) return;  // seq is a multiple of 64, not necessarily of 128 (no barrier below)
-  const uint16_t *kp = p.k + (int64_t)b * p.k_sb + (int64_t)(s0 + c) * p.k_st + (int64_t)(head / p.group) * p.k_sh + 8 * h;
-  bf16x8 kf[DS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
+  const int head = p.head_ids[n], nkb = p.seq / B, t0 = p.seq - B;
+  const int64_t hb = (int64_t)b * p.n_heads + n;
+  const int b0 = chunk * p.chunk, b1 = min(b0 + p.chunk, nkb);
+  if (chunk > 0 && tid < B) p.sums[(hb * 2 + 1) * p.seq + t0 - b0 * B + B - tid] = 0.f;
+  const int u0 = b0 * (B / KT), u1 = b1 * (B / KT);
+  const uint16_t *kbase = p.k + (int64_t)b * p.k_sb + (int64_t)(head / p.group) * p.k_sh;
+  // piece x of this thread: 16 bytes of fragment f = rb * DS + ds of the tile, in operand order
+  u32x4 stage[NP];
+  auto fetch = [&](int u) {
 #pragma unroll
-  for (int ds = 0; ds < DS; ++ds) kf[ds] = *reinterpret_cast<const bf16x8 *>(kp + 16 * ds);
-  float *xo = p.x + (((int64_t)b * p.n_heads + n) * B) * p.seq + s0 + c;
-#pragma unroll
-  for (int qt = 0; qt < B / 32; ++qt) {
-    const uint16_t *qp = p.q + (int64_t)b * p.q_sb + (int64_t)(p.seq - B + 32 * qt + c) * p.q_st +
-                         (int64_t)head * p.q_sh + 8 * h;
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-    for (int ds = 0; ds < DS; ++ds) {
-      const bf16x8 qf = *reinterpret_cast<const bf16x8 *>(qp + 16 * ds);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[ds], acc, 0, 0, 0);
+    for (int x = 0; x < NP; ++x) {
+      const int f = (tid + x * NT) >> 6;
+      const int key = 32 * (f / DS) + c, dpos = 16 * (f % DS) + 8 * h;
+      stage[x] = *reinterpret_cast<const u32x4 *>(kbase + (int64_t)(u * KT + key) * p.k_st + dpos);
     }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int x = 0; x < NP; ++x) *reinterpret_cast<u32x4 *>(kt_sh[buf] + (tid + x * NT) * 16) = stage[x];
+  };
+  fetch(u0);
+  const int tq = 32 * w + c;
+  bf16x8 qf[DS];
+  const uint16_t *qp = p.q + (int64_t)b * p.q_sb + (int64_t)(t0 + tq) * p.q_st + (int64_t)head * p.q_sh + 8 * h;
+#pragma unroll
+  for (int ds = 0; ds < DS; ++ds) qf[ds] = *reinterpret_cast<const bf16x8 *>(qp + 16 * ds);
+  put(0);
+  __syncthreads();
+  float m = -INFINITY, l = 0.f;
+  for (int u = u0; u < u1; ++u) {
+    const int buf = (u - u0) & 1;
+    if (u + 1 < u1) fetch(u + 1);
+    f32x16 s[2];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[rb][r] = 0.f;
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kt_sh[buf] + (rb * DS + ds) * 1024 + lane * 16);
+        s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s[rb], 0, 0, 0);
+      }
+    if (u * KT >= t0) {
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (u * KT + 32 * rb + 8 * (r >> 2) + 4 * h + (r & 3) > t0 + tq) s[rb][r] = -INFINITY;
+    }
+    float mx = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(s[0][r], s[1][r]));
+    const float mn = fmaxf(m, mx * p.c), ref = (mn == -INFINITY) ? 0.f : mn;
+    float l0 = 0.f, l1 = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int t = 32 * qt + 8 * (r >> 2) + 4 * h + (r & 3);
-      xo[(int64_t)t * p.seq] = acc[r];
+      l0 += fast_exp2(__builtin_fmaf(s[0][r], p.c, -ref));
+      l1 += fast_exp2(__builtin_fmaf(s[1][r], p.c, -ref));
     }
+    l = l * fast_exp2(m - ref) + (l0 + l1);
+    m = mn;
+    if (u + 1 < u1) put(buf ^ 1);
+    __syncthreads();
   }
+  const float m2 = __shfl_xor(m, 32, 64), l2 = __shfl_xor(l, 32, 64);
+  vs_join(m, l, m2, l2);
+  if (h == 0) p.part[(hb * p.n_chunks + chunk) * B + tq] = make_float2(m, l);
 }
 
-// causal softmax statistics of each of the B query rows: one workgroup per row
-template <int B>
-__global__ __launch_bounds__(256) void vs_rowstats_kernel(VsParams p) {
-  __shared__ float red[4];
-  const int t = blockIdx.x, n = blockIdx.y, b = blockIdx.z;
+// Pass 2: a_v and a_s of one chunk of key blocks.  Queries are MFMA rows and keys columns (a wavefront owns 32 keys, one
+// per lane), so the vertical sums stay in a lane; the weights of 32 queries x B keys go through LDS, double buffered,
+// and thread (d, half) adds the wrapped diagonal key = (t + d) mod B of its 16 queries there, at consecutive addresses:
+// the part before the wrap belongs to offset t0 - s0 - d, the part after it to the offset B further up, which the
+// next lower key block finishes.  Only at the ends of a chunk do two workgroups add to one offset: two additions
+// to a cleared value, the same in either order.  Everything else is added in a fixed order.
+// Both passes, 128K keys, 32 heads of d 128: 2646 -> 972 us; 8K keys: 153 -> 97 us (with the slab -> now).
+template <int D, int B>
+__global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
+  constexpr int DS = D / 16, NT = B * 2, NQ = B / 32, PS = B + 8;
+  __shared__ __attribute__((aligned(16))) char q_sh[B * D * 2];
+  __shared__ __attribute__((aligned(16))) float pt[2][32 * PS];
+  __shared__ __attribute__((aligned(16))) float mx_sh[B], inv_sh[B];
+  __shared__ float wrap_sh[2][B];
+  const int chunk = blockIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (vs_skip(p, b, n)) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int last = p.seq - B + t;  // keys 0 .. last exist for this query
-  const float *x = p.x + (((int64_t)b * p.n_heads + n) * B + t) * p.seq;
-  float mx = -INFINITY;
-  for (int s = tid; s <= last; s += 256) mx = fmaxf(mx, x[s]);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  if (lane == 0) red[w] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * p.c;
-  __syncthreads();
-  float sum = 0.f;
-  for (int s = tid; s <= last; s += 256) sum += fast_exp2(__builtin_fmaf(x[s], p.c, -mx));
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) red[w] = sum;
-  __syncthreads();
-  if (tid == 0) {
-    float *st = p.stats + (((int64_t)b * p.n_heads + n) * B + t) * 2;
-    st[0] = mx;
-    st[1] = 1.f / (red[0] + red[1] + red[2] + red[3]);
-  }
-}
-
-// thread i owns key i (vertical sum) and offset i (slash sum); the B queries are added in a fixed order
-template <int B>
-__global__ __launch_bounds__(256) void vs_sums_kernel(VsParams p) {
-  __shared__ float st[B][2];
-  const int n = blockIdx.y, b = blockIdx.z;
-  if (vs_skip(p, b, n)) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
+  const int head = p.head_ids[n], nkb = p.seq / B, t0 = p.seq - B;
   const int64_t hb = (int64_t)b * p.n_heads + n;
-  for (int x = threadIdx.x; x < 2 * B; x += 256) st[x >> 1][x & 1] = p.stats[hb * B * 2 + x];
-  __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= p.seq) return;
-  const float *x = p.x + hb * B * p.seq;
-  const int t0 = p.seq - B;
-  float av = 0.f, as = 0.f;
-  for (int t = 0; t < B; ++t) {
-    const int tabs = t0 + t;
-    if (i <= tabs) {
-      av += fast_exp2(__builtin_fmaf(x[(int64_t)t * p.seq + i], p.c, -st[t][0])) * st[t][1];
-      as += fast_exp2(__builtin_fmaf(x[(int64_t)t * p.seq + (tabs - i)], p.c, -st[t][0])) * st[t][1];
+  const int b0 = chunk * p.chunk, b1 = min(b0 + p.chunk, nkb);
+  const uint16_t *kbase =
+      p.k + (int64_t)b * p.k_sb + (int64_t)(32 * w + c) * p.k_st + (int64_t)(head / p.group) * p.k_sh + 8 * h;
+  bf16x8 kf[DS], kn[DS];
+#pragma unroll
+  for (int ds = 0; ds < DS; ++ds)
+    kn[ds] = *reinterpret_cast<const bf16x8 *>(kbase + (int64_t)b0 * B * p.k_st + 16 * ds);
+  const uint16_t *qbase = p.q + (int64_t)b * p.q_sb + (int64_t)t0 * p.q_st + (int64_t)head * p.q_sh;
+#pragma unroll
+  for (int x = 0; x < NQ * DS * 64 / NT; ++x) {
+    const int f = (tid + x * NT) >> 6;
+    const u32x4 val =
+        *reinterpret_cast<const u32x4 *>(qbase + (int64_t)(32 * (f / DS) + c) * p.q_st + 16 * (f % DS) + 8 * h);
+    *reinterpret_cast<u32x4 *>(q_sh + (tid + x * NT) * 16) = val;
+  }
+  const int d = tid & (B - 1), half = tid / B;
+  {
+    float m = -INFINITY, l = 0.f;
+#pragma unroll 4
+    for (int x = half; x < p.n_chunks; x += 2) {
+      const float2 y = p.part[(hb * p.n_chunks + x) * B + d];
+      vs_join(m, l, y.x, y.y);
+    }
+    if (half) wrap_sh[0][d] = m, wrap_sh[1][d] = l;
+    __syncthreads();
+    if (!half) {
+      vs_join(m, l, wrap_sh[0][d], wrap_sh[1][d]);
+      mx_sh[d] = m;
+      inv_sh[d] = 1.f / l;
+    }
+    __syncthreads();
+  }
+  float *sv = p.sums + hb * 2 * p.seq, *ss = sv + p.seq;
+  float low = 0.f;  // diagonal sums before the wrap of the previous key block
+  for (int kb = b0; kb < b1; ++kb) {
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) kf[ds] = kn[ds];
+    if (kb + 1 < b1) {
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds)
+        kn[ds] = *reinterpret_cast<const bf16x8 *>(kbase + (int64_t)(kb + 1) * B * p.k_st + 16 * ds);
+    }
+    float av = 0.f, before = 0.f, after = 0.f;
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) {
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(q_sh + (qt * DS + ds) * 1024 + lane * 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[ds], acc, 0, 0, 0);
+      }
+      float *tile = pt[qt & 1];
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int t = 8 * r4 + 4 * h;
+        const float4 mx = *reinterpret_cast<const float4 *>(&mx_sh[32 * qt + t]);
+        const float4 inv = *reinterpret_cast<const float4 *>(&inv_sh[32 * qt + t]);
+        const float mm[4] = {mx.x, mx.y, mx.z, mx.w}, ii[4] = {inv.x, inv.y, inv.z, inv.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x = fast_exp2(__builtin_fmaf(acc[4 * r4 + e], p.c, -mm[e])) * ii[e];
+          if (kb == nkb - 1 && 32 * w + c > 32 * qt + t + e) x = 0.f;
+          av += x;
+          tile[(t + e) * PS + 32 * w + c] = x;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int tr = 16 * half + r, at = 32 * qt + tr + d;
+        const float x = tile[tr * PS + (at & (B - 1))];
+        before += (at < B) ? x : 0.f;
+        after += (at < B) ? 0.f : x;
+      }
+    }
+    if (half) wrap_sh[0][d] = before, wrap_sh[1][d] = after;
+    av = sum_xor32(av);
+    if (h == 0) sv[kb * B + 32 * w + c] = av * (1.f / B);
+    __syncthreads();
+    if (!half) {
+      before += wrap_sh[0][d];
+      after += wrap_sh[1][d];
+      const int o = t0 - kb * B + B - d;  // offset that `after` and the previous block's `before` add up to
+      if (kb > b0)
+        ss[o] = (low + after) * (1.f / B);
+      else if (kb == 0 && d > 0)
+        ss[o] = after * (1.f / B);
+      else if (kb > 0 && d > 0)
+        atomicAdd(&ss[o], after * (1.f / B));
+      low = before;
     }
   }
-  p.sums[(hb * 2) * p.seq + i] = av * (1.f / B);
-  p.sums[(hb * 2 + 1) * p.seq + i] = as * (1.f / B);
+  if (!half) {
+    if (b1 < nkb)
+      atomicAdd(&ss[t0 - (b1 - 1) * B - d], low * (1.f / B));
+    else if (d == 0)
+      ss[0] = low * (1.f / B);
+  }
 }
 
 // Kept keys / offsets -> key-block lists.  flags[b][n][2][nkb] come from the vector selection with rows of
