@@ -120,18 +120,20 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
 
 // Pass 2: a_v and a_s of one chunk of key blocks.  Queries are MFMA rows and keys columns (a wavefront owns 32 keys, one
 // per lane), so the vertical sums stay in a lane; the weights of 32 queries x B keys go through LDS, double buffered,
-// and thread (d, half) adds the wrapped diagonal key = (t + d) mod B of its 16 queries there, at consecutive addresses:
-// the part before the wrap belongs to offset t0 - s0 - d, the part after it to the offset B further up, which the
-// next lower key block finishes.  Only at the ends of a chunk do two workgroups add to one offset: two additions
+// each query's row shifted by its number so that a diagonal is a column (what a row leaves free stays zero): thread q
+// adds column q, all reads at fixed distances, into the block's 2B - 1 diagonals, of which the lower half joins the
+// upper half of the next key block.  (First written with a row's keys unshifted and two predicated sums per thread:
+// 734 us at 128K keys, 75 us at 8K.)  Only at the ends of a chunk do two workgroups add to one offset: two additions
 // to a cleared value, the same in either order.  Everything else is added in a fixed order.
-// Both passes, 128K keys, 32 heads of d 128: 2646 -> 972 us; 8K keys: 153 -> 97 us (with the slab -> now).
+// Both passes, 128K keys, 32 heads of d 128: 2646 -> 590 us; 8K keys: 153 -> 61 us (with the slab -> now).
 template <int D, int B>
 __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
-  constexpr int DS = D / 16, NT = B * 2, NQ = B / 32, PS = B + 8;
+  constexpr int DS = D / 16, NT = B * 2, NQ = B / 32;
+  constexpr int PS = B + 41;  // one float more than the distance of two writes: 4 (PS - 1) = 32 mod 64 banks
   __shared__ __attribute__((aligned(16))) char q_sh[B * D * 2];
   __shared__ __attribute__((aligned(16))) float pt[2][32 * PS];
   __shared__ __attribute__((aligned(16))) float mx_sh[B], inv_sh[B];
-  __shared__ float wrap_sh[2][B];
+  __shared__ float diag_sh[2 * B + 1];  // [t - key + B], entry 2B stays zero
   const int chunk = blockIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (vs_skip(p, b, n)) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, h = lane >> 5, c = lane & 31;
@@ -160,17 +162,20 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
       const float2 y = p.part[(hb * p.n_chunks + x) * B + d];
       vs_join(m, l, y.x, y.y);
     }
-    if (half) wrap_sh[0][d] = m, wrap_sh[1][d] = l;
+    if (half) diag_sh[d] = m, diag_sh[B + d] = l;
+    for (int x = tid; x < 64 * PS; x += NT) (&pt[0][0])[x] = 0.f;
     __syncthreads();
     if (!half) {
-      vs_join(m, l, wrap_sh[0][d], wrap_sh[1][d]);
+      vs_join(m, l, diag_sh[d], diag_sh[B + d]);
       mx_sh[d] = m;
       inv_sh[d] = 1.f / l;
+      diag_sh[d] = diag_sh[B + d] = 0.f;
+      if (d == 0) diag_sh[2 * B] = 0.f;
     }
     __syncthreads();
   }
   float *sv = p.sums + hb * 2 * p.seq, *ss = sv + p.seq;
-  float low = 0.f;  // diagonal sums before the wrap of the previous key block
+  float low = 0.f;  // lower diagonals of the previous key block
   for (int kb = b0; kb < b1; ++kb) {
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds) kf[ds] = kn[ds];
@@ -179,7 +184,8 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
       for (int ds = 0; ds < DS; ++ds)
         kn[ds] = *reinterpret_cast<const bf16x8 *>(kbase + (int64_t)(kb + 1) * B * p.k_st + 16 * ds);
     }
-    float av = 0.f, before = 0.f, after = 0.f;
+    const bool last = kb == nkb - 1;
+    float av = 0.f;
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
       f32x16 acc;
@@ -190,7 +196,7 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
         const bf16x8 a = *reinterpret_cast<const bf16x8 *>(q_sh + (qt * DS + ds) * 1024 + lane * 16);
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kf[ds], acc, 0, 0, 0);
       }
-      float *tile = pt[qt & 1];
+      float *put = pt[qt & 1] + 31 + 32 * w + c + 4 * h * (PS - 1);
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const int t = 8 * r4 + 4 * h;
@@ -200,27 +206,30 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float x = fast_exp2(__builtin_fmaf(acc[4 * r4 + e], p.c, -mm[e])) * ii[e];
-          if (kb == nkb - 1 && 32 * w + c > 32 * qt + t + e) x = 0.f;
+          if (last) x = (32 * w + c > 32 * qt + t + e) ? 0.f : x;
           av += x;
-          tile[(t + e) * PS + 32 * w + c] = x;
+          put[(8 * r4 + e) * (PS - 1)] = x;
         }
       }
       __syncthreads();
+      if (tid < B + 31) {
+        const float *get = pt[qt & 1] + tid;
+        float x0 = 0.f, x1 = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int tr = 16 * half + r, at = 32 * qt + tr + d;
-        const float x = tile[tr * PS + (at & (B - 1))];
-        before += (at < B) ? x : 0.f;
-        after += (at < B) ? 0.f : x;
+        for (int r = 0; r < 32; r += 2) {
+          x0 += get[r * PS];
+          x1 += get[(r + 1) * PS];
+        }
+        diag_sh[32 * qt + 31 - tid + B] += x0 + x1;
       }
     }
-    if (half) wrap_sh[0][d] = before, wrap_sh[1][d] = after;
     av = sum_xor32(av);
     if (h == 0) sv[kb * B + 32 * w + c] = av * (1.f / B);
     __syncthreads();
     if (!half) {
-      before += wrap_sh[0][d];
-      after += wrap_sh[1][d];
+      const float before = diag_sh[B - d], after = diag_sh[2 * B - d];
+      diag_sh[B - d] = 0.f;
+      diag_sh[2 * B - d] = 0.f;
       const int o = t0 - kb * B + B - d;  // offset that `after` and the previous block's `before` add up to
       if (kb > b0)
         ss[o] = (low + after) * (1.f / B);
