@@ -123,12 +123,22 @@ __device__ __forceinline__ void wait_vm() {
 // wavefronts of different workgroups and one's barrier / load-issue time is covered by the other.
 // At most 256 registers per lane (two wavefronts per SIMD) for every block size: without the bound the block 64
 // kernels spread over accumulation registers and paid moves for it (tiny layer 53.1 -> 50.0 us).
-template <int D, int B, bool DENSE, bool SCORES>
-__global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
-  constexpr int NW = B / 32;        // wavefronts per workgroup, 32 queries each
-  constexpr int SPB = B / KT;       // sub-tiles per key block
-  constexpr int IMG = KT * D * 2;   // bytes of a packed K (or V) image
-  constexpr int STAGE = 2 * IMG;    // K image + V image in the packed buffer
+//
+// SK: keys per sub-tile.  64, except for d 128 / block 64: a workgroup is two wavefronts there and its rings of 64-key
+// images take 80 KiB, so only one wavefront per SIMD fits; half images (32 keys) make it two.
+// G: groups of B / 32 wavefronts that share one query block, each with rings of its own and a run of the row's key
+// blocks; their (O, m, l) are joined in LDS at the end.  For launches that leave CUs idle under the longest rows.
+template <int D, int B>
+constexpr int attn_step_keys() { return (D == 128 && B == 64) ? 32 : 64; }
+template <int D, int B, bool DENSE, bool SCORES, int G>
+__global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
+  constexpr int SK = attn_step_keys<D, B>();
+  constexpr int NW = B / 32;        // wavefronts per group, 32 queries each
+  constexpr int SPB = B / SK;       // sub-tiles per key block
+  constexpr int NR = SK / 32;       // 32-key row blocks of S^T
+  constexpr int NKS = SK / 16;      // 16-key steps of the PV product
+  constexpr int IMG = SK * D * 2;   // bytes of a sub-tile of K (or V)
+  constexpr int PACKED = KT * D * 2;  // bytes of a packed K (or V) image of KT keys, K image then V image
   constexpr int DS = D / 16;        // k-steps of the QK^T product
   constexpr int DB = D / 32;        // 32-row blocks of O^T
   constexpr int DK = 2, DV = 2;                              // prefetch distances (steps)
@@ -139,12 +149,15 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // may still be in flight (vmcnt counts in order).
   constexpr int VM_KEEP = CH;
   static_assert(IMG % (1024 * NW) == 0, "image must split evenly over the wavefronts");
-  __shared__ __attribute__((aligned(1024))) char smem[(RK + RV) * IMG];
-  const uint32_t lds_k = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
-  const uint32_t lds_v = lds_k + RK * IMG;
+  constexpr int RING = (RK + RV) * IMG;
+  __shared__ __attribute__((aligned(1024))) char smem_all[G * RING];
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, kept scalar
+  const int wg_wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, kept scalar
+  const int grp = G > 1 ? wg_wave / NW : 0, w = G > 1 ? wg_wave % NW : wg_wave;
+  char *const smem = smem_all + grp * RING;
+  const uint32_t lds_k = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
+  const uint32_t lds_v = lds_k + RK * IMG;
   // workgroup -> (XCD, strand, query block, batch).  Workgroups are dealt round-robin to the 8 XCDs by the
   // hardware.  Every listed head is cut into 8 strands (the query blocks i with (nqb-1-i) % 8 == s, all of
   // about equal work and each spanning short and long rows); the 8n strands g = 8*slot + s, in slot-table
@@ -226,8 +239,16 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       list = p.kb_idx + lrow_id * nkb;
     }
   }
+  // this group's run of the row's entries: e0 .. e0 + nblk - 1; every group passes steps + 1 barriers
+  int e0 = 0, steps = nblk * SPB;
+  if (G > 1) {
+    steps = (nblk + G - 1) / G * SPB;
+    e0 = nblk * grp / G;
+    nblk = nblk * (grp + 1) / G - e0;
+    if (list) list += e0;
+  }
   const int nsub = nblk * SPB;
-  const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * STAGE;
+  const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * (2 * PACKED);
   float *lrow = nullptr;
   // block log-sum-exps: causal half, row i of a (batch entry, head) starts at i(i+1)/2 key-block slots
   const int64_t lws_row = ((int64_t)b * p.n_heads + hpos) * ((int64_t)p.nqb * (p.nqb + 1) / 2) + (int64_t)i * (i + 1) / 2;
@@ -237,41 +258,45 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // whatever the list holds)
   auto block_of = [&](int t) -> int {
     int e = (t < nsub ? t : nsub - 1) / SPB;
-    if (DENSE || list == nullptr) return e;
+    if (DENSE || list == nullptr) return e0 + e;
     const int j = list[e];
     return j < 0 ? 0 : (j > i ? i : j);
   };
   // what this wavefront has to do for sub-tile `sub` of key block j: 0 all of it, 1 causal mask, 2 nothing
   auto mode_of = [&](int j, int sub) -> int {
     if (j != i) return 0;
-    const int klo = KT * sub, qlo = 32 * w;
-    return (klo > qlo + 31) ? 2 : ((klo + KT - 1 <= qlo) ? 0 : 1);
+    const int klo = SK * sub, qlo = 32 * w;
+    return (klo > qlo + 31) ? 2 : ((klo + SK - 1 <= qlo) ? 0 : 1);
   };
-  // every wavefront moves CH chunks of the image of sub-tile t (clamped) into ring slot `slot_base`
+  // every wavefront moves CH chunks of sub-tile t (clamped) into ring slot `slot_base`; a half image is the first or
+  // second half of a packed K image, and of every 4 KiB (one 32-dim block) of a packed V image
   auto img_src = [&](int t, int j, bool is_v) -> const char * {
     const int tt = t < nsub ? t : nsub - 1;
-    return kvbase + (int64_t)(j * SPB + tt % SPB) * STAGE + (is_v ? IMG : 0) + (w * CH) * 1024;
+    const int key = j * B + (tt % SPB) * SK;
+    const char *src = kvbase + (int64_t)(key / KT) * (2 * PACKED) + (is_v ? PACKED : 0);
+    return SK == KT ? src : src + (key % KT) / SK * (is_v ? NKS * 1024 : IMG);
   };
   // chunk n (0 .. CH-1) of this wavefront's share of an image
-  auto issue_chunk = [&](const char *src, uint32_t slot_base, int n) {
-    lds_dma16(src + n * 1024, lane * 16, slot_base + (w * CH + n) * 1024);
+  auto issue_chunk = [&](const char *src, uint32_t slot_base, int n, bool is_v) {
+    const int q = w * CH + n;
+    lds_dma16(src + (SK == KT || !is_v ? q * 1024 : q / NKS * 4096 + q % NKS * 1024), lane * 16, slot_base + q * 1024);
   };
   auto issue_img = [&](int t, int j, bool is_v, uint32_t slot_base) {
     const char *src = img_src(t, j, is_v);
 #pragma unroll
-    for (int n = 0; n < CH; ++n) issue_chunk(src, slot_base, n);
+    for (int n = 0; n < CH; ++n) issue_chunk(src, slot_base, n, is_v);
   };
 
-  auto qk = [&](const char *kbuf, f32x16(&s)[2]) {
+  auto qk = [&](const char *kbuf, f32x16(&s)[NR]) {
     const char *kb = kbuf + lane * 16;
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[rb][r] = 0.f;
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
+      for (int rb = 0; rb < NR; ++rb) {
         const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kb + (rb * DS + ds) * 1024);
         s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s[rb], 0, 0, 0);
       }
@@ -292,30 +317,36 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // Online softmax, split in two halves that sit in different pipeline steps.
   // tile_max: (optionally causal-masked) row max of a freshly computed S tile; moves the running max,
   // rescales the running sums, returns alpha = 2^(m_old - m_new) for the O accumulators.
-  auto tile_max = [&](f32x16(&s)[2], int mode, int sub) -> float {
+  auto tile_max = [&](f32x16(&s)[NR], int mode, int sub) -> float {
     if (mode == 1) {
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
+      for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int kk = KT * sub + 32 * rb + 8 * (r >> 2) + 4 * h + (r & 3);
+          const int kk = SK * sub + 32 * rb + 8 * (r >> 2) + 4 * h + (r & 3);
           if (kk > tq) s[rb][r] = -INFINITY;
         }
     }
     float mx = fmaxf(s[0][0], s[0][1]);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
       for (int r = (rb == 0 ? 2 : 0); r < 16; r += 2) mx = fmaxf(mx, fmaxf(s[rb][r], s[rb][r + 1]));
     mx = max_xor32(mx);
     return move_reference(mx);
   };
+  auto sum_p = [&](const bf16x8(&pb)[NKS]) -> float {
+    float sum = sum_bf16x8(pb[0]);
+#pragma unroll
+    for (int ks = 1; ks < NKS; ++ks) sum += sum_bf16x8(pb[ks]);
+    return sum;
+  };
   // tile_exp: P = 2^(S*c - m) for a tile whose max is already folded into m; adds the row sums,
   // leaves P rounded to bf16 in pb (the B operand of the PV product)
-  auto tile_exp = [&](f32x16(&s)[2], bf16x8(&pb)[4]) {
+  auto tile_exp = [&](f32x16(&s)[NR], bf16x8(&pb)[NKS]) {
     float rs0 = 0.f, rs1 = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int ks = 0; ks < NKS; ++ks) {
       u32x4 t;
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) {
@@ -331,7 +362,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     const float rs = sum_xor32(rs0 + rs1);
     l += rs;
     bs += rs;
-    lc += sum_xor32(sum_bf16x8(pb[0]) + sum_bf16x8(pb[1]) + sum_bf16x8(pb[2]) + sum_bf16x8(pb[3])) - rs;
+    lc += sum_xor32(sum_p(pb)) - rs;
   };
   auto rescale = [&](float alpha) {
     if (__any(alpha != 1.f)) {
@@ -341,13 +372,13 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
         for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
     }
   };
-  auto pv = [&](const char *vbuf, const bf16x8(&pb)[4]) {
+  auto pv = [&](const char *vbuf, const bf16x8(&pb)[NKS]) {
     const char *vb = vbuf + lane * 16;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(vb + (db * 4 + ks) * 1024);
+        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(vb + (db * NKS + ks) * 1024);
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[ks], oacc[db], 0, 0, 0);
       }
   };
@@ -365,7 +396,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     issue_img(t + DV, jv, true, lds_v + ((t + DV) % RV) * IMG);
   };
   // fast step: tiles t and t+1 both off the diagonal.  One basic block up to the rescale test.
-  auto fast_step = [&](int t, int j0, int jv, int jk, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+  auto fast_step = [&](int t, int j0, int jv, int jk, f32x16(&s_cur)[NR], f32x16(&s_next)[NR]) {
     // the ring refills (K for the step after next, then V for the same step) are dropped one chunk at a time
     // into the MFMA groups below instead of going out in a burst after the barrier
     wait_vm<VM_KEEP>();
@@ -384,40 +415,41 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // The groups are expanded at compile time (static_for): left to the unroller, the d 128 / block 64 kernels kept
     // a run-time loop over register arrays, i.e. 320 B of scratch per lane (a gated layer of 2 x 8128 tokens, 32
     // heads: 49.2 ms, now 1.07 ms).
-    constexpr int NQ = 2 * DS, NP = 4 * DB, NM = NQ + NP;
+    constexpr int NQ = NR * DS, NP = NKS * DB, NM = NQ + NP, NU = SK / 4;  // NU: exp units (2 scores each)
     constexpr int PF = 4;       // LDS fragments read ahead of the MFMA that uses them
     constexpr int MAXTAIL = 4;  // the running-max update sits this many groups before the end
     auto frag = [&](int n) -> bf16x8 {
-      if (n < NQ) return *reinterpret_cast<const bf16x8 *>(kb + ((n % 2) * DS + n / 2) * 1024);
+      if (n < NQ) return *reinterpret_cast<const bf16x8 *>(kb + ((n % NR) * DS + n / NR) * 1024);
       const int np = n - NQ;
-      return *reinterpret_cast<const bf16x8 *>(vb + ((np % DB) * 4 + np / DB) * 1024);
+      return *reinterpret_cast<const bf16x8 *>(vb + ((np % DB) * NKS + np / DB) * 1024);
     };
     bf16x8 fr[PF + 1];
-    bf16x8 pb[4];
+    bf16x8 pb[NKS];
     u32x4 pt;
     float rs0 = 0.f, rs1 = 0.f, mx = 0.f, lval = 0.f, alpha = 1.f, rs_tile = 0.f;
     const bool care_t = care;  // set when this tile's max was taken
-    float xa[16], xb[16];
+    float xa[NU], xb[NU];
 #pragma unroll
     for (int n = 0; n < PF; ++n) fr[n] = frag(n);
     static_for<0, NM>([&](auto nc) __attribute__((always_inline)) {
       constexpr int n = decltype(nc)::value;
       if (n + PF < NM) fr[(n + PF) % (PF + 1)] = frag(n + PF);
       if (n < NQ) {
-        if (n < 2) {
+        if (n < NR) {
           f32x16 z;
 #pragma unroll
           for (int r = 0; r < 16; ++r) z[r] = 0.f;
           s_next[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[0], z, 0, 0, 0);
         } else {
-          s_next[n % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[n / 2], s_next[n % 2], 0, 0, 0);
+          s_next[n % NR] =
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[n / NR], s_next[n % NR], 0, 0, 0);
         }
       }
       // exp units u (2 scores each), three stages in consecutive groups so that no instruction waits
       // on the one just issued: scale+shift in group g(u), exp2 in g(u)+1, row sum + bf16 pack in g(u)+2
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int gu = u * NQ / 16;
+      for (int u = 0; u < NU; ++u) {
+        const int gu = u * NQ / NU;
         const int ks = u / 4, e2 = u % 4, r = 8 * (ks & 1) + 2 * e2;
         if (gu == n) {
           xa[u] = __builtin_fmaf(s_cur[ks >> 1][r], p.c, -m);
@@ -446,17 +478,17 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       }
       {
         constexpr int GAP = NM / (2 * CH);  // groups between two chunk loads
-        if (n % GAP == 1 && n / GAP < CH) issue_chunk(ksrc, kslot, n / GAP);
-        if (n % GAP == 1 && n / GAP >= CH && n / GAP < 2 * CH) issue_chunk(vsrc, vslot, n / GAP - CH);
+        if (n % GAP == 1 && n / GAP < CH) issue_chunk(ksrc, kslot, n / GAP, false);
+        if (n % GAP == 1 && n / GAP >= CH && n / GAP < 2 * CH) issue_chunk(vsrc, vslot, n / GAP - CH, true);
       }
       if (n >= NQ) {
         const int np = n - NQ;
         oacc[np % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], pb[np / DB], oacc[np % DB], 0, 0, 0);
-        // row max of S[t+1]: 16 max3 units spread over groups 2 .. NP-1-MAXTAIL, then the running-max
+        // row max of S[t+1]: NU max3 units spread over groups 2 .. NP-1-MAXTAIL, then the running-max
         // update MAXTAIL groups before the end (its dependent chain hides under the last MFMAs)
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          if (2 + u * (NP - 2 - MAXTAIL) / 16 != np) continue;
+        for (int u = 0; u < NU; ++u) {
+          if (2 + u * (NP - 2 - MAXTAIL) / NU != np) continue;
           const float a0 = s_next[u / 8][2 * (u % 8)], a1 = s_next[u / 8][2 * (u % 8) + 1];
           mx = (u == 0) ? fmaxf(a0, a1) : max3f(mx, a0, a1);
         }
@@ -465,12 +497,12 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       __builtin_amdgcn_sched_barrier(0);
     });
     if (__any(care_t))  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
-      lc += (sum_xor32(sum_bf16x8(pb[0]) + sum_bf16x8(pb[1]) + sum_bf16x8(pb[2]) + sum_bf16x8(pb[3])) - rs_tile) * alpha;
+      lc += (sum_xor32(sum_p(pb)) - rs_tile) * alpha;
     rescale(alpha);
     if (SCORES && t % SPB == SPB - 1 && h == 0) lrow[(int64_t)j0 * B] = lval;
   };
   // general step: per-wavefront causal mask / skip near the diagonal, optional next tile
-  auto slow_step = [&](int t, int j0, int j1, int jv, int jk, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+  auto slow_step = [&](int t, int j0, int j1, int jv, int jk, f32x16(&s_cur)[NR], f32x16(&s_next)[NR]) {
     sync_and_fill(t, jv, jk);
     const char *k_next = smem + ((t + 1) % RK) * IMG;
     const char *v_cur = smem + (RK + t % RV) * IMG;
@@ -479,7 +511,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     const int mode1 = (t + 1 < nsub) ? mode_of(j1, sub1) : 2;
     if (mode1 != 2) qk(k_next, s_next);
     if (mode0 != 2) {
-      bf16x8 pb[4];
+      bf16x8 pb[NKS];
       tile_exp(s_cur, pb);
       pv(v_cur, pb);
     }
@@ -494,7 +526,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // leading run of sub-tiles that lie before the first diagonal entry of the list
     int nfast;
     if (DENSE || list == nullptr) {
-      nfast = i * SPB;
+      nfast = (nblk < i - e0 ? nblk : i - e0) * SPB;
     } else {
       int first = nblk;
       for (int e = lane; e < nblk; e += 64)
@@ -509,7 +541,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // fast steps need tile t+1 off the diagonal too; keep their count even (tail starts on even parity)
     nfast = nfast > 0 ? ((nfast - 1) & ~1) : 0;
 
-    f32x16 s_a[2], s_b[2];
+    f32x16 s_a[NR], s_b[NR];
     // jw[n] = key block of sub-tile t + n
     int jw[6];
 #pragma unroll
@@ -551,9 +583,40 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     }
     wait_vm<0>();  // drain the ring's look-ahead loads before the LDS is reused or released
   }
+  if (G > 1) {
+    for (int n = nsub > 0 ? nsub + 1 : 0; n < (steps > 0 ? steps + 1 : 0); ++n) __builtin_amdgcn_s_barrier();
+    // join the groups: each but the first leaves m, l, lc and its O accumulators, [value][lane] per wavefront
+    constexpr int JN = 3 + DB * 16;
+    static_assert((G - 1) * NW * JN * 256 <= G * RING, "the groups' results must fit the idle rings");
+    float *const mine = reinterpret_cast<float *>(smem_all) + (wg_wave - NW) * (JN * 64) + lane;
+    __syncthreads();
+    if (grp > 0) {
+      mine[0] = m, mine[64] = l, mine[128] = lc;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[(3 + db * 16 + r) * 64] = oacc[db][r];
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll 1
+      for (int g = 1; g < G; ++g) {
+        const float *of = mine + g * NW * (JN * 64);
+        const float mg = of[0], mn = fmaxf(m, mg), ref = (mn == -INFINITY) ? 0.f : mn;
+        const float a0 = fast_exp2(m - ref), a1 = fast_exp2(mg - ref);
+        m = mn;
+        l = l * a0 + of[64] * a1;
+        lc = lc * a0 + of[128] * a1;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[db][r] = oacc[db][r] * a0 + of[(3 + db * 16 + r) * 64] * a1;
+      }
+    }
+  }
 
   // ---- output: O = O^T accumulators / l, rounded to bf16 ----
-  {
+  if (grp == 0) {
     const float inv = (l > 0.f) ? 1.f / (l + lc) : 0.f;
     uint16_t *op = p.o + (int64_t)b * p.o_sb + ((int64_t)i * B + tq) * p.o_st + (int64_t)head * p.o_sh;
 #pragma unroll
@@ -577,13 +640,14 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // score maps of 32 heads of 12352 tokens, d 64, block 64: 1200 us with it, 850 us without; 32K layer 3505 -> 3390.)
   if (SCORES) {
     constexpr int TPL = B / 64, PST = 65, JU = 8;
-    constexpr int JB = (1024 + NW * 32 * PST * 4 <= (RK + RV) * IMG) ? 32 : 16;  // key blocks per tile
+    constexpr int WV = NW * G;  // all wavefronts of the workgroup
+    constexpr int JB = (1024 + WV * 32 * PST * 4 <= G * RING) ? 32 : 16;  // key blocks per tile
     constexpr int NPART = 64 / JB, PLEN = 64 / NPART;  // stage 2: NPART lanes share a key block, PLEN entries each
-    static_assert(1024 + NW * JB * PST * 4 <= (RK + RV) * IMG, "score epilogue tiles must fit the idle rings");
-    float *lse_sh = reinterpret_cast<float *>(smem);  // [B]; the rings are idle now
-    float *part = reinterpret_cast<float *>(smem + 1024) + w * (JB * PST);
+    static_assert(1024 + WV * JB * PST * 4 <= G * RING, "score epilogue tiles must fit the idle rings");
+    float *lse_sh = reinterpret_cast<float *>(smem_all);  // [B]; the rings are idle now
+    float *part = reinterpret_cast<float *>(smem_all + 1024) + wg_wave * (JB * PST);
     __syncthreads();
-    if (h == 0) lse_sh[tq] = m + fast_log2(l);
+    if (h == 0 && grp == 0) lse_sh[tq] = m + fast_log2(l);
     __syncthreads();
     float lt[TPL];
 #pragma unroll
@@ -591,7 +655,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     const float *lblk = p.lws + lws_row * B;
     float *srow = p.scores + (((int64_t)b * p.n_heads + hpos) * p.nqb + i) * nkb;
     const int jr = lane % JB, jp = lane / JB;
-    for (int j0 = w * JB; j0 <= i; j0 += NW * JB) {
+    for (int j0 = wg_wave * JB; j0 <= i; j0 += WV * JB) {
 #pragma unroll
       for (int u0 = 0; u0 < JB; u0 += JU) {
         float x[JU][TPL];
@@ -623,7 +687,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    for (int j = i + 1 + w * 64 + lane; j < nkb; j += NW * 64) srow[j] = 0.f;
+    for (int j = i + 1 + wg_wave * 64 + lane; j < nkb; j += WV * 64) srow[j] = 0.f;
   }
 }
 
