@@ -500,9 +500,19 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
   g.per_head = 2;
   const int n_maps = s->batch * n * 2;
   const uint32_t gq = (uint32_t)rintf(gamma * 16777216.f);
-  launch_gsel_threshold(vp.sums, n_maps, g, gq, vs_ws + L.gsel, st);
-  hipLaunchKernelGGL(gsel_emit_flags_kernel, dim3((nkb + 3) / 4, n_maps), dim3(256), 0, st, vp.sums, g,
-                     vs_ws + L.gsel, flags, keep_bits);
+  // One launch for vectors of up to 16K entries, where the eight launches are latency: 64 vectors of 8K 597 -> 578 us
+  // of the whole call, of 16K 1650 -> 1625, 8 of 16K 144 -> 139.  Beyond, a workgroup per vector is too few: 8 vectors of
+  // 32K 262 -> 264, of 128K 7030 -> 7190.
+  if (s->seq <= GSEL_VECTOR_MAX) {
+    if (s->block == 128)
+      hipLaunchKernelGGL(gsel_vector_kernel<2>, dim3(n_maps), dim3(1024), 0, st, vp.sums, g, gq, flags, keep_bits);
+    else
+      hipLaunchKernelGGL(gsel_vector_kernel<1>, dim3(n_maps), dim3(1024), 0, st, vp.sums, g, gq, flags, keep_bits);
+  } else {
+    launch_gsel_threshold(vp.sums, n_maps, g, gq, vs_ws + L.gsel, st);
+    hipLaunchKernelGGL(gsel_emit_flags_kernel, dim3((nkb + 3) / 4, n_maps), dim3(256), 0, st, vp.sums, g,
+                       vs_ws + L.gsel, flags, keep_bits);
+  }
   if (kb_idx)  // the pattern at block granularity (not needed by the token-level attention)
     hipLaunchKernelGGL(vs_block_lists_kernel, dim3((nkb + 3) / 4, n, s->batch), dim3(256), 0, st, vp, flags, nkb,
                        forced, by_head, kb_idx, kb_cnt);

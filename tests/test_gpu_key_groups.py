@@ -82,3 +82,18 @@ def test_search_chunks(d, B, nkb):
         _sum_check(sums_h[n, 0], a_v, f"head {h} a_v")
         _sum_check(sums_h[n, 1], a_s, f"head {h} a_s")
     _check_lists(oracle, sums_h, idx.cpu().numpy()[0], cnt.cpu().numpy()[0], B, 0.8, True, f"nkb {nkb}")
+
+
+# vectors of 16384 entries are selected in one launch, longer ones over several; ties: all keys alike
+@pytest.mark.parametrize("B,nkb", [(128, 128), (64, 256), (64, 257)])
+@pytest.mark.parametrize("alike", [False, True])
+def test_vector_selection_at_the_edge_of_the_single_launch(B, nkb, alike):
+    import oracle
+    import paper_2505_19578_amd as sp
+    from synth import random_qkv
+    from tests.gpu_util import to_dev
+    qb, kb, _ = random_qkv(89, nkb * B, 2, 1, 64, 2.5)
+    if alike:
+        kb[1:] = kb[:1]
+    _, sums_h, idx, cnt = _search(sp, to_dev(qb), to_dev(kb), B, [0, 1], 0.6, False)
+    _check_lists(oracle, sums_h, idx.cpu().numpy()[0], cnt.cpu().numpy()[0], B, 0.6, False, f"nkb {nkb}")
