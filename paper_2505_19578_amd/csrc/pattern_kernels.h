@@ -25,8 +25,23 @@ struct PoolParams {
   float *out;        // [b][n][n_rows][nqb] row softmax of the block-mean logits
   float c_full, c_diag;
   const int32_t *head_dev;  // optional [b][n_heads]: head of listed position n chosen on the device, < 0 = empty
+  // optional, one wanted row (n_rows == 1): the row's distances for the pivot election, js[b][n][2] = d_sparse and, if
+  // the dictionary has an entry for the head's cluster, d_sim against its representative
+  double *js;
+  const int32_t *dict_valid;  // [b][n_clusters]
+  const float *dict_a_tilde;  // [b][n_clusters][nqb]
+  int n_clusters;
   int32_t head_ids[SP_MAX_HEADS];
+  int32_t head_cluster[SP_MAX_HEADS];  // with js: dictionary cluster of listed position n, or -1
 };
+// x ln(x/m) + y ln(y/m), m = (x+y)/2: one entry's contribution to 2*JSD, never negative
+__device__ __forceinline__ double js_term(double x, double y) {
+  const double m = 0.5 * (x + y);
+  double t = 0.0;
+  if (x > 0.0) t += x * log(x / m);
+  if (y > 0.0) t += y * log(y / m);
+  return t;
+}
 __device__ __forceinline__ int pool_head(const PoolParams &p, int b, int n) {
   return p.head_dev ? p.head_dev[(int64_t)b * p.n_heads + n] : p.head_ids[n];
 }
@@ -85,6 +100,9 @@ __global__ __launch_bounds__(D) void query_pool_kernel(PoolParams p) {
 // (block index fastest in ksumT, so the loads coalesce), then one wavefront per row applies the row
 // softmax in place (Alg. 2, first step; Alg. 3's estimate when only the last row is asked for).
 // Entries beyond the diagonal are written as 0.
+// With js the workgroup of a head goes on to its Jensen-Shannon distances: about 600 fp64 logarithms per head at 313
+// blocks, which elect_kernel's single workgroup took for all heads in turn (32 heads: four dictionary layers of 64K
+// 34.98 -> 34.70 ms, three of 2K 539 -> 525 us).
 template <int D>
 __global__ __launch_bounds__(256) void mean_logit_softmax_kernel(PoolParams p) {
   constexpr int R = 4;
@@ -120,18 +138,45 @@ __global__ __launch_bounds__(256) void mean_logit_softmax_kernel(PoolParams p) {
     }
   }
   __syncthreads();
-  if (r0 + w >= p.n_rows) return;
-  const int i = p.row0 + r0 + w;
-  float *row = p.out + (hb * p.n_rows + r0 + w) * nqb;
-  float mx = -INFINITY;
-  for (int j = lane; j <= i; j += 64) mx = fmaxf(mx, row[j]);
+  if (r0 + w < p.n_rows) {
+    const int i = p.row0 + r0 + w;
+    float *row = p.out + (hb * p.n_rows + r0 + w) * nqb;
+    float mx = -INFINITY;
+    for (int j = lane; j <= i; j += 64) mx = fmaxf(mx, row[j]);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  float den = 0.f;
-  for (int j = lane; j <= i; j += 64) den += expf(row[j] - mx);
+    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float den = 0.f;
+    for (int j = lane; j <= i; j += 64) den += expf(row[j] - mx);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
-  for (int j = lane; j < nqb; j += 64) row[j] = (j <= i) ? expf(row[j] - mx) / den : 0.f;
+    for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
+    for (int j = lane; j < nqb; j += 64) row[j] = (j <= i) ? expf(row[j] - mx) / den : 0.f;
+  }
+  if (!p.js) return;
+  __shared__ double part[4][2];
+  __syncthreads();
+  const int c = p.head_cluster[n];
+  const float *row = p.out + hb * nqb;
+  const float *ref = (c >= 0 && p.dict_valid[(int64_t)b * p.n_clusters + c])
+                         ? p.dict_a_tilde + ((int64_t)b * p.n_clusters + c) * nqb
+                         : nullptr;
+  const double u = 1.0 / (double)nqb;
+  double s0 = 0.0, s1 = 0.0;
+  for (int j = tid; j < nqb; j += 256) {
+    const double a = (double)row[j];
+    s0 += js_term(a, u);
+    if (ref) s1 += js_term(a, (double)ref[j]);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    s0 += __shfl_xor(s0, off, 64);
+    s1 += __shfl_xor(s1, off, 64);
+  }
+  if (lane == 0) part[w][0] = s0, part[w][1] = s1;
+  __syncthreads();
+  if (tid < 2) {
+    const double jsd = 0.5 * ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
+    p.js[hb * 2 + tid] = sqrt(jsd > 0.0 ? jsd : 0.0);
+  }
 }
 
 // ---- Alg. 3 (Determine Sparse Pattern): Jensen-Shannon gate ------------------------------------
@@ -146,14 +191,6 @@ struct GateParams {
   int32_t shared_map[SP_MAX_HEADS];  // value written when the pattern is shared
 };
 
-// x ln(x/m) + y ln(y/m), m = (x+y)/2: one entry's contribution to 2*JSD, never negative
-__device__ __forceinline__ double js_term(double x, double y) {
-  const double m = 0.5 * (x + y);
-  double t = 0.0;
-  if (x > 0.0) t += x * log(x / m);
-  if (y > 0.0) t += y * log(y / m);
-  return t;
-}
 // sqrt(JSD(a || ref)) over n entries, natural logarithm, fp64; ref == nullptr: the uniform distribution.
 // Called by a whole wavefront; every lane returns the result.
 __device__ __forceinline__ double js_distance_wave(const float *a, const float *ref, int n, int lane) {
@@ -187,6 +224,7 @@ __global__ __launch_bounds__(64) void js_gate_kernel(GateParams p) {
 // (dense, no update), -2 is elected pivot of its cluster in this layer (dense + pattern construction).
 struct ElectParams {
   const float *a_hat;   // [b][Hq][nkb] last-row estimates of every head
+  const double *js;     // [b][Hq][2] d_sparse; d_sim where the dictionary already has the head's cluster; or null
   float *dist;          // [b][Hq][2]
   int32_t *role;        // [b][Hq]
   int32_t *pivot_head;  // [b][n_slots] head elected for the slot's cluster in this layer, or -1
@@ -218,9 +256,14 @@ __global__ __launch_bounds__(1024) void elect_kernel(ElectParams p) {
   __shared__ int had[SP_MAX_HEADS];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const float *ah = p.a_hat + (int64_t)b * p.n_q_heads * p.nkb;
-  for (int h = w; h < p.n_q_heads; h += 16) {
-    const double d = js_distance_wave(ah + (int64_t)h * p.nkb, nullptr, p.nkb, lane);
-    if (lane == 0) ds[h] = d;
+  const double *js = p.js + (int64_t)b * p.n_q_heads * 2;
+  if (p.js) {
+    for (int h = tid; h < p.n_q_heads; h += 1024) ds[h] = js[2 * h];
+  } else {
+    for (int h = w; h < p.n_q_heads; h += 16) {
+      const double d = js_distance_wave(ah + (int64_t)h * p.nkb, nullptr, p.nkb, lane);
+      if (lane == 0) ds[h] = d;
+    }
   }
   __syncthreads();
   if (tid < p.n_slots) {
@@ -254,7 +297,7 @@ __global__ __launch_bounds__(1024) void elect_kernel(ElectParams p) {
         const float *ref = had[s] ? p.a_tilde + ((int64_t)b * p.n_clusters + c) * p.nkb
                                   : (piv[s] >= 0 && piv[s] < h ? ah + (int64_t)piv[s] * p.nkb : nullptr);
         if (ref) {
-          d_sim = js_distance_wave(ah + (int64_t)h * p.nkb, ref, p.nkb, lane);
+          d_sim = had[s] && p.js ? js[2 * h + 1] : js_distance_wave(ah + (int64_t)h * p.nkb, ref, p.nkb, lane);
           if (ds[h] < (double)p.delta && d_sim < (double)p.tau) role = c;
         }
       }

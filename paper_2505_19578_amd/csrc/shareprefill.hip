@@ -329,10 +329,11 @@ sp_status launch_mask(const float *scores, int n_maps, int nqb, int nkb, float g
 }
 
 // row softmax of the block-mean logits of the listed heads, query-block rows row0 .. row0+n_rows-1,
-// into out[b][n][n_rows][nkb]
+// into out[b][n][n_rows][nkb]; elect (all heads listed, one row): also the distances the election needs, left at
+// elect->js in pattern_ws
 sp_status launch_mean_logit_scores(const sp_shape *s, const void *q, const void *k, const int32_t *heads, int n,
                                    int row0, int n_rows, float *out, char *pattern_ws, hipStream_t st,
-                                   const int32_t *head_dev = nullptr) {
+                                   const int32_t *head_dev = nullptr, ElectParams *elect = nullptr) {
   if ((int64_t)s->batch * n > 65535) {
     set_err("batch * heads = %lld exceeds 65535", (long long)s->batch * n);
     return SP_ERR_UNSUPPORTED;
@@ -361,6 +362,15 @@ sp_status launch_mean_logit_scores(const sp_shape *s, const void *q, const void 
   pp.out = out;
   pp.head_dev = head_dev;
   for (int a = 0; a < n; ++a) pp.head_ids[a] = heads ? heads[a] : 0;
+  if (elect) {
+    // the selection scratch is idle here and larger than two doubles per head (see gsel_map_bytes)
+    pp.js = (double *)(pattern_ws + L.gsel);
+    pp.dict_valid = elect->valid;
+    pp.dict_a_tilde = elect->a_tilde;
+    pp.n_clusters = elect->n_clusters;
+    for (int a = 0; a < n; ++a) pp.head_cluster[a] = elect->head_cluster[heads[a]];
+    elect->js = pp.js;
+  }
   const float scale = (s->softmax_scale > 0.f) ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   const float B = (float)s->block;
   pp.c_full = scale / (B * B);
@@ -1319,7 +1329,6 @@ sp_status sp_prefill_layer_dict(const sp_shape *shape, const void *q, const void
   // 1. Alg. 3: every head's last-row estimate, then roles (election / sharing / fallback) on the device
   int32_t all[SP_MAX_HEADS];
   for (int hq = 0; hq < Hq; ++hq) all[hq] = hq;
-  if ((rc = launch_mean_logit_scores(shape, q, k, all, Hq, nqb - 1, 1, a_hat, ws + off_pat, st))) return rc;
   ep.a_hat = a_hat;
   ep.dist = dist;
   ep.role = role;
@@ -1341,6 +1350,11 @@ sp_status sp_prefill_layer_dict(const sp_shape *shape, const void *q, const void
   ep.n_clusters = dict->n_clusters;
   ep.delta = delta;
   ep.tau = tau;
+  // elect_kernel has a wavefront for each of 16 heads: only with more of them do the distances belong to the estimates'
+  // kernel (4 heads of 43 blocks, two layers: 281 us without, 282 with)
+  if ((rc = launch_mean_logit_scores(shape, q, k, all, Hq, nqb - 1, 1, a_hat, ws + off_pat, st, nullptr,
+                                     Hq > 16 ? &ep : nullptr)))
+    return rc;
   {
     ProfScope prof(KK_SCORE, st);
     hipLaunchKernelGGL(elect_kernel, dim3(shape->batch), dim3(1024), 0, st, ep);
