@@ -126,14 +126,16 @@ __device__ __forceinline__ void wait_vm() {
 //
 // SK: keys per sub-tile.  64, except for d 128 / block 64: a workgroup is two wavefronts there and its rings of 64-key
 // images take 80 KiB, so only one wavefront per SIMD fits; half images (32 keys) make it two.
-// G: groups of B / 32 wavefronts that share one query block, each with rings of its own and a run of the row's key
-// blocks; their (O, m, l) are joined in LDS at the end.  For launches that leave CUs idle under the longest rows.
+//
+// One workgroup walks the whole row, whatever else the launch holds: groups of wavefronts that walked a part of the row
+// each and were joined at the end (for launches of at most one wavefront per SIMD: 45 -> 35.5 us of a tiny layer) had
+// references of their own, so that a head's output depended on how many heads and batch entries were in the call.
 template <int D, int B>
 constexpr int attn_step_keys() { return (D == 128 && B == 64) ? 32 : 64; }
-template <int D, int B, bool DENSE, bool SCORES, int G>
-__global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
+template <int D, int B, bool DENSE, bool SCORES>
+__global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   constexpr int SK = attn_step_keys<D, B>();
-  constexpr int NW = B / 32;        // wavefronts per group, 32 queries each
+  constexpr int NW = B / 32;        // wavefronts per workgroup, 32 queries each
   constexpr int SPB = B / SK;       // sub-tiles per key block
   constexpr int NR = SK / 32;       // 32-key row blocks of S^T
   constexpr int NKS = SK / 16;      // 16-key steps of the PV product
@@ -149,15 +151,12 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
   // may still be in flight (vmcnt counts in order).
   constexpr int VM_KEEP = CH;
   static_assert(IMG % (1024 * NW) == 0, "image must split evenly over the wavefronts");
-  constexpr int RING = (RK + RV) * IMG;
-  __shared__ __attribute__((aligned(1024))) char smem_all[G * RING];
-
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-  const int wg_wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, kept scalar
-  const int grp = G > 1 ? wg_wave / NW : 0, w = G > 1 ? wg_wave % NW : wg_wave;
-  char *const smem = smem_all + grp * RING;
+  __shared__ __attribute__((aligned(1024))) char smem[(RK + RV) * IMG];
   const uint32_t lds_k = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
   const uint32_t lds_v = lds_k + RK * IMG;
+
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, kept scalar
   // workgroup -> (XCD, strand, query block, batch).  Workgroups are dealt round-robin to the 8 XCDs by the
   // hardware.  Every listed head is cut into 8 strands (the query blocks i with (nqb-1-i) % 8 == s, all of
   // about equal work and each spanning short and long rows); the 8n strands g = 8*slot + s, in slot-table
@@ -239,14 +238,6 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
       list = p.kb_idx + lrow_id * nkb;
     }
   }
-  // this group's run of the row's entries: e0 .. e0 + nblk - 1; every group passes steps + 1 barriers
-  int e0 = 0, steps = nblk * SPB;
-  if (G > 1) {
-    steps = (nblk + G - 1) / G * SPB;
-    e0 = nblk * grp / G;
-    nblk = nblk * (grp + 1) / G - e0;
-    if (list) list += e0;
-  }
   const int nsub = nblk * SPB;
   const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * (2 * PACKED);
   float *lrow = nullptr;
@@ -258,7 +249,7 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
   // whatever the list holds)
   auto block_of = [&](int t) -> int {
     int e = (t < nsub ? t : nsub - 1) / SPB;
-    if (DENSE || list == nullptr) return e0 + e;
+    if (DENSE || list == nullptr) return e;
     const int j = list[e];
     return j < 0 ? 0 : (j > i ? i : j);
   };
@@ -526,7 +517,7 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
     // leading run of sub-tiles that lie before the first diagonal entry of the list
     int nfast;
     if (DENSE || list == nullptr) {
-      nfast = (nblk < i - e0 ? nblk : i - e0) * SPB;
+      nfast = i * SPB;
     } else {
       int first = nblk;
       for (int e = lane; e < nblk; e += 64)
@@ -583,40 +574,9 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
     }
     wait_vm<0>();  // drain the ring's look-ahead loads before the LDS is reused or released
   }
-  if (G > 1) {
-    for (int n = nsub > 0 ? nsub + 1 : 0; n < (steps > 0 ? steps + 1 : 0); ++n) __builtin_amdgcn_s_barrier();
-    // join the groups: each but the first leaves m, l, lc and its O accumulators, [value][lane] per wavefront
-    constexpr int JN = 3 + DB * 16;
-    static_assert((G - 1) * NW * JN * 256 <= G * RING, "the groups' results must fit the idle rings");
-    float *const mine = reinterpret_cast<float *>(smem_all) + (wg_wave - NW) * (JN * 64) + lane;
-    __syncthreads();
-    if (grp > 0) {
-      mine[0] = m, mine[64] = l, mine[128] = lc;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(3 + db * 16 + r) * 64] = oacc[db][r];
-    }
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll 1
-      for (int g = 1; g < G; ++g) {
-        const float *of = mine + g * NW * (JN * 64);
-        const float mg = of[0], mn = fmaxf(m, mg), ref = (mn == -INFINITY) ? 0.f : mn;
-        const float a0 = fast_exp2(m - ref), a1 = fast_exp2(mg - ref);
-        m = mn;
-        l = l * a0 + of[64] * a1;
-        lc = lc * a0 + of[128] * a1;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[db][r] = oacc[db][r] * a0 + of[(3 + db * 16 + r) * 64] * a1;
-      }
-    }
-  }
 
   // ---- output: O = O^T accumulators / l, rounded to bf16 ----
-  if (grp == 0) {
+  {
     const float inv = (l > 0.f) ? 1.f / (l + lc) : 0.f;
     uint16_t *op = p.o + (int64_t)b * p.o_sb + ((int64_t)i * B + tq) * p.o_st + (int64_t)head * p.o_sh;
 #pragma unroll
@@ -640,14 +600,13 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
   // score maps of 32 heads of 12352 tokens, d 64, block 64: 1200 us with it, 850 us without; 32K layer 3505 -> 3390.)
   if (SCORES) {
     constexpr int TPL = B / 64, PST = 65, JU = 8;
-    constexpr int WV = NW * G;  // all wavefronts of the workgroup
-    constexpr int JB = (1024 + WV * 32 * PST * 4 <= G * RING) ? 32 : 16;  // key blocks per tile
+    constexpr int JB = (1024 + NW * 32 * PST * 4 <= (RK + RV) * IMG) ? 32 : 16;  // key blocks per tile
     constexpr int NPART = 64 / JB, PLEN = 64 / NPART;  // stage 2: NPART lanes share a key block, PLEN entries each
-    static_assert(1024 + WV * JB * PST * 4 <= G * RING, "score epilogue tiles must fit the idle rings");
-    float *lse_sh = reinterpret_cast<float *>(smem_all);  // [B]; the rings are idle now
-    float *part = reinterpret_cast<float *>(smem_all + 1024) + wg_wave * (JB * PST);
+    static_assert(1024 + NW * JB * PST * 4 <= (RK + RV) * IMG, "score epilogue tiles must fit the idle rings");
+    float *lse_sh = reinterpret_cast<float *>(smem);  // [B]; the rings are idle now
+    float *part = reinterpret_cast<float *>(smem + 1024) + w * (JB * PST);
     __syncthreads();
-    if (h == 0 && grp == 0) lse_sh[tq] = m + fast_log2(l);
+    if (h == 0) lse_sh[tq] = m + fast_log2(l);
     __syncthreads();
     float lt[TPL];
 #pragma unroll
@@ -655,7 +614,7 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
     const float *lblk = p.lws + lws_row * B;
     float *srow = p.scores + (((int64_t)b * p.n_heads + hpos) * p.nqb + i) * nkb;
     const int jr = lane % JB, jp = lane / JB;
-    for (int j0 = wg_wave * JB; j0 <= i; j0 += WV * JB) {
+    for (int j0 = w * JB; j0 <= i; j0 += NW * JB) {
 #pragma unroll
       for (int u0 = 0; u0 < JB; u0 += JU) {
         float x[JU][TPL];
@@ -687,7 +646,7 @@ __global__ __launch_bounds__(B * 2 * G, 2) void attn_kernel(AttnParams p) {
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    for (int j = i + 1 + wg_wave * 64 + lane; j < nkb; j += WV * 64) srow[j] = 0.f;
+    for (int j = i + 1 + w * 64 + lane; j < nkb; j += NW * 64) srow[j] = 0.f;
   }
 }
 

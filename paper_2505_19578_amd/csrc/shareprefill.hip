@@ -275,27 +275,12 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
   dim3 grid((unsigned)nwg);
   const bool sc = DENSE && ap.scores != nullptr;
   ProfScope prof(DENSE ? KK_DENSE : KK_SPARSE, st);
-  // Key groups inside a workgroup (8 wavefronts on one query block) while the launch has at most one wavefront per
-  // SIMD without them: the longest rows then are the launch's time.  Measured without -> with: d 64 / block 64, 8 heads
-  // of 2048 tokens dense 36.9 -> 26.6 us, 8 of 8192 (2048 wavefronts) 144.5 -> 139.9, 16 of 8192 214.7 -> 260.1; d 128 /
-  // block 128, 8 heads of 4096 80.9 -> 74.8, 16 of 4096 (2048) 100.7 -> 101.7.  Lists leave rows of about equal length,
-  // so with blocks of 64 (4 groups) they fill the chip from half as many: 512 wavefronts 51.9 -> 35.0, 1024 48.0 ->
-  // 50.4.  Below 8 query blocks (block 128: 22.9 -> 24.2 us at 4) joining the groups costs more than it saves.
-  const int64_t waves = (int64_t)s->batch * n * ap.nqb * (s->block / 32);
-  const bool split = ap.nqb >= 8 && waves <= (!DENSE && s->block == 64 ? 512 : 1024);
-#define SP_LAUNCH_G(D_, B_, G_)                                                                                  \
-  do {                                                                                                           \
-    if (sc)                                                                                                      \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, true, true, G_>), grid, dim3(B_ * 2 * G_), 0, st, ap);             \
-    else                                                                                                         \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false, G_>), grid, dim3(B_ * 2 * G_), 0, st, ap);           \
-  } while (0)
-#define SP_LAUNCH(D_, B_)                \
-  do {                                   \
-    if (split)                           \
-      SP_LAUNCH_G(D_, B_, 256 / B_);     \
-    else                                 \
-      SP_LAUNCH_G(D_, B_, 1);            \
+#define SP_LAUNCH(D_, B_)                                                                           \
+  do {                                                                                              \
+    if (sc)                                                                                         \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, true, true>), grid, dim3(B_ * 2), 0, st, ap);        \
+    else                                                                                            \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false>), grid, dim3(B_ * 2), 0, st, ap);      \
   } while (0)
   if (s->head_dim == 128 && s->block == 128)
     SP_LAUNCH(128, 128);
@@ -305,7 +290,6 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
     SP_LAUNCH(64, 128);
   else
     SP_LAUNCH(64, 64);
-#undef SP_LAUNCH_G
 #undef SP_LAUNCH
   return hip_check(hipGetLastError(), DENSE ? "dense attn_kernel launch" : "sparse attn_kernel launch");
 }

@@ -1,0 +1,47 @@
+"""What a head gives does not depend on what else is in the call: its output, score map and search sums are the same
+bits whether it is listed alone, beside fifteen others or in a batch of two (a row has one order of tiles and sums)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HQ, HK = 16, 4
+
+
+def _inputs(seed, N, d, batch=2):
+    import torch
+    from synth import random_qkv
+    from tests.gpu_util import to_dev
+    q, k, v = zip(*[[to_dev(x) for x in random_qkv(seed + b, N, HQ, HK, d, 2.0)] for b in range(batch)])
+    return torch.cat(q), torch.cat(k), torch.cat(v)
+
+
+# the launches of the two calls differ 16-fold: 2 x 16 heads of 4096 tokens fill the chip, 2 heads leave it idle
+@pytest.mark.parametrize("d,B,nqb", [(128, 128, 32), (64, 128, 32), (128, 64, 64), (64, 64, 64)])
+def test_attention_of_a_head_alone_and_among_others(d, B, nqb):
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, v = _inputs(31, nqb * B, d)
+    g = torch.Generator().manual_seed(7)
+    keep = torch.rand((2, 2, nqb, nqb), generator=g) < 0.4
+    keep |= torch.eye(nqb, dtype=torch.bool)
+    keep &= torch.ones(nqb, nqb, dtype=torch.bool).tril()
+    key = torch.where(keep, torch.arange(nqb), nqb).sort(dim=-1).values
+    idx, cnt = torch.where(key < nqb, key, -1).int().cuda(), keep.sum(-1, dtype=torch.int32).cuda()
+
+    def run(q, k, v, heads, idx, cnt):
+        shape, b, n = sp.shape_of(q, k, None, B), q.shape[0], len(heads)
+        ws = torch.empty(sp.sp_workspace_bytes(shape, n), dtype=torch.uint8, device="cuda")
+        o, ol = torch.zeros_like(q), torch.zeros_like(q)
+        sc = torch.full((b, n, nqb, nqb), -1.0, dtype=torch.float32, device="cuda")
+        sp.sp_dense_attn_with_block_scores(shape, q, k, v, heads, o, sc, ws)
+        sp.sp_block_sparse_attn(shape, q, k, v, heads, [h % 2 for h in heads], idx, cnt, 2, ol, ws)
+        torch.cuda.synchronize()
+        return o[:, :, heads], sc, ol[:, :, heads]
+
+    everything = run(q, k, v, list(range(HQ)), idx, cnt)
+    few = [3, 8]
+    for b in range(2):
+        alone = run(q[b:b + 1], k[b:b + 1], v[b:b + 1], few, idx[b:b + 1].contiguous(), cnt[b:b + 1].contiguous())
+        for what, a, e in zip(("dense output", "score map", "output over lists"), alone, everything):
+            e = e[b:b + 1, few] if what == "score map" else e[b:b + 1][:, :, few]
+            assert torch.equal(a, e), f"{what}, batch entry {b}: {int((a != e).sum())} of {a.numel()} differ"

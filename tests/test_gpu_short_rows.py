@@ -1,6 +1,6 @@
-"""Workgroups of several key groups on one query block (launches of few wavefronts) and the chunked vertical-slash
-search, at the sizes where their splits leave remainders: rows shorter than the number of groups, groups without a key
-block, lists without the diagonal, a last chunk of one key block, a single chunk per head.
+"""Attention over rows of few key blocks (lists of every length from none, with and without the diagonal) and the
+chunked vertical-slash search, at the sizes where their loops leave remainders: rows of less than a step, an odd number
+of sub-tiles, a last chunk of one key block, a single chunk per head.
 Bars: every output within its rounding bound.  Weights and outputs are rounded to bf16 (relative error 2^-9 each), sums
 are fp32: the numerator is off by at most 2^-9 max|V|, the normaliser by 2^-9, i.e. by 2^-9 |O| <= 2^-9 max|V| of the
 output, the stored output by 2^-9 |O| (these peaked inputs have outputs above 4, where one bf16 half step is 0.0156
@@ -21,10 +21,10 @@ def _check_out(got, want, v, what):
     assert np.all(err <= bound) and err.mean() <= OUT_MEAN, (what, float((err / bound).max()), float(err.mean()))
 
 
-# 8 query blocks are the fewest that are split; 9 and 11 leave remainders for two and for four groups
+# odd and even numbers of query blocks: 7 is one row per strand but the last, 8 one each, 9 and 11 leave strands short
 @pytest.mark.parametrize("d,B", [(128, 128), (128, 64), (64, 128), (64, 64)])
 @pytest.mark.parametrize("nqb", [7, 8, 9, 11])
-def test_split_rows_dense_and_lists(d, B, nqb):
+def test_short_rows_dense_and_lists(d, B, nqb):
     import torch
     import oracle
     import paper_2505_19578_amd as sp
