@@ -110,7 +110,7 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Flash-attention sweep over 64-key sub-tiles t = 0 .. nsub-1, 32 queries per wavefront.
+// Flash-attention sweep over 64-key tiles t = 0 .. nsub-1, 32 queries per wavefront.
 //
 // Software pipeline (per wavefront), step t:
 //     MFMA stream   S[t+1] = K[t+1] Q^T          then   O += V[t]^T P[t]^T
@@ -124,30 +124,36 @@ __device__ __forceinline__ void wait_vm() {
 // At most 256 registers per lane (two wavefronts per SIMD) for every block size: without the bound the block 64
 // kernels spread over accumulation registers and paid moves for it (tiny layer 53.1 -> 50.0 us).
 //
-// SK: keys per sub-tile.  64, except for d 128 / block 64: a workgroup is two wavefronts there and its rings of 64-key
-// images take 80 KiB, so only one wavefront per SIMD fits; half images (32 keys) make it two.
+// SK: keys of a ring image.  64, except for d 128 / block 64: a workgroup is two wavefronts there and its rings of 64-key
+// images take 80 KiB, so only one wavefront per SIMD fits; half images (32 keys) make it two (gated layer of 2 x 8128
+// tokens, 32 heads: 980 us with whole images, 856 us with halves).  A step of a half image is half of a tile's step: its
+// S, P and PV.  The reference still moves once per 64-key tile, the row sums and O are added up in the same order, so the
+// results are the bits that steps of whole images give.  (Tiles of 32 keys had moved the reference twice as often, at
+// 886 us, and rounded the weights at other points than the other block size.)
 //
 // One workgroup walks the whole row, whatever else the launch holds: groups of wavefronts that walked a part of the row
 // each and were joined at the end (for launches of at most one wavefront per SIMD: 45 -> 35.5 us of a tiny layer) had
 // references of their own, so that a head's output depended on how many heads and batch entries were in the call.
 template <int D, int B>
-constexpr int attn_step_keys() { return (D == 128 && B == 64) ? 32 : 64; }
+constexpr int attn_image_keys() { return (D == 128 && B == 64) ? 32 : 64; }
 template <int D, int B, bool DENSE, bool SCORES>
 __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
-  constexpr int SK = attn_step_keys<D, B>();
+  constexpr int SK = attn_image_keys<D, B>();
+  constexpr int KH = KT / SK;       // ring images, and steps, per 64-key tile
   constexpr int NW = B / 32;        // wavefronts per workgroup, 32 queries each
-  constexpr int SPB = B / SK;       // sub-tiles per key block
-  constexpr int NR = SK / 32;       // 32-key row blocks of S^T
-  constexpr int NKS = SK / 16;      // 16-key steps of the PV product
-  constexpr int IMG = SK * D * 2;   // bytes of a sub-tile of K (or V)
+  constexpr int SPB = B / KT;       // tiles per key block
+  constexpr int NR = SK / 32;       // 32-key row blocks of S^T per step
+  constexpr int NKS = SK / 16;      // 16-key parts of the PV product per step
+  constexpr int IMG = SK * D * 2;   // bytes of a ring image of K (or V)
   constexpr int PACKED = KT * D * 2;  // bytes of a packed K (or V) image of KT keys, K image then V image
   constexpr int DS = D / 16;        // k-steps of the QK^T product
   constexpr int DB = D / 32;        // 32-row blocks of O^T
-  constexpr int DK = 2, DV = 2;                              // prefetch distances (steps)
-  constexpr int RK = DK, RV = DV + 1;                        // ring slots
+  // Step u = KH * tile + part reads K image u + KH and V image u; it fetches K image u + DK and V image u + DV.
+  constexpr int DK = KH + 1, DV = 2;
+  constexpr int RK = DK - KH + 1, RV = DV + 1;               // ring slots; image u lies in slot u % RK resp. u % RV
   constexpr int CH = IMG / 1024 / NW;                        // 1 KiB chunks per wavefront per image
-  // Each step issues its CH chunks of K[t+DK] first, then its CH chunks of V[t+DV].  At the top of the next
-  // step K[t+1] (issued a step ago) must have landed; the V chunks issued after it are for a later step and
+  // Each step issues its CH chunks of K[u+DK] first, then its CH chunks of V[u+DV].  At the top of the next
+  // step its K image (issued a step ago) must have landed; the V chunks issued after it are for a later step and
   // may still be in flight (vmcnt counts in order).
   constexpr int VM_KEEP = CH;
   static_assert(IMG % (1024 * NW) == 0, "image must split evenly over the wavefronts");
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   const int64_t lws_row = ((int64_t)b * p.n_heads + hpos) * ((int64_t)p.nqb * (p.nqb + 1) / 2) + (int64_t)i * (i + 1) / 2;
   if (SCORES) lrow = p.lws + lws_row * B + tq;
 
-  // key block of sub-tile t (t clamped to the sequence; list entries clamped into [0, i]: memory-safe
+  // key block of tile t (t clamped to the sequence; list entries clamped into [0, i]: memory-safe
   // whatever the list holds)
   auto block_of = [&](int t) -> int {
     int e = (t < nsub ? t : nsub - 1) / SPB;
@@ -253,43 +259,44 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     const int j = list[e];
     return j < 0 ? 0 : (j > i ? i : j);
   };
-  // what this wavefront has to do for sub-tile `sub` of key block j: 0 all of it, 1 causal mask, 2 nothing
+  // what this wavefront has to do for tile `sub` of key block j: 0 all of it, 1 causal mask, 2 nothing
   auto mode_of = [&](int j, int sub) -> int {
     if (j != i) return 0;
-    const int klo = SK * sub, qlo = 32 * w;
-    return (klo > qlo + 31) ? 2 : ((klo + SK - 1 <= qlo) ? 0 : 1);
+    const int klo = KT * sub, qlo = 32 * w;
+    return (klo > qlo + 31) ? 2 : ((klo + KT - 1 <= qlo) ? 0 : 1);
   };
-  // every wavefront moves CH chunks of sub-tile t (clamped) into ring slot `slot_base`; a half image is the first or
-  // second half of a packed K image, and of every 4 KiB (one 32-dim block) of a packed V image
-  auto img_src = [&](int t, int j, bool is_v) -> const char * {
+  // every wavefront moves CH chunks of image `part` of tile t (clamped) into ring slot `slot_base`; a half image is one
+  // half of a packed K image, and of every 4 KiB (one 32-dim block) of a packed V image
+  auto img_src = [&](int t, int part, int j, bool is_v) -> const char * {
     const int tt = t < nsub ? t : nsub - 1;
-    const int key = j * B + (tt % SPB) * SK;
-    const char *src = kvbase + (int64_t)(key / KT) * (2 * PACKED) + (is_v ? PACKED : 0);
-    return SK == KT ? src : src + (key % KT) / SK * (is_v ? NKS * 1024 : IMG);
+    const char *src = kvbase + (int64_t)(j * SPB + tt % SPB) * (2 * PACKED) + (is_v ? PACKED : 0);
+    return KH == 1 ? src : src + part * (is_v ? NKS * 1024 : IMG);
   };
   // chunk n (0 .. CH-1) of this wavefront's share of an image
   auto issue_chunk = [&](const char *src, uint32_t slot_base, int n, bool is_v) {
     const int q = w * CH + n;
-    lds_dma16(src + (SK == KT || !is_v ? q * 1024 : q / NKS * 4096 + q % NKS * 1024), lane * 16, slot_base + q * 1024);
+    lds_dma16(src + (KH == 1 || !is_v ? q * 1024 : q / NKS * 4096 + q % NKS * 1024), lane * 16, slot_base + q * 1024);
   };
-  auto issue_img = [&](int t, int j, bool is_v, uint32_t slot_base) {
-    const char *src = img_src(t, j, is_v);
+  auto issue_img = [&](int t, int part, int j, bool is_v, uint32_t slot_base) {
+    const char *src = img_src(t, part, j, is_v);
 #pragma unroll
     for (int n = 0; n < CH; ++n) issue_chunk(src, slot_base, n, is_v);
   };
 
-  auto qk = [&](const char *kbuf, f32x16(&s)[NR]) {
+  // S rows of image `part` of a tile
+  auto qk = [&](auto part, const char *kbuf, f32x16(&s)[2]) {
+    constexpr int R0 = decltype(part)::value * NR;
     const char *kb = kbuf + lane * 16;
 #pragma unroll
     for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[rb][r] = 0.f;
+      for (int r = 0; r < 16; ++r) s[R0 + rb][r] = 0.f;
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds)
 #pragma unroll
       for (int rb = 0; rb < NR; ++rb) {
         const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kb + (rb * DS + ds) * 1024);
-        s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s[rb], 0, 0, 0);
+        s[R0 + rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s[R0 + rb], 0, 0, 0);
       }
   };
   // move_reference: mx = raw row max of a fresh tile.  Moves the reference if the max outgrew the slack,
@@ -308,52 +315,58 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // Online softmax, split in two halves that sit in different pipeline steps.
   // tile_max: (optionally causal-masked) row max of a freshly computed S tile; moves the running max,
   // rescales the running sums, returns alpha = 2^(m_old - m_new) for the O accumulators.
-  auto tile_max = [&](f32x16(&s)[NR], int mode, int sub) -> float {
+  auto tile_max = [&](f32x16(&s)[2], int mode, int sub) -> float {
     if (mode == 1) {
 #pragma unroll
-      for (int rb = 0; rb < NR; ++rb)
+      for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int kk = SK * sub + 32 * rb + 8 * (r >> 2) + 4 * h + (r & 3);
+          const int kk = KT * sub + 32 * rb + 8 * (r >> 2) + 4 * h + (r & 3);
           if (kk > tq) s[rb][r] = -INFINITY;
         }
     }
     float mx = fmaxf(s[0][0], s[0][1]);
 #pragma unroll
-    for (int rb = 0; rb < NR; ++rb)
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
       for (int r = (rb == 0 ? 2 : 0); r < 16; r += 2) mx = fmaxf(mx, fmaxf(s[rb][r], s[rb][r + 1]));
     mx = max_xor32(mx);
     return move_reference(mx);
   };
-  auto sum_p = [&](const bf16x8(&pb)[NKS]) -> float {
-    float sum = sum_bf16x8(pb[0]);
+  // what a tile's steps hand on to one another: two halves of its row sum, the row max of the next tile, the sum of the
+  // weights as PV sees them
+  float rs0, rs1, mx, psum;
+  auto add_p = [&](auto part, const bf16x8(&pb)[NKS]) {
+    psum = decltype(part)::value == 0 ? sum_bf16x8(pb[0]) : psum + sum_bf16x8(pb[0]);
 #pragma unroll
-    for (int ks = 1; ks < NKS; ++ks) sum += sum_bf16x8(pb[ks]);
-    return sum;
+    for (int ks = 1; ks < NKS; ++ks) psum += sum_bf16x8(pb[ks]);
   };
-  // tile_exp: P = 2^(S*c - m) for a tile whose max is already folded into m; adds the row sums,
-  // leaves P rounded to bf16 in pb (the B operand of the PV product)
-  auto tile_exp = [&](f32x16(&s)[NR], bf16x8(&pb)[NKS]) {
-    float rs0 = 0.f, rs1 = 0.f;
+  // tile_exp: P = 2^(S*c - m) for image `part` of a tile whose max is already folded into m, left rounded to bf16 in pb
+  // (the B operand of the PV product); the last one adds the tile's row sums
+  auto tile_exp = [&](auto part, f32x16(&s)[2], bf16x8(&pb)[NKS]) {
+    constexpr int P = decltype(part)::value;
+    if (P == 0) rs0 = rs1 = 0.f;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       u32x4 t;
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) {
         const int r = 8 * (ks & 1) + 2 * e2;
-        const float p0 = fast_exp2(__builtin_fmaf(s[ks >> 1][r], p.c, -m));
-        const float p1 = fast_exp2(__builtin_fmaf(s[ks >> 1][r + 1], p.c, -m));
+        const float p0 = fast_exp2(__builtin_fmaf(s[P * NR + (ks >> 1)][r], p.c, -m));
+        const float p1 = fast_exp2(__builtin_fmaf(s[P * NR + (ks >> 1)][r + 1], p.c, -m));
         rs0 += p0;
         rs1 += p1;
         t[e2] = pack_bf16(p0, p1);
       }
       pb[ks] = __builtin_bit_cast(bf16x8, t);
     }
-    const float rs = sum_xor32(rs0 + rs1);
-    l += rs;
-    bs += rs;
-    lc += sum_xor32(sum_p(pb)) - rs;
+    add_p(part, pb);
+    if (P == KH - 1) {
+      const float rs = sum_xor32(rs0 + rs1);
+      l += rs;
+      bs += rs;
+      lc += sum_xor32(psum) - rs;
+    }
   };
   auto rescale = [&](float alpha) {
     if (__any(alpha != 1.f)) {
@@ -374,41 +387,39 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       }
   };
 
-  // On entry to step t: s_cur = raw S[t] (masked where needed), m / l / bs / O already moved to the
-  // running max that includes tile t.  jv = key block of the V image to fetch (tile t+DV), jk = of
-  // the K image (tile t+DK).
-  // sync_and_fill: wait until the images this step reads have landed for every wavefront, then
-  // refill the ring slots the previous step freed.
-  auto sync_and_fill = [&](int t, int jv, int jk) {
+  // On entry to the steps of tile t: s_cur = raw S[t] (masked where needed), m / l / bs / O already moved to the
+  // running max that includes tile t.  jt[x] = key block of tile t + x.
+  // sync: wait until the images this step reads have landed for every wavefront; the ring slots that the previous step
+  // freed may be refilled then.
+  auto sync = [&]() {
     wait_vm<VM_KEEP>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    issue_img(t + DK, jk, false, lds_k + ((t + DK) % RK) * IMG);
-    issue_img(t + DV, jv, true, lds_v + ((t + DV) % RV) * IMG);
   };
   // fast step: tiles t and t+1 both off the diagonal.  One basic block up to the rescale test.
-  auto fast_step = [&](int t, int j0, int jv, int jk, f32x16(&s_cur)[NR], f32x16(&s_next)[NR]) {
-    // the ring refills (K for the step after next, then V for the same step) are dropped one chunk at a time
-    // into the MFMA groups below instead of going out in a burst after the barrier
-    wait_vm<VM_KEEP>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const char *ksrc = img_src(t + DK, jk, false);
-    const uint32_t kslot = lds_k + ((t + DK) % RK) * IMG;
-    const char *vsrc = img_src(t + DV, jv, true);
-    const uint32_t vslot = lds_v + ((t + DV) % RV) * IMG;
-    const char *kb = smem + ((t + 1) % RK) * IMG + lane * 16;
-    const char *vb = smem + (RK + t % RV) * IMG + lane * 16;
+  auto fast_step = [&](auto part, int t, const int(&jt)[3], f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+    constexpr int P = decltype(part)::value;
+    constexpr bool LAST = P == KH - 1;
+    const int u0 = t * KH + P;
+    // the ring refills (K, then V) are dropped one chunk at a time into the MFMA groups below instead of going out in a
+    // burst after the barrier
+    sync();
+    const char *ksrc = img_src(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], false);
+    const uint32_t kslot = lds_k + ((u0 + DK) % RK) * IMG;
+    const char *vsrc = img_src(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], true);
+    const uint32_t vslot = lds_v + ((u0 + DV) % RV) * IMG;
+    const char *kb = smem + ((u0 + KH) % RK) * IMG + lane * 16;
+    const char *vb = smem + (RK + u0 % RV) * IMG + lane * 16;
     // Hand-laid schedule: NM groups, each = one MFMA + one LDS read (PF fragments ahead) + a slice
     // of the VALU work; nothing may cross a group boundary (sched_barrier).
     //   groups 0 .. NQ-1   : S[t+1] += K frag * Q frag ; exp / row-sum / bf16 pack of S[t]
-    //   groups NQ .. NM-1  : O += V frag * P frag       ; row max of S[t+1], running-max update
+    //   groups NQ .. NM-1  : O += V frag * P frag       ; row max of S[t+1], running-max update (a tile's last step)
     // The groups are expanded at compile time (static_for): left to the unroller, the d 128 / block 64 kernels kept
     // a run-time loop over register arrays, i.e. 320 B of scratch per lane (a gated layer of 2 x 8128 tokens, 32
-    // heads: 49.2 ms, now 1.07 ms).
+    // heads: 49.2 ms with the loop, 1.07 ms without).
     constexpr int NQ = NR * DS, NP = NKS * DB, NM = NQ + NP, NU = SK / 4;  // NU: exp units (2 scores each)
     constexpr int PF = 4;       // LDS fragments read ahead of the MFMA that uses them
-    constexpr int MAXTAIL = 4;  // the running-max update sits this many groups before the end
+    constexpr int MAXTAIL = LAST ? 4 : 0;  // the running-max update sits this many groups before the end
     auto frag = [&](int n) -> bf16x8 {
       if (n < NQ) return *reinterpret_cast<const bf16x8 *>(kb + ((n % NR) * DS + n / NR) * 1024);
       const int np = n - NQ;
@@ -417,7 +428,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     bf16x8 fr[PF + 1];
     bf16x8 pb[NKS];
     u32x4 pt;
-    float rs0 = 0.f, rs1 = 0.f, mx = 0.f, lval = 0.f, alpha = 1.f, rs_tile = 0.f;
+    if (P == 0) rs0 = rs1 = 0.f;
+    float lval = 0.f, alpha = 1.f, rs_tile = 0.f;
     const bool care_t = care;  // set when this tile's max was taken
     float xa[NU], xb[NU];
 #pragma unroll
@@ -430,10 +442,10 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
           f32x16 z;
 #pragma unroll
           for (int r = 0; r < 16; ++r) z[r] = 0.f;
-          s_next[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[0], z, 0, 0, 0);
+          s_next[P * NR + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[0], z, 0, 0, 0);
         } else {
-          s_next[n % NR] =
-              __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[n / NR], s_next[n % NR], 0, 0, 0);
+          f32x16 &s = s_next[P * NR + n % NR];
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[n / NR], s, 0, 0, 0);
         }
       }
       // exp units u (2 scores each), three stages in consecutive groups so that no instruction waits
@@ -443,8 +455,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
         const int gu = u * NQ / NU;
         const int ks = u / 4, e2 = u % 4, r = 8 * (ks & 1) + 2 * e2;
         if (gu == n) {
-          xa[u] = __builtin_fmaf(s_cur[ks >> 1][r], p.c, -m);
-          xb[u] = __builtin_fmaf(s_cur[ks >> 1][r + 1], p.c, -m);
+          xa[u] = __builtin_fmaf(s_cur[P * NR + (ks >> 1)][r], p.c, -m);
+          xb[u] = __builtin_fmaf(s_cur[P * NR + (ks >> 1)][r + 1], p.c, -m);
         }
         if (gu + 1 == n) {
           xa[u] = fast_exp2(xa[u]);
@@ -457,12 +469,12 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
           if (e2 == 3) pb[ks] = __builtin_bit_cast(bf16x8, pt);
         }
       }
-      if (n == NQ + 2) {
+      if (LAST && n == NQ + 2) {
         const float rs = sum_xor32(rs0 + rs1);
         rs_tile = rs;
         l += rs;
         bs += rs;
-        if (SCORES && t % SPB == SPB - 1) {  // end of key block j0: log2 of the block's exp-sum
+        if (SCORES && t % SPB == SPB - 1) {  // end of the key block: log2 of the block's exp-sum
           lval = m + fast_log2(bs);
           bs = 0.f;
         }
@@ -480,41 +492,61 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
           if (2 + u * (NP - 2 - MAXTAIL) / NU != np) continue;
-          const float a0 = s_next[u / 8][2 * (u % 8)], a1 = s_next[u / 8][2 * (u % 8) + 1];
-          mx = (u == 0) ? fmaxf(a0, a1) : max3f(mx, a0, a1);
+          const f32x16 &s = s_next[P * NR + u / 8];
+          const float a0 = s[2 * (u % 8)], a1 = s[2 * (u % 8) + 1];
+          mx = (P == 0 && u == 0) ? fmaxf(a0, a1) : max3f(mx, a0, a1);
         }
-        if (np == NP - MAXTAIL) alpha = move_reference(max_xor32(mx));
+        if (LAST && np == NP - MAXTAIL) alpha = move_reference(max_xor32(mx));
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (__any(care_t))  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
-      lc += (sum_xor32(sum_p(pb)) - rs_tile) * alpha;
-    rescale(alpha);
-    if (SCORES && t % SPB == SPB - 1 && h == 0) lrow[(int64_t)j0 * B] = lval;
+    if (__any(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
+      add_p(part, pb);
+      if (LAST) lc += (sum_xor32(psum) - rs_tile) * alpha;
+    }
+    if (LAST) {
+      rescale(alpha);
+      if (SCORES && t % SPB == SPB - 1 && h == 0) lrow[(int64_t)jt[0] * B] = lval;
+    }
   };
   // general step: per-wavefront causal mask / skip near the diagonal, optional next tile
-  auto slow_step = [&](int t, int j0, int j1, int jv, int jk, f32x16(&s_cur)[NR], f32x16(&s_next)[NR]) {
-    sync_and_fill(t, jv, jk);
-    const char *k_next = smem + ((t + 1) % RK) * IMG;
-    const char *v_cur = smem + (RK + t % RV) * IMG;
+  auto slow_step = [&](auto part, int t, const int(&jt)[3], f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+    constexpr int P = decltype(part)::value;
+    const int u0 = t * KH + P;
+    // the previous step's last LDS reads must be done before others refill their slot (a fast step ends with its MFMAs)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    sync();
+    issue_img(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], false, lds_k + ((u0 + DK) % RK) * IMG);
+    issue_img(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], true, lds_v + ((u0 + DV) % RV) * IMG);
+    const char *k_next = smem + ((u0 + KH) % RK) * IMG;
+    const char *v_cur = smem + (RK + u0 % RV) * IMG;
     const int sub = t % SPB, sub1 = (t + 1) % SPB;
-    const int mode0 = mode_of(j0, sub);
-    const int mode1 = (t + 1 < nsub) ? mode_of(j1, sub1) : 2;
-    if (mode1 != 2) qk(k_next, s_next);
+    const int mode0 = mode_of(jt[0], sub);
+    const int mode1 = (t + 1 < nsub) ? mode_of(jt[1], sub1) : 2;
+    if (mode1 != 2) qk(part, k_next, s_next);
     if (mode0 != 2) {
       bf16x8 pb[NKS];
-      tile_exp(s_cur, pb);
+      tile_exp(part, s_cur, pb);
       pv(v_cur, pb);
     }
-    if (SCORES && sub == SPB - 1 && mode_of(j0, 0) != 2) {
-      if (h == 0) lrow[(int64_t)j0 * B] = m + fast_log2(bs);
+    if (P < KH - 1) return;
+    if (SCORES && sub == SPB - 1 && mode_of(jt[0], 0) != 2) {
+      if (h == 0) lrow[(int64_t)jt[0] * B] = m + fast_log2(bs);
       bs = 0.f;
     }
     if (mode1 != 2) rescale(tile_max(s_next, mode1, sub1));
   };
+  auto fast_tile = [&](int t, int j0, int j1, int j2, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+    const int jt[3] = {j0, j1, j2};
+    static_for<0, KH>([&](auto part) __attribute__((always_inline)) { fast_step(part, t, jt, s_cur, s_next); });
+  };
+  auto slow_tile = [&](int t, int j0, int j1, int j2, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
+    const int jt[3] = {j0, j1, j2};
+    static_for<0, KH>([&](auto part) __attribute__((always_inline)) { slow_step(part, t, jt, s_cur, s_next); });
+  };
 
   if (nsub > 0) {
-    // leading run of sub-tiles that lie before the first diagonal entry of the list
+    // leading run of tiles that lie before the first diagonal entry of the list
     int nfast;
     if (DENSE || list == nullptr) {
       nfast = i * SPB;
@@ -532,32 +564,39 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // fast steps need tile t+1 off the diagonal too; keep their count even (tail starts on even parity)
     nfast = nfast > 0 ? ((nfast - 1) & ~1) : 0;
 
-    f32x16 s_a[NR], s_b[NR];
-    // jw[n] = key block of sub-tile t + n
+    f32x16 s_a[2], s_b[2];
+    // jw[n] = key block of tile t + n
     int jw[6];
 #pragma unroll
     for (int n = 0; n < 6; ++n) jw[n] = block_of(n);
-    // prologue: K[0 .. DK-1], V[0 .. DV-1]
-#pragma unroll
-    for (int n = 0; n < DK; ++n) {
-      if (n < DV && n < nsub) issue_img(n, jw[n], true, lds_v + (n % RV) * IMG);
-      if (n < nsub) issue_img(n, jw[n], false, lds_k + (n % RK) * IMG);
-    }
+    // prologue: V images 0 .. DV-1, K images 0 .. DK-1.  Those of K are one more than the ring has slots for where a tile
+    // is two images: the first waits in the V slot that the first step will fill.
+    const uint32_t k_first = (DK > RK) ? lds_v + DV * IMG : lds_k;
+    static_for<0, (DK > DV ? DK : DV)>([&](auto nc) __attribute__((always_inline)) {
+      constexpr int n = decltype(nc)::value;
+      if (n / KH < nsub) {
+        if (n < DV) issue_img(n / KH, n % KH, jw[n / KH], true, lds_v + n * IMG);
+        if (n < DK) issue_img(n / KH, n % KH, jw[n / KH], false, n == 0 ? k_first : lds_k + (n % RK) * IMG);
+      }
+    });
     wait_vm<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     {
       const int mode = mode_of(jw[0], 0);
       if (mode != 2) {
-        qk(smem, s_a);
+        static_for<0, KH>([&](auto part) __attribute__((always_inline)) {
+          constexpr int n = decltype(part)::value;
+          qk(part, smem + ((n == 0 && DK > RK) ? RK + DV : n % RK) * IMG, s_a);
+        });
         tile_max(s_a, mode, 0);  // O is still zero: nothing to rescale
       }
     }
     int t = 0;
     for (; t < nfast; t += 2) {
       const int jn0 = block_of(t + 6), jn1 = block_of(t + 7);
-      fast_step(t, jw[0], jw[DV], jw[DK], s_a, s_b);
-      fast_step(t + 1, jw[1], jw[DV + 1], jw[DK + 1], s_b, s_a);
+      fast_tile(t, jw[0], jw[1], jw[2], s_a, s_b);
+      fast_tile(t + 1, jw[1], jw[2], jw[3], s_b, s_a);
 #pragma unroll
       for (int n = 0; n < 4; ++n) jw[n] = jw[n + 2];
       jw[4] = jn0;
@@ -565,8 +604,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     }
     for (; t < nsub; t += 2) {
       const int jn0 = block_of(t + 6), jn1 = block_of(t + 7);
-      slow_step(t, jw[0], jw[1], jw[DV], jw[DK], s_a, s_b);
-      if (t + 1 < nsub) slow_step(t + 1, jw[1], jw[2], jw[DV + 1], jw[DK + 1], s_b, s_a);
+      slow_tile(t, jw[0], jw[1], jw[2], s_a, s_b);
+      if (t + 1 < nsub) slow_tile(t + 1, jw[1], jw[2], jw[3], s_b, s_a);
 #pragma unroll
       for (int n = 0; n < 4; ++n) jw[n] = jw[n + 2];
       jw[4] = jn0;

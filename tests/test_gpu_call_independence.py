@@ -45,3 +45,26 @@ def test_attention_of_a_head_alone_and_among_others(d, B, nqb):
         for what, a, e in zip(("dense output", "score map", "output over lists"), alone, everything):
             e = e[b:b + 1, few] if what == "score map" else e[b:b + 1][:, :, few]
             assert torch.equal(a, e), f"{what}, batch entry {b}: {int((a != e).sum())} of {a.numel()} differ"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_weights_are_rounded_at_the_same_points_for_both_block_sizes(d):
+    """Dense attention of one input under blocks of 64 and of 128: the running reference moves once per 64 keys under
+    both, so the weights are the same bf16 numbers and O's sums the same bits; only the general steps near the diagonal
+    (one block of them) add weights to the second normaliser sum that the fast steps leave out, each below 1/32 of its
+    row: outputs close to a rounding step of bf16 may fall on the other side."""
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, v = _inputs(37, 2048, d, batch=1)
+    out = []
+    for B in (64, 128):
+        shape = sp.shape_of(q, k, None, B)
+        nqb = 2048 // B
+        ws = torch.empty(sp.sp_workspace_bytes(shape, HQ), dtype=torch.uint8, device="cuda")
+        o, sc = torch.zeros_like(q), torch.empty((1, HQ, nqb, nqb), dtype=torch.float32, device="cuda")
+        sp.sp_dense_attn_with_block_scores(shape, q, k, v, list(range(HQ)), o, sc, ws)
+        out.append(o)
+    torch.cuda.synchronize()
+    differ = float((out[0] != out[1]).float().mean())
+    print(f"[block sizes] d {d}: {differ:.5f} of the outputs differ", flush=True)
+    assert differ <= 1e-3
