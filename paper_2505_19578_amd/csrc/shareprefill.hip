@@ -409,6 +409,7 @@ sp_status launch_determine(const sp_shape *s, const void *q, const void *k, cons
 void launch_gsel_threshold(const float *scores, int n_maps, const GselGeom &g, uint32_t gq, char *scratch,
                            hipStream_t st);
 
+constexpr int VS_PARTS = 64;  // parts of the keys that the search keeps row statistics of, at most
 // workspace of the vertical-slash search for n listed heads per batch entry
 struct VsLayout {
   size_t part, sums, flags, gsel, total;
@@ -456,11 +457,13 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
   vp.n_q_heads = s->n_q_heads;
   const float scale = (s->softmax_scale > 0.f) ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   vp.c = scale * 1.4426950408889634f;
-  // Chunks of whole key blocks: about 1024 workgroups over all listed heads (four per CU, so that the heads that
-  // a role leaves out do not empty the chip), at most 64 because every workgroup of the second pass merges the
-  // statistics of all of them.
-  const int want = std::min(64, std::max(1, 1024 / (s->batch * n)));
-  vp.chunk = (nkb + want - 1) / want;
+  // Parts of whole key blocks, at most VS_PARTS because every workgroup of the second pass merges the statistics of all
+  // of them, and chunks of whole parts: about 1024 workgroups over all listed heads (four per CU, so that the heads that
+  // a role leaves out do not empty the chip).
+  vp.part_blocks = (nkb + VS_PARTS - 1) / VS_PARTS;
+  vp.n_parts = (nkb + vp.part_blocks - 1) / vp.part_blocks;
+  const int want = std::min(vp.n_parts, std::max(1, 1024 / (s->batch * n)));
+  vp.chunk = (vp.n_parts + want - 1) / want * vp.part_blocks;
   vp.n_chunks = (nkb + vp.chunk - 1) / vp.chunk;
   vp.part = (float2 *)(vs_ws + L.part);
   vp.sums = sums_out ? sums_out : (float *)(vs_ws + L.sums);

@@ -10,18 +10,20 @@ namespace {
 
 // ---- Search Vertical Slash Pattern (Alg. 5) ------------------------------------------------------
 // Q_hat = the last `block` queries, A_hat = their causal softmax over every key.  Two passes over K form the logits by
-// MFMA and keep them on chip: the first leaves row max and row sum per chunk of keys, the second merges those, forms
+// MFMA and keep them on chip: the first leaves row max and row sum per part of the keys, the second merges those, forms
 // the logits again and adds up the normalised vertical sums a_v[s] and slash sums a_s[t - s].  (K is read twice, 2 x
 // 64 MiB per 128K keys and KV head; a slab of logits in memory, written once and read three times, was 64 MiB per
-// query head.)  The vector selection above keeps the shortest prefixes reaching gamma, and the kept keys / offsets
+// query head.)  The parts follow from the number of key blocks alone, and with them the order of every sum: how many
+// parts a workgroup takes depends on the heads of the call, a head's sums do not.  The vector selection above keeps the shortest prefixes reaching gamma, and the kept keys / offsets
 // become per-row key-block lists.
 struct VsParams {
   const uint16_t *q, *k;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
   int seq, group, n_heads, n_q_heads;
-  int n_chunks, chunk;   // chunks of `chunk` key blocks, the last one may be shorter
+  int n_parts, part_blocks;  // the keys in parts of part_blocks key blocks, the last one may be shorter
+  int n_chunks, chunk;   // a workgroup's chunk: `chunk` key blocks, whole parts
   float c;               // softmax scale * log2(e)
-  float2 *part;          // [b][n][n_chunks][B]  row max (log2 domain) and row sum of a chunk
+  float2 *part;          // [b][n][n_parts][B]  row max (log2 domain) and row sum of a part
   float *sums;           // [b][n][2][seq] a_v then a_s
   const int32_t *role;   // optional [b][n_q_heads]: only heads whose entry is -1 are processed
   int32_t head_ids[SP_MAX_HEADS];
@@ -36,7 +38,7 @@ __device__ __forceinline__ void vs_join(float &m, float &l, float m2, float l2) 
   m = mn;
 }
 
-// Pass 1: causal softmax statistics of the B query rows over one chunk of keys.  Bound by MFMA and the exponentials
+// Pass 1: causal softmax statistics of the B query rows over the parts of one chunk.  Bound by MFMA and the exponentials
 // (one per logit); a wavefront owns 32 queries (one per lane, as in attn_kernel, so nothing is exchanged before the end)
 // and the wavefronts share 64-key tiles of K in LDS, fetched one tile ahead.
 // Also clears the slash sums that two chunks add to in pass 2.
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
   const int64_t hb = (int64_t)b * p.n_heads + n;
   const int b0 = chunk * p.chunk, b1 = min(b0 + p.chunk, nkb);
   if (chunk > 0 && tid < B) p.sums[(hb * 2 + 1) * p.seq + t0 - b0 * B + B - tid] = 0.f;
-  const int u0 = b0 * (B / KT), u1 = b1 * (B / KT);
+  const int u0 = b0 * (B / KT), u1 = b1 * (B / KT), upart = p.part_blocks * (B / KT);
   const uint16_t *kbase = p.k + (int64_t)b * p.k_sb + (int64_t)(head / p.group) * p.k_sh;
   // piece x of this thread: 16 bytes of fragment f = rb * DS + ds of the tile, in operand order
   u32x4 stage[NP];
@@ -76,6 +78,7 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
   put(0);
   __syncthreads();
   float m = -INFINITY, l = 0.f;
+  int uend = u0 + upart, part = b0 / p.part_blocks;  // end and number of the part at hand
   for (int u = u0; u < u1; ++u) {
     const int buf = (u - u0) & 1;
     if (u + 1 < u1) fetch(u + 1);
@@ -111,11 +114,17 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
     l = l * fast_exp2(m - ref) + (l0 + l1);
     m = mn;
     if (u + 1 < u1) put(buf ^ 1);
+    if (u + 1 == uend || u + 1 == u1) {
+      const float m2 = __shfl_xor(m, 32, 64), l2 = __shfl_xor(l, 32, 64);
+      vs_join(m, l, m2, l2);
+      if (h == 0) p.part[(hb * p.n_parts + part) * B + tq] = make_float2(m, l);
+      m = -INFINITY;
+      l = 0.f;
+      uend += upart;
+      ++part;
+    }
     __syncthreads();
   }
-  const float m2 = __shfl_xor(m, 32, 64), l2 = __shfl_xor(l, 32, 64);
-  vs_join(m, l, m2, l2);
-  if (h == 0) p.part[(hb * p.n_chunks + chunk) * B + tq] = make_float2(m, l);
 }
 
 // Pass 2: a_v and a_s of one chunk of key blocks.  Queries are MFMA rows and keys columns (a wavefront owns 32 keys, one
@@ -157,9 +166,9 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
   const int d = tid & (B - 1), half = tid / B;
   {
     float m = -INFINITY, l = 0.f;
-#pragma unroll 4
-    for (int x = half; x < p.n_chunks; x += 2) {
-      const float2 y = p.part[(hb * p.n_chunks + x) * B + d];
+#pragma unroll 8
+    for (int x = half; x < p.n_parts; x += 2) {
+      const float2 y = p.part[(hb * p.n_parts + x) * B + d];
       vs_join(m, l, y.x, y.y);
     }
     if (half) diag_sh[d] = m, diag_sh[B + d] = l;

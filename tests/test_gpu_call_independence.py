@@ -68,3 +68,29 @@ def test_weights_are_rounded_at_the_same_points_for_both_block_sizes(d):
     differ = float((out[0] != out[1]).float().mean())
     print(f"[block sizes] d {d}: {differ:.5f} of the outputs differ", flush=True)
     assert differ <= 1e-3
+
+
+# 65 key blocks and more: the keys are dealt to fewer, longer chunks the more heads a call lists
+@pytest.mark.parametrize("d,B,nkb", [(128, 128, 67), (64, 64, 130), (64, 128, 64), (128, 64, 257)])
+def test_search_of_a_head_alone_and_among_others(d, B, nkb):
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, _ = _inputs(41, nkb * B, d)
+
+    def run(q, k, heads):
+        shape, b, n = sp.shape_of(q, k, None, B), q.shape[0], len(heads)
+        ws = torch.empty(sp.sp_vs_workspace_bytes(shape, n), dtype=torch.uint8, device="cuda")
+        sums = torch.full((b, n, 2, nkb * B), -1.0, dtype=torch.float32, device="cuda")
+        idx = torch.full((b, n, nkb, nkb), -5, dtype=torch.int32, device="cuda")
+        cnt = torch.full((b, n, nkb), -5, dtype=torch.int32, device="cuda")
+        sp.sp_search_vertical_slash(shape, q, k, heads, 0.9, True, sums, idx, cnt, ws)
+        torch.cuda.synchronize()
+        return sums, idx, cnt
+
+    everything = run(q, k, list(range(HQ)))
+    for b in range(2):
+        for h in (0, 11):
+            alone = run(q[b:b + 1], k[b:b + 1], [h])
+            for what, a, e in zip(("sums", "lists", "counts"), alone, everything):
+                e = e[b:b + 1, h:h + 1]
+                assert torch.equal(a, e), f"{what}, head {h}, batch entry {b}: {int((a != e).sum())} of {a.numel()} differ"
