@@ -50,8 +50,28 @@ __device__ __forceinline__ GselView gsel_view(char *scratch, int map, int nqb) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void gsel_zero_kernel(char *scratch, GselGeom g) {
-  GselView v = gsel_view(scratch, blockIdx.x, g.n_rows);
+// Slash sums at the borders of the search's chunks, of which the search leaves two halves: `low` here and the other one,
+// not yet divided by the block, in the vector itself.  They are added up by the kernel that comes before the first
+// reading of the vectors, once, always as low + after.  Vectors come in pairs, the slash sums second.
+struct VsBorders {
+  float *sums;       // [n_maps][seq], or null: nothing to add up
+  const float *low;  // [n_maps / 2][n_chunks][block]
+  int n_chunks, chunk_keys, block, seq;
+};
+constexpr int VS_PARTS = 64;  // parts of the keys that the search keeps row statistics of, and chunks, at most
+
+// grid y 0 clears the map's histograms, y > 0 adds up border y of a search's slash sums
+__global__ __launch_bounds__(256) void gsel_zero_kernel(char *scratch, GselGeom g, VsBorders e) {
+  const int map = blockIdx.x;
+  if (blockIdx.y > 0) {
+    const int c = blockIdx.y, d = threadIdx.x;
+    if ((map & 1) && d < e.block && !gsel_skip(g, map)) {
+      float *const at = e.sums + (int64_t)map * e.seq + (e.seq - c * e.chunk_keys - d);
+      *at = (e.low[((int64_t)(map >> 1) * e.n_chunks + c - 1) * e.block + d] + *at) * (1.f / e.block);
+    }
+    return;
+  }
+  GselView v = gsel_view(scratch, map, g.n_rows);
   for (int x = threadIdx.x; x < 2 * GS_BINS; x += 256) v.hist1[x] = 0ull;
 }
 
@@ -285,11 +305,11 @@ __global__ __launch_bounds__(256) void gsel_emit_flags_kernel(const float *__res
 
 // The whole selection over plain vectors of at most GSEL_VECTOR_MAX entries, rows of NC * 64, in one launch: a
 // workgroup per vector, histogram, tie counts and threshold in LDS, the vector read four times (from L2 after the
-// first).  Same integers as the eight launches above, which are latency alone on short vectors: the vertical-slash
+// first).  It first adds up the borders of the search's slash sums.  Same integers as the eight launches above, which are latency alone on short vectors: the vertical-slash
 // attention of 32 heads (64 vectors) of 8K tokens takes 597 us with them and 578 us with this.
 constexpr int GSEL_VECTOR_MAX = 16384;
 template <int NC>
-__global__ __launch_bounds__(1024) void gsel_vector_kernel(const float *__restrict__ scores, GselGeom g, uint32_t gq,
+__global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeom g, uint32_t gq,
                                                            int32_t *__restrict__ flags, uint64_t *__restrict__ bits) {
   __shared__ unsigned long long hist[GS_BINS];
   __shared__ unsigned long long wt[16];
@@ -297,7 +317,25 @@ __global__ __launch_bounds__(1024) void gsel_vector_kernel(const float *__restri
   __shared__ uint32_t ties[GSEL_VECTOR_MAX / 64];  // at least as many as there are rows
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, map = blockIdx.x;
   if (gsel_skip(g, map)) return;
-  const float *src = scores + (int64_t)map * g.n_rows * (NC * 64) + lane;
+  float *const vec = vs.sums + (int64_t)map * vs.seq;
+  constexpr int BL = NC * 64, NB = ((VS_PARTS - 1) * BL + 1023) / 1024;
+  const int nb = (vs.n_chunks - 1) * BL;
+  if ((map & 1) && nb > 0) {  // all loads in flight at once
+    const float *low = vs.low + (int64_t)(map >> 1) * vs.n_chunks * BL;
+    float a[NB], b[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int x = min(tid + 1024 * k, nb - 1);
+      a[k] = low[x];
+      b[k] = vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL];
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int x = tid + 1024 * k;
+      if (x < nb) vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL] = (a[k] + b[k]) * (1.f / BL);
+    }
+  }
+  const float *src = vec + lane;
   // f(row, the row's quantised entries), four rows of a wavefront in flight
   auto each_row = [&](auto f) {
     for (int r0 = w; r0 < g.n_rows; r0 += 64) {

@@ -407,19 +407,19 @@ sp_status launch_determine(const sp_shape *s, const void *q, const void *k, cons
 }
 
 void launch_gsel_threshold(const float *scores, int n_maps, const GselGeom &g, uint32_t gq, char *scratch,
-                           hipStream_t st);
+                           hipStream_t st, const VsBorders *borders = nullptr);
 
-constexpr int VS_PARTS = 64;  // parts of the keys that the search keeps row statistics of, at most
 // workspace of the vertical-slash search for n listed heads per batch entry
 struct VsLayout {
-  size_t part, sums, flags, gsel, total;
+  size_t part, low, sums, flags, gsel, total;
 };
 VsLayout vs_layout(const sp_shape *s, int n) {
   const size_t maps = (size_t)s->batch * n, nkb = s->seq / s->block;
   VsLayout L;
   L.part = 0;
   // (the sizes that callers have been told: room for every logit of a query block, of which the partial row statistics
-  // take nkb * block * 8 bytes at most)
+  // take nkb * block * 8 bytes at most and the borders' lower halves nkb * block * 4)
+  L.low = L.part + maps * std::min<size_t>(nkb, VS_PARTS) * s->block * sizeof(float2);
   L.sums = L.part + align_up(maps * s->block * s->seq * sizeof(float), 256) +
            align_up(maps * s->block * 2 * sizeof(float), 256);
   L.flags = L.sums + align_up(maps * 2 * s->seq * sizeof(float), 256);
@@ -466,6 +466,7 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
   vp.chunk = (vp.n_parts + want - 1) / want * vp.part_blocks;
   vp.n_chunks = (nkb + vp.chunk - 1) / vp.chunk;
   vp.part = (float2 *)(vs_ws + L.part);
+  vp.low = (float *)(vs_ws + L.low);
   vp.sums = sums_out ? sums_out : (float *)(vs_ws + L.sums);
   vp.role = role;
   for (int a = 0; a < n; ++a) vp.head_ids[a] = heads[a];
@@ -497,16 +498,17 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
   g.per_head = 2;
   const int n_maps = s->batch * n * 2;
   const uint32_t gq = (uint32_t)rintf(gamma * 16777216.f);
+  const VsBorders borders = {vp.sums, vp.low, vp.n_chunks, vp.chunk * s->block, s->block, s->seq};
   // One launch for vectors of up to 16K entries, where the eight launches are latency: 64 vectors of 8K 597 -> 578 us
   // of the whole call, of 16K 1650 -> 1625, 8 of 16K 144 -> 139.  Beyond, a workgroup per vector is too few: 8 vectors of
   // 32K 262 -> 264, of 128K 7030 -> 7190.
   if (s->seq <= GSEL_VECTOR_MAX) {
     if (s->block == 128)
-      hipLaunchKernelGGL(gsel_vector_kernel<2>, dim3(n_maps), dim3(1024), 0, st, vp.sums, g, gq, flags, keep_bits);
+      hipLaunchKernelGGL(gsel_vector_kernel<2>, dim3(n_maps), dim3(1024), 0, st, borders, g, gq, flags, keep_bits);
     else
-      hipLaunchKernelGGL(gsel_vector_kernel<1>, dim3(n_maps), dim3(1024), 0, st, vp.sums, g, gq, flags, keep_bits);
+      hipLaunchKernelGGL(gsel_vector_kernel<1>, dim3(n_maps), dim3(1024), 0, st, borders, g, gq, flags, keep_bits);
   } else {
-    launch_gsel_threshold(vp.sums, n_maps, g, gq, vs_ws + L.gsel, st);
+    launch_gsel_threshold(vp.sums, n_maps, g, gq, vs_ws + L.gsel, st, &borders);
     hipLaunchKernelGGL(gsel_emit_flags_kernel, dim3((nkb + 3) / 4, n_maps), dim3(256), 0, st, vp.sums, g,
                        vs_ws + L.gsel, flags, keep_bits);
   }
@@ -606,10 +608,11 @@ sp_status check_thresholds(float delta, float tau) {
 // the seven launches that leave, per map, the threshold value, the number of ties to take and every
 // row's tie count prefix in the selection scratch
 void launch_gsel_threshold(const float *scores, int n_maps, const GselGeom &g, uint32_t gq, char *scratch,
-                           hipStream_t st) {
+                           hipStream_t st, const VsBorders *borders) {
   const int row_groups = (g.n_rows + 3) / 4;
   const dim3 ghist(std::min(row_groups, 64), n_maps), grows(row_groups, n_maps);
-  hipLaunchKernelGGL(gsel_zero_kernel, dim3(n_maps), dim3(256), 0, st, scratch, g);
+  hipLaunchKernelGGL(gsel_zero_kernel, dim3(n_maps, borders ? borders->n_chunks : 1), dim3(256), 0, st, scratch, g,
+                     borders ? *borders : VsBorders{});
   hipLaunchKernelGGL(gsel_hist_kernel<1>, ghist, dim3(256), 0, st, scores, g, scratch);
   hipLaunchKernelGGL(gsel_scan_kernel<1>, dim3(n_maps), dim3(1024), 0, st, scratch, g, gq);
   hipLaunchKernelGGL(gsel_hist_kernel<2>, ghist, dim3(256), 0, st, scores, g, scratch);

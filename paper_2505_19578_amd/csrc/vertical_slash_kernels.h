@@ -25,6 +25,7 @@ struct VsParams {
   float c;               // softmax scale * log2(e)
   float2 *part;          // [b][n][n_parts][B]  row max (log2 domain) and row sum of a part
   float *sums;           // [b][n][2][seq] a_v then a_s
+  float *low;            // [b][n][n_chunks][B] lower diagonals of each chunk's last key block (see VsBorders)
   const int32_t *role;   // optional [b][n_q_heads]: only heads whose entry is -1 are processed
   int32_t head_ids[SP_MAX_HEADS];
 };
@@ -41,7 +42,6 @@ __device__ __forceinline__ void vs_join(float &m, float &l, float m2, float l2) 
 // Pass 1: causal softmax statistics of the B query rows over the parts of one chunk.  Bound by MFMA and the exponentials
 // (one per logit); a wavefront owns 32 queries (one per lane, as in attn_kernel, so nothing is exchanged before the end)
 // and the wavefronts share 64-key tiles of K in LDS, fetched one tile ahead.
-// Also clears the slash sums that two chunks add to in pass 2.
 template <int D, int B>
 __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
   constexpr int DS = D / 16, NT = B * 2, IMG = KT * D * 2, NP = IMG / 16 / NT;
@@ -52,7 +52,6 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
   const int head = p.head_ids[n], nkb = p.seq / B, t0 = p.seq - B;
   const int64_t hb = (int64_t)b * p.n_heads + n;
   const int b0 = chunk * p.chunk, b1 = min(b0 + p.chunk, nkb);
-  if (chunk > 0 && tid < B) p.sums[(hb * 2 + 1) * p.seq + t0 - b0 * B + B - tid] = 0.f;
   const int u0 = b0 * (B / KT), u1 = b1 * (B / KT), upart = p.part_blocks * (B / KT);
   const uint16_t *kbase = p.k + (int64_t)b * p.k_sb + (int64_t)(head / p.group) * p.k_sh;
   // piece x of this thread: 16 bytes of fragment f = rb * DS + ds of the tile, in operand order
@@ -132,8 +131,8 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
 // each query's row shifted by its number so that a diagonal is a column (what a row leaves free stays zero): thread q
 // adds column q, all reads at fixed distances, into the block's 2B - 1 diagonals, of which the lower half joins the
 // upper half of the next key block.  (First written with a row's keys unshifted and two predicated sums per thread:
-// 734 us at 128K keys, 75 us at 8K.)  Only at the ends of a chunk do two workgroups add to one offset: two additions
-// to a cleared value, the same in either order.  Everything else is added in a fixed order.
+// 734 us at 128K keys, 75 us at 8K.)  At the ends of a chunk, where the halves belong to two workgroups, both are stored
+// and the selection's first kernel adds them up (VsBorders).  Everything is added in a fixed order.
 // Both passes, 128K keys, 32 heads of d 128: 2646 -> 590 us; 8K keys: 153 -> 61 us (with the slab -> now).
 template <int D, int B>
 __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
@@ -242,16 +241,16 @@ __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
       const int o = t0 - kb * B + B - d;  // offset that `after` and the previous block's `before` add up to
       if (kb > b0)
         ss[o] = (low + after) * (1.f / B);
-      else if (kb == 0 && d > 0)
+      else if (kb > 0)
+        ss[o] = after;  // a border: the previous chunk's `low` and the factor come later
+      else if (d > 0)
         ss[o] = after * (1.f / B);
-      else if (kb > 0 && d > 0)
-        atomicAdd(&ss[o], after * (1.f / B));
       low = before;
     }
   }
   if (!half) {
     if (b1 < nkb)
-      atomicAdd(&ss[t0 - (b1 - 1) * B - d], low * (1.f / B));
+      p.low[(hb * p.n_chunks + chunk) * B + d] = low;
     else if (d == 0)
       ss[0] = low * (1.f / B);
   }

@@ -31,6 +31,21 @@ def test_header_symbols_are_exported():
     assert L.sp_status_string(0) == b"SP_OK"
 
 
+def test_atomics_are_integer():
+    """The header promises that no floating-point atomics are used: every atomic adds a 64-bit integer to a variable
+    that is declared as one (or reinterpreted, for the caller's int64 pair counts)."""
+    src = os.path.join(ROOT, "paper_2505_19578_amd", "csrc")
+    found = 0
+    for f in sorted(os.listdir(src)):
+        text = open(os.path.join(src, f)).read()
+        for m in re.finditer(r"\batomic(\w+)\s*\(([^;]*);", text):
+            found += 1
+            name = re.match(r"&(\w+)\[", m[2])
+            integer = name and re.search(r"\bunsigned long long (\*)?" + name[1] + r"\b", text)
+            assert m[1] == "Add" and (integer or m[2].startswith("reinterpret_cast<unsigned long long *>")), (f, m[0])
+    assert found
+
+
 def test_workspace_bytes_and_shape_validation():
     import paper_2505_19578_amd as sp
     s = _shape(sp)
