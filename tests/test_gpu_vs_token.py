@@ -29,6 +29,24 @@ def _run(sp, q, k, v, B, heads, gamma, forced):
     return shape, o, bits.cpu().numpy()[0].view(np.uint64), pairs.cpu().numpy()[0]
 
 
+def _check_kept_sets(oracle, sp, shape, q, k, heads, gamma, bits):
+    """The kept keys and offsets are the oracle's selection over the search's own sums (the same bits run to run)."""
+    import torch
+    B, N, n = shape.block, shape.seq, len(heads)
+    ws = torch.empty(sp.sp_vs_workspace_bytes(shape, n), dtype=torch.uint8, device="cuda")
+    sums = torch.empty((1, n, 2, N), dtype=torch.float32, device="cuda")
+    idx = torch.empty((1, n, N // B, N // B), dtype=torch.int32, device="cuda")
+    cnt = torch.empty((1, n, N // B), dtype=torch.int32, device="cuda")
+    sp.sp_search_vertical_slash(shape, q, k, heads, gamma, True, sums, idx, cnt, ws)
+    torch.cuda.synchronize()
+    sums_h = sums.cpu().numpy()[0]
+    for a, h in enumerate(heads):
+        for x, what in enumerate(("keys", "offsets")):
+            want, _ = oracle.select_cumulative(sums_h[a, x], gamma)
+            got = _bits_to_keep(bits[a, x], N)
+            assert np.array_equal(got, want), f"head {h}: {int((got != want).sum())} {what} differ"
+
+
 def _pair_count(keep_v, keep_s, B, forced):
     N = len(keep_v)
     total = 0
@@ -145,6 +163,7 @@ def test_token_attention_llama8b_128k_sampled_rows():
     heads = [1, 22]
     shape, o, bits, pairs = _run(sp, q, k, v, B, heads, cfg.gamma, True)
     o_h = o.float().cpu().numpy()[0]
+    _check_kept_sets(oracle, sp, shape, q, k, heads, cfg.gamma, bits)
     rows = _sample_rows(cfg.nqb, 77, extra=1)
     sel_t = np.concatenate([np.arange(i * B, (i + 1) * B) for i in rows])
     for n, h in enumerate(heads):
@@ -159,3 +178,68 @@ def test_token_attention_llama8b_128k_sampled_rows():
         print(f"[vs token] cfg3 head {h}: kept keys {int(keep_v.sum())}, kept offsets {int(keep_s.sum())}, "
               f"pairs {frac_tok:.4f} of causal, block superset {frac_blk:.4f} of causal blocks", flush=True)
         assert frac_tok <= frac_blk + 1e-9
+
+
+# vectors of 16384 entries are selected in one launch, longer ones over several; ties: all keys alike
+@pytest.mark.parametrize("B,nkb", [(128, 128), (64, 256), (64, 257), (128, 129)])
+@pytest.mark.parametrize("alike", [False, True])
+def test_kept_sets_at_the_edge_of_the_single_launch(B, nkb, alike):
+    import oracle
+    import paper_2505_19578_amd as sp
+    from synth import random_qkv
+    from tests.gpu_util import to_dev
+    qb, kb, vb = random_qkv(93, nkb * B, 2, 1, 64, 2.0)
+    if alike:
+        kb[1:] = kb[:1]
+    q, k, v = to_dev(qb), to_dev(kb), to_dev(vb)
+    for gamma in (0.3, 0.9):
+        shape, _, bits, _ = _run(sp, q, k, v, B, [0, 1], gamma, True)
+        _check_kept_sets(oracle, sp, shape, q, k, [0, 1], gamma, bits)
+
+
+@pytest.mark.parametrize("token_level", [True, False])
+def test_dictionary_fallback_above_16k_tokens(token_level):
+    """A dictionary layer of 129 key blocks whose heads take every role: the selection's launches over long vectors
+    skip the heads that do not fall back, and those that do give the bits of a stand-alone call on them."""
+    import torch
+    import paper_2505_19578_amd as sp
+    from synth import CONFIGS, make_layer
+    from tests.gpu_util import to_dev
+    from tests.test_gpu_dict import _Dict
+    L = make_layer(CONFIGS["llama8b_128k_regime"], seq=16512)
+    cfg = L["cfg"]
+    B, Hq, C, nqb = cfg.block, cfg.n_q_heads, cfg.n_clusters, cfg.seq // cfg.block
+    q, k, v = (to_dev(L[x]) for x in "qkv")
+    shape = sp.shape_of(q, k, None, B)
+    D = _Dict(sp, 1, C, nqb)
+    ws = torch.empty(sp.sp_workspace_bytes(shape, C) + max(sp.sp_vs_workspace_bytes(shape, Hq),
+                                                             sp.sp_vs_token_workspace_bytes(shape, Hq)),
+                     dtype=torch.uint8, device="cuda")
+    o, sc = torch.zeros_like(q), torch.empty((1, C, nqb, nqb), dtype=torch.float32, device="cuda")
+    role = torch.full((1, Hq), -7, dtype=torch.int32, device="cuda")
+    a_hat = torch.empty((1, Hq, nqb), dtype=torch.float32, device="cuda")
+    dist = torch.empty((1, Hq, 2), dtype=torch.float32, device="cuda")
+    vi = torch.full((1, Hq, nqb, nqb), -3, dtype=torch.int32, device="cuda")
+    vc = torch.full((1, Hq, nqb), -3, dtype=torch.int32, device="cuda")
+    mode = sp.SP_FALLBACK_VERTICAL_SLASH_TOKEN if token_level else sp.SP_FALLBACK_VERTICAL_SLASH
+    sp.sp_prefill_layer_dict(shape, q, k, v, [int(x) for x in L["head_to_cluster"]], cfg.gamma, 0.3, 0.2, 0, 0, D.c, o, sc,
+                             role, a_hat, dist, ws, fallback_mode=mode, **({} if token_level else dict(vs_idx=vi, vs_cnt=vc)))
+    torch.cuda.synchronize()
+    role_h = role.cpu().numpy()[0]
+    fb = [h for h in range(Hq) if role_h[h] == -1]
+    assert fb and (role_h == -2).any() and (role_h >= 0).any()
+    print(f"[vs token] {cfg.seq} tokens: {len(fb)} of {Hq} heads fall back", flush=True)
+    if token_level:
+        _, alone, _, _ = _run(sp, q, k, v, B, fb, cfg.gamma, True)
+    else:
+        n = len(fb)
+        wv = torch.empty(max(sp.sp_vs_workspace_bytes(shape, n), sp.sp_workspace_bytes(shape, 0)), dtype=torch.uint8,
+                         device="cuda")
+        idx = torch.empty((1, n, nqb, nqb), dtype=torch.int32, device="cuda")
+        cnt = torch.empty((1, n, nqb), dtype=torch.int32, device="cuda")
+        sp.sp_search_vertical_slash(shape, q, k, fb, cfg.gamma, True, None, idx, cnt, wv)
+        alone = torch.zeros_like(q)
+        sp.sp_block_sparse_attn(shape, q, k, v, fb, list(range(n)), idx, cnt, n, alone, wv)
+        torch.cuda.synchronize()
+        assert torch.equal(vi[:, fb], idx) and torch.equal(vc[:, fb], cnt)
+    assert torch.equal(o[:, :, fb].view(torch.int16), alone[:, :, fb].view(torch.int16))
