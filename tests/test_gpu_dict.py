@@ -226,6 +226,48 @@ def test_dict_batch_of_two_prompts_equals_two_single_runs():
             assert (roles == -1).any()
 
 
+def test_dict_batch_of_two_with_many_heads():
+    """More than 16 heads: the distances come from the estimates' kernel, which reads the dictionary entry of its own
+    batch entry.  32 heads over two layers at the paper's thresholds, two prompts in a batch against each alone."""
+    import torch
+    import paper_2505_19578_amd as sp
+    from tests.gpu_util import to_dev
+    from synth import CONFIGS, make_layer
+    cfg = CONFIGS["llama8b_128k_regime"]
+    prompts = [[make_layer(cfg, layer=l, seq=2048, structure_layer=s0) for l in (s0, s0 + 1)] for s0 in (0, 20)]
+    B, Hq, C, nqb = cfg.block, cfg.n_q_heads, cfg.n_clusters, 2048 // cfg.block
+    h2c = [int(x) for x in prompts[0][0]["head_to_cluster"]]
+
+    def run(batch):
+        nb, outs = len(batch), []
+        D = _Dict(sp, nb, C, nqb)
+        for l in range(2):
+            q, k, v = (torch.cat([to_dev(p[l][x]) for p in batch], dim=0) for x in "qkv")
+            shape = sp.shape_of(q, k, None, B)
+            ws = torch.empty(sp.sp_workspace_bytes(shape, C) + sp.sp_vs_token_workspace_bytes(shape, Hq),
+                             dtype=torch.uint8, device="cuda")
+            o, sc = torch.zeros_like(q), torch.zeros((nb, C, nqb, nqb), dtype=torch.float32, device="cuda")
+            role = torch.full((nb, Hq), -7, dtype=torch.int32, device="cuda")
+            a_hat = torch.empty((nb, Hq, nqb), dtype=torch.float32, device="cuda")
+            dist = torch.empty((nb, Hq, 2), dtype=torch.float32, device="cuda")
+            sp.sp_prefill_layer_dict(shape, q, k, v, h2c, cfg.gamma, 0.3, 0.2, 0, 0, D.c, o, sc, role, a_hat, dist, ws,
+                                     fallback_mode=sp.SP_FALLBACK_VERTICAL_SLASH_TOKEN)
+            torch.cuda.synchronize()
+            outs.append((o, role, dist, a_hat))
+        return outs, D
+
+    both, Db = run(prompts)
+    for n, p in enumerate(prompts):
+        single, Ds = run([p])
+        for l in range(2):
+            for what, tb, ts in zip(("o", "role", "dist", "a_hat"), both[l], single[l]):
+                assert torch.equal(tb[n:n + 1], ts), (what, n, l)
+        assert torch.equal(Db.valid[n], Ds.valid[0]) and torch.equal(Db.a_tilde[n], Ds.a_tilde[0])
+        assert (single[1][1] >= 0).any() and (single[1][1] == -1).any()
+    # the prompts' dictionaries differ, so a distance taken against the other batch entry's would be another number
+    assert not torch.equal(Db.a_tilde[0], Db.a_tilde[1]) and not torch.equal(both[1][2][0], both[1][2][1])
+
+
 def test_dict_permuted_clusters_with_fallbacks():
     """Clusters that straddle KV heads (a seeded permutation of the heads): the slot table of the role-driven
     launches is then not in head order, which the device-side compaction of sharing / falling-back heads has to
