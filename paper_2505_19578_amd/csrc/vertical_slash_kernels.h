@@ -10,7 +10,7 @@ namespace {
 
 // ---- Search Vertical Slash Pattern (Alg. 5) ------------------------------------------------------
 // Q_hat = the last `block` queries, A_hat = their causal softmax over every key.  Two passes over K form the logits by
-// MFMA and keep them on chip: the first leaves row max and row sum per part of the keys, the second merges those, forms
+// MFMA and keep them on chip: the first leaves row reference and row sum per part of the keys, the second merges those, forms
 // the logits again and adds up the normalised vertical sums a_v[s] and slash sums a_s[t - s].  (K is read twice, 2 x
 // 64 MiB per 128K keys and KV head; a slab of logits in memory, written once and read three times, was 64 MiB per
 // query head.)  The parts follow from the number of key blocks alone, and with them the order of every sum: how many
@@ -23,7 +23,7 @@ struct VsParams {
   int n_parts, part_blocks;  // the keys in parts of part_blocks key blocks, the last one may be shorter
   int n_chunks, chunk;   // a workgroup's chunk: `chunk` key blocks, whole parts
   float c;               // softmax scale * log2(e)
-  float2 *part;          // [b][n][n_parts][B]  row max (log2 domain) and row sum of a part
+  float2 *part;          // [b][n][n_parts][B]  row reference (log2 domain) and row sum of a part
   float *sums;           // [b][n][2][seq] a_v then a_s
   float *low;            // [b][n][n_chunks][B] lower diagonals of each chunk's last key block (see VsBorders)
   const int32_t *role;   // optional [b][n_q_heads]: only heads whose entry is -1 are processed
@@ -41,7 +41,10 @@ __device__ __forceinline__ void vs_join(float &m, float &l, float m2, float l2) 
 
 // Pass 1: causal softmax statistics of the B query rows over the parts of one chunk.  Bound by MFMA and the exponentials
 // (one per logit); a wavefront owns 32 queries (one per lane, as in attn_kernel, so nothing is exchanged before the end)
-// and the wavefronts share 64-key tiles of K in LDS, fetched one tile ahead.
+// and the wavefronts share 64-key tiles of K in LDS, fetched one tile ahead.  References are whole numbers (the maximum
+// rounded up): moving from one to another is then exact, and the weights of pass 2 are the ones that the normaliser added
+// up.  With the maximum itself as reference, the slash sums were up to 6 % further from 64 bits than with one global
+// maximum per row, now they are 2 to 6 % nearer, at the same speed.
 template <int D, int B>
 __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
   constexpr int DS = D / 16, NT = B * 2, IMG = KT * D * 2, NP = IMG / 16 / NT;
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
     float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(s[0][r], s[1][r]));
-    const float mn = fmaxf(m, mx * p.c), ref = (mn == -INFINITY) ? 0.f : mn;
+    const float mn = fmaxf(m, ceilf(mx * p.c)), ref = (mn == -INFINITY) ? 0.f : mn;
     float l0 = 0.f, l1 = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {

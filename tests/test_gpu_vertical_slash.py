@@ -222,3 +222,36 @@ def test_vertical_slash_llama8b_128k_full_size():
         emax, emean = err_stats(o_h[sel_t, n], o_o)
         assert emax <= OUT_MAX and emean <= OUT_MEAN, f"head {h}: {emax} / {emean}"
     print(f"[vs cfg3] sums at {worst:.3f} of the bound, block density of the vertical-slash lists {dens:.3f}", flush=True)
+
+
+# the last column: mean errors of a_v and a_s with every logit kept in memory and one pass for the row's maximum before
+# the pass for its sum, measured on these inputs; the search must not be further off
+@pytest.mark.parametrize("d,B,N,most", [(64, 64, 2048, (1.28e-7, 2.39e-7)), (128, 64, 8192, (2.00e-7, 5.97e-7)),
+                                        (128, 128, 8192, (2.15e-7, 5.44e-7))])
+def test_sums_error_against_64_bits(d, B, N, most):
+    """Mean relative error (2-norm) of the sums against 64 bits over 64 heads whose keys follow topics of 256 tokens, with a
+    sink: a row's maximum moves from part to part of the keys, and a slash sum is a few weights and shows their row's
+    normaliser."""
+    import torch
+    import paper_2505_19578_amd as sp
+    err = np.zeros((64, 2))
+    t, s = np.arange(N - B, N)[:, None], np.arange(N)[None, :]
+    for seed in range(8):
+        g = torch.Generator().manual_seed(seed)
+        topic = torch.randint(0, 4, (N // 256, 1), generator=g).repeat_interleave(256, 0)[:, 0]
+        base, gain = torch.randn((4, d), generator=g), 1.2 if seed % 2 else 0.4
+        hq = (torch.randn((N, 8, d), generator=g) + (gain * base[topic] + base[0])[:, None]).bfloat16()
+        hk = torch.randn((N, 2, d), generator=g) + gain * base[topic][:, None]
+        hk[0] += 1.5 * base[0]
+        hk = hk.bfloat16()
+        _, sums, _, _ = _search(sp, hq[None].cuda(), hk[None].cuda(), B, list(range(8)), 0.9, True)
+        hq, hk = hq[N - B:].double().numpy(), hk.double().numpy()
+        for h in range(8):
+            x = np.where(s <= t, hq[:, h] @ hk[:, h // 4].T / np.sqrt(d), -np.inf)
+            a = np.exp(x - x.max(axis=1, keepdims=True))
+            a /= a.sum(axis=1, keepdims=True) * B
+            a_s = np.bincount(np.maximum(t - s, 0).ravel(), weights=a.ravel(), minlength=N)
+            for n, want in enumerate((a.sum(axis=0), a_s)):
+                err[8 * seed + h, n] = np.linalg.norm(sums[h, n] - want) / np.linalg.norm(want)
+    print(f"[vs error] d{d} B{B} N{N}: a_v {err[:, 0].mean():.3e} a_s {err[:, 1].mean():.3e}", flush=True)
+    assert np.all(err.mean(axis=0) <= most)
