@@ -19,7 +19,8 @@
  *     default stream) and the call returns without waiting for it.
  *   - Arguments are validated first; on any error nothing is launched, the
  *     status says why and sp_last_error() (thread-local) has the detail.
- *   - Results are deterministic: no floating-point atomics anywhere.
+ *   - Results are deterministic: no floating-point atomics anywhere, and a head's attention,
+ *     score map and search sums are the same bits whatever else the call lists or batches.
  *   - Q, K, V, O are bfloat16.  Element strides (not bytes) are given per batch,
  *     token and head; head_dim is contiguous; every row start must be 16-byte
  *     aligned (strides multiples of 8 elements).

@@ -119,8 +119,9 @@ __device__ __forceinline__ void wait_vm() {
 //   shadow of the matrix pipe.  Steps near the diagonal take a general path (causal mask / skip).
 // K and V images ride in LDS rings (RK, RV slots) filled by LDS-direct loads issued DK resp. DV
 // steps ahead, one chunk at a time from inside the MFMA groups; one workgroup barrier per step.
-// One query block per workgroup (B/32 wavefronts); two workgroups per CU, so each SIMD holds two
-// wavefronts of different workgroups and one's barrier / load-issue time is covered by the other.
+// One query block per workgroup (B/32 wavefronts); two wavefronts per SIMD, of different workgroups, so that one's
+// barrier / load-issue time is covered by the other: two workgroups per CU at block 128 (80 KiB of LDS each at d 128, 40
+// KiB at d 64), four at block 64 (40 KiB each).
 // At most 256 registers per lane (two wavefronts per SIMD) for every block size: without the bound the block 64
 // kernels spread over accumulation registers and paid moves for it (tiny layer 53.1 -> 50.0 us).
 //

@@ -10,12 +10,13 @@ namespace {
 
 // ---- Search Vertical Slash Pattern (Alg. 5) ------------------------------------------------------
 // Q_hat = the last `block` queries, A_hat = their causal softmax over every key.  Two passes over K form the logits by
-// MFMA and keep them on chip: the first leaves row reference and row sum per part of the keys, the second merges those, forms
-// the logits again and adds up the normalised vertical sums a_v[s] and slash sums a_s[t - s].  (K is read twice, 2 x
-// 64 MiB per 128K keys and KV head; a slab of logits in memory, written once and read three times, was 64 MiB per
-// query head.)  The parts follow from the number of key blocks alone, and with them the order of every sum: how many
-// parts a workgroup takes depends on the heads of the call, a head's sums do not.  The vector selection above keeps the shortest prefixes reaching gamma, and the kept keys / offsets
-// become per-row key-block lists.
+// MFMA and keep them on chip: the first leaves row reference and row sum per part of the keys, the second merges those,
+// forms the logits again and adds up the normalised vertical sums a_v[s] and slash sums a_s[t - s].  (K is read twice by
+// every listed head, 2 x 32 MiB per 128K keys of d 128, from L2 where heads share a KV head; a slab of logits in memory,
+// written once and read three times, was 64 MiB per query head.)  The parts follow from the number of key blocks alone,
+// and with them the order of every sum: how many parts a workgroup takes depends on the heads of the call, a head's sums
+// do not.  The vector selection above keeps the shortest prefixes reaching gamma, and the kept keys / offsets become
+// per-row key-block lists.
 struct VsParams {
   const uint16_t *q, *k;
   int64_t q_sb, q_st, q_sh, k_sb, k_st, k_sh;
