@@ -137,7 +137,7 @@ __global__ __launch_bounds__(B * 2) void vs_rowpart_kernel(VsParams p) {
 // upper half of the next key block.  (First written with a row's keys unshifted and two predicated sums per thread:
 // 734 us at 128K keys, 75 us at 8K.)  At the ends of a chunk, where the halves belong to two workgroups, both are stored
 // and the selection's first kernel adds them up (VsBorders).  Everything is added in a fixed order.
-// Both passes, 128K keys, 32 heads of d 128: 2646 -> 590 us; 8K keys: 153 -> 61 us (with the slab -> now).
+// Both passes, 128K keys, 32 heads of d 128: 2646 -> 588 us; 8K keys: 153 -> 63 us (with the slab -> now).
 template <int D, int B>
 __global__ __launch_bounds__(B * 2) void vs_sums_kernel(VsParams p) {
   constexpr int DS = D / 16, NT = B * 2, NQ = B / 32;
