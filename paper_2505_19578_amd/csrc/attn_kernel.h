@@ -100,9 +100,12 @@ __device__ __forceinline__ float max3f(float a, float b, float c) {
 // 16 bytes at g_uniform + lane_off to LDS byte address lds_base + 16 l (g_uniform and lds_base are
 // wave-uniform).  Issued from inline assembly so that the compiler does not serialise it against
 // the kernel's own LDS reads; the kernel counts these loads itself (wait_vm).
+// OFF is the instruction's own offset, which moves both addresses: the chunks of one image share their scalar bases.
+template <int OFF = 0>
 __device__ __forceinline__ void lds_dma16(const void *g_uniform, uint32_t lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_off),
-               "s"(g_uniform)
+  static_assert(OFF >= 0 && OFF < 4096, "13-bit signed immediate");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(lds_base),
+               "v"(lane_off), "s"(g_uniform), "n"(OFF)
                : "memory", "m0");
 }
 template <int N>
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   auto block_of = [&](int t) -> int {
     int e = (t < nsub ? t : nsub - 1) / SPB;
     if (DENSE || list == nullptr) return e;
-    const int j = list[e];
+    const int j = __builtin_amdgcn_readfirstlane(list[e]);
     return j < 0 ? 0 : (j > i ? i : j);
   };
   // what this wavefront has to do for tile `sub` of key block j: 0 all of it, 1 causal mask, 2 nothing
@@ -273,16 +276,23 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     const char *src = kvbase + (int64_t)(j * SPB + tt % SPB) * (2 * PACKED) + (is_v ? PACKED : 0);
     return KH == 1 ? src : src + part * (is_v ? NKS * 1024 : IMG);
   };
-  // chunk n (0 .. CH-1) of this wavefront's share of an image
-  auto issue_chunk = [&](const char *src, uint32_t slot_base, int n, bool is_v) {
-    const int q = w * CH + n;
-    lds_dma16(src + (KH == 1 || !is_v ? q * 1024 : q / NKS * 4096 + q % NKS * 1024), lane * 16, slot_base + q * 1024);
+  // chunk n (0 .. CH-1) of this wavefront's share of an image.  The chunk number goes into the instruction's offset: with
+  // an address computed per chunk, a step of d 128 had 14 scalar instructions more.  That shows where a wavefront is alone
+  // on its SIMD, and so bound by the instructions it issues, and where a step is short (tiny layer 45.9 -> 45.2 us, 4K
+  // layer 146.7 -> 145.3, d 128 / block 64 811 -> 798), hardly where two wavefronts share the matrix pipe (-0.1 to -0.6 %).
+  auto issue_chunk = [&](const char *src, uint32_t slot_base, auto nc, auto is_v) __attribute__((always_inline)) {
+    constexpr int n = decltype(nc)::value;
+    constexpr bool HALF_V = KH > 1 && decltype(is_v)::value;  // NKS KiB of every 4 KiB of the packed image
+    static_assert(!HALF_V || CH % NKS == 0, "a wavefront's share of a half V image starts at a 4 KiB piece");
+    lds_dma16<n * 1024>(src + (HALF_V ? w * (CH / NKS) * 4096 + n / NKS * (4096 - NKS * 1024) : w * CH * 1024), lane * 16,
+                        slot_base + w * CH * 1024);
   };
-  auto issue_img = [&](int t, int part, int j, bool is_v, uint32_t slot_base) {
-    const char *src = img_src(t, part, j, is_v);
-#pragma unroll
-    for (int n = 0; n < CH; ++n) issue_chunk(src, slot_base, n, is_v);
+  auto issue_img = [&](int t, int part, int j, auto is_v, uint32_t slot_base) __attribute__((always_inline)) {
+    const char *src = img_src(t, part, j, decltype(is_v)::value);
+    static_for<0, CH>([&](auto nc) __attribute__((always_inline)) { issue_chunk(src, slot_base, nc, is_v); });
   };
+  using IsK = std::false_type;
+  using IsV = std::true_type;
 
   // S rows of image `part` of a tile
   auto qk = [&](auto part, const char *kbuf, f32x16(&s)[2]) {
@@ -435,6 +445,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     float xa[NU], xb[NU];
 #pragma unroll
     for (int n = 0; n < PF; ++n) fr[n] = frag(n);
+    __builtin_amdgcn_sched_barrier(0);  // all PF reads in flight before the first MFMA waits for one of them
     static_for<0, NM>([&](auto nc) __attribute__((always_inline)) {
       constexpr int n = decltype(nc)::value;
       if (n + PF < NM) fr[(n + PF) % (PF + 1)] = frag(n + PF);
@@ -482,8 +493,10 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       }
       {
         constexpr int GAP = NM / (2 * CH);  // groups between two chunk loads
-        if (n % GAP == 1 && n / GAP < CH) issue_chunk(ksrc, kslot, n / GAP, false);
-        if (n % GAP == 1 && n / GAP >= CH && n / GAP < 2 * CH) issue_chunk(vsrc, vslot, n / GAP - CH, true);
+        constexpr int x = n / GAP;
+        if constexpr (n % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{}, IsK{});
+        if constexpr (n % GAP == 1 && x >= CH && x < 2 * CH)
+          issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{}, IsV{});
       }
       if (n >= NQ) {
         const int np = n - NQ;
@@ -517,8 +530,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // the previous step's last LDS reads must be done before others refill their slot (a fast step ends with its MFMAs)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     sync();
-    issue_img(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], false, lds_k + ((u0 + DK) % RK) * IMG);
-    issue_img(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], true, lds_v + ((u0 + DV) % RV) * IMG);
+    issue_img(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], IsK{}, lds_k + ((u0 + DK) % RK) * IMG);
+    issue_img(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], IsV{}, lds_v + ((u0 + DV) % RV) * IMG);
     const char *k_next = smem + ((u0 + KH) % RK) * IMG;
     const char *v_cur = smem + (RK + u0 % RV) * IMG;
     const int sub = t % SPB, sub1 = (t + 1) % SPB;
@@ -576,8 +589,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     static_for<0, (DK > DV ? DK : DV)>([&](auto nc) __attribute__((always_inline)) {
       constexpr int n = decltype(nc)::value;
       if (n / KH < nsub) {
-        if (n < DV) issue_img(n / KH, n % KH, jw[n / KH], true, lds_v + n * IMG);
-        if (n < DK) issue_img(n / KH, n % KH, jw[n / KH], false, n == 0 ? k_first : lds_k + (n % RK) * IMG);
+        if (n < DV) issue_img(n / KH, n % KH, jw[n / KH], IsV{}, lds_v + n * IMG);
+        if (n < DK) issue_img(n / KH, n % KH, jw[n / KH], IsK{}, n == 0 ? k_first : lds_k + (n % RK) * IMG);
       }
     });
     wait_vm<0>();

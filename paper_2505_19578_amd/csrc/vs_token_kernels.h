@@ -247,12 +247,12 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   // the row's items
   const int jmin = p.forced ? 1 : 0;
   const int n0 = (p.forced && i > 0) ? SPB : 0;
-  const int G = p.cumv[hb * (p.nqb + 1) + i];
+  const int G = __builtin_amdgcn_readfirstlane(p.cumv[hb * (p.nqb + 1) + i]);
   // A row whose gathered items and kept bands together outnumber the key blocks below it walks all of those
   // blocks instead, each with the mask kept offsets | kept keys (a head that keeps nearly everything would
   // otherwise visit its kept keys twice: in the gathered images and, masked out, in the bands).
   const int ng_list = (G + KT - 1) / KT;
-  const int nb_list = (i - jmin >= 1) ? p.cumband[hb * p.nqb + (i - jmin)] : 0;
+  const int nb_list = (i - jmin >= 1) ? __builtin_amdgcn_readfirstlane(p.cumband[hb * p.nqb + (i - jmin)]) : 0;
   const int nbelow = (i - jmin > 0) ? i - jmin : 0;  // key blocks strictly between the forced sink block and the diagonal
   const bool walk_all = ng_list + nb_list * SPB > nbelow * SPB;
   const int ng = walk_all ? 0 : ng_list;
@@ -268,7 +268,8 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     if (t < ng) return VsItem{gbase + (int64_t)t * STAGE, 1, 0, t};
     t -= ng;
     if (t < nb * SPB) {
-      const int j = i - (walk_all ? 1 + t / SPB : bandlist[t / SPB]), sub = t % SPB;
+      const int d = walk_all ? 1 + t / SPB : __builtin_amdgcn_readfirstlane(bandlist[t / SPB]);
+      const int j = i - d, sub = t % SPB;
       return VsItem{kvbase + (int64_t)(j * SPB + sub) * STAGE, 2, j, sub};
     }
     t -= nb * SPB;
@@ -315,13 +316,13 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   };
 
   // every wavefront moves CH chunks of an image into a ring slot
-  auto issue_chunk = [&](const char *src, uint32_t slot_base, int nchunk) {
-    lds_dma16(src + nchunk * 1024, lane * 16, slot_base + (w * CH + nchunk) * 1024);
+  auto issue_chunk = [&](const char *src, uint32_t slot_base, auto nc) __attribute__((always_inline)) {
+    constexpr int OFF = decltype(nc)::value * 1024, HI = OFF & ~4095;  // (a share of more than 4 KiB: block 64, d 128)
+    lds_dma16<OFF - HI>(src + HI, lane * 16, slot_base + w * CH * 1024 + HI);
   };
-  auto issue_img = [&](const VsItem &it, bool is_v, uint32_t slot_base) {
+  auto issue_img = [&](const VsItem &it, bool is_v, uint32_t slot_base) __attribute__((always_inline)) {
     const char *src = it.src + (is_v ? IMG : 0) + (w * CH) * 1024;
-#pragma unroll
-    for (int nchunk = 0; nchunk < CH; ++nchunk) issue_chunk(src, slot_base, nchunk);
+    static_for<0, CH>([&](auto nc) __attribute__((always_inline)) { issue_chunk(src, slot_base, nc); });
   };
   auto qk = [&](const char *kbuf, f32x16(&s)[2]) {
     const char *kb = kbuf + lane * 16;
@@ -447,6 +448,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     uint64_t Mnn = 0ull;
 #pragma unroll
     for (int g = 0; g < PF; ++g) fr[g] = frag(g);
+    __builtin_amdgcn_sched_barrier(0);
     static_for<0, NM>([&](auto gc) __attribute__((always_inline)) {
       constexpr int g = decltype(gc)::value;
       if (g + PF < NM) fr[(g + PF) % (PF + 1)] = frag(g + PF);
@@ -486,8 +488,9 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
       }
       {
         constexpr int GAP = NM / (2 * CH);  // groups between two chunk loads
-        if (g % GAP == 1 && g / GAP < CH) issue_chunk(ksrc, kslot, g / GAP);
-        if (g % GAP == 1 && g / GAP >= CH && g / GAP < 2 * CH) issue_chunk(vsrc, vslot, g / GAP - CH);
+        constexpr int x = g / GAP;
+        if constexpr (g % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{});
+        if constexpr (g % GAP == 1 && x >= CH && x < 2 * CH) issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{});
       }
       if (g >= NQ) {
         const int np = g - NQ;
