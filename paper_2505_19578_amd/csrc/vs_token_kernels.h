@@ -330,13 +330,12 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[rb][r] = 0.f;
-#pragma unroll
-    for (int ds = 0; ds < DS; ++ds)
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kb + (rb * DS + ds) * 1024);
-        s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ds], s[rb], 0, 0, 0);
-      }
+    products_read_ahead<2 * DS>(
+        [&](int n) { return *reinterpret_cast<const bf16x8 *>(kb + ((n % 2) * DS + n / 2) * 1024); },
+        [&](auto nc, bf16x8 a) __attribute__((always_inline)) {
+          constexpr int n = decltype(nc)::value;
+          s[n % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[n / 2], s[n % 2], 0, 0, 0);
+        });
   };
   // score (rb, r) of this lane is key 32 rb + 8 (r / 4) + 4 h + r % 4 of the item: mw = the mask's word rb with the
   // 4 h already shifted out.  A score whose bit is clear becomes -inf (two instructions: bit -> 0 / -1, select).
@@ -404,13 +403,12 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   };
   auto pv = [&](const char *vbuf, const bf16x8(&pb)[4]) {
     const char *vb = vbuf + lane * 16;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(vb + (db * 4 + ks) * 1024);
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[ks], oacc[db], 0, 0, 0);
-      }
+    products_read_ahead<4 * DB>(
+        [&](int n) { return *reinterpret_cast<const bf16x8 *>(vb + ((n % DB) * 4 + n / DB) * 1024); },
+        [&](auto nc, bf16x8 a) __attribute__((always_inline)) {
+          constexpr int n = decltype(nc)::value;
+          oacc[n % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[n / DB], oacc[n % DB], 0, 0, 0);
+        });
   };
 
   // On entry to step t: s_cur = masked raw S[t] with its max folded into m / l / O (if this wavefront has anything
