@@ -216,7 +216,7 @@ void fill_attn(AttnParams &ap, const sp_shape *s, const void *q, const void *kvp
   ap.seq = s->seq;
   ap.nqb = s->seq / s->block;
   ap.n_kv_heads = s->n_kv_heads;
-  ap.group = s->n_q_heads / s->n_kv_heads;
+  ap.inv_group = (float)s->n_kv_heads / (float)s->n_q_heads;
   const float scale = (s->softmax_scale > 0.f) ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   ap.c = scale * 1.4426950408889634f;
 }
@@ -250,11 +250,11 @@ void sort_head_list(HeadList &hl, int group, bool dense) {
 // (and, for the sparse kernel, walk the same list) run on one XCD together and meet in its L2.
 template <bool DENSE>
 sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipStream_t st) {
-  const int n = hl.n;
+  const int n = hl.n, group = s->n_q_heads / s->n_kv_heads;
   struct Ent {
     int kvh, map, head, pos;
   } ent[SP_MAX_HEADS];
-  for (int a = 0; a < n; ++a) ent[a] = {hl.head[a] / ap.group, DENSE ? 0 : hl.map[a], hl.head[a], a};
+  for (int a = 0; a < n; ++a) ent[a] = {hl.head[a] / group, DENSE ? 0 : hl.map[a], hl.head[a], a};
   std::stable_sort(ent, ent + n, [](const Ent &x, const Ent &y) {
     if (x.kvh != y.kvh) return x.kvh < y.kvh;
     if (x.map != y.map) return x.map < y.map;
@@ -272,7 +272,8 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
     set_err("grid too large");
     return SP_ERR_UNSUPPORTED;
   }
-  dim3 grid((unsigned)nwg);
+  // a batch entry's workgroups are a multiple of 8, so its first one is again the first XCD's
+  dim3 grid((unsigned)(8 * n * ap.rgroups), (unsigned)s->batch);
   const bool sc = DENSE && ap.scores != nullptr;
   ProfScope prof(DENSE ? KK_DENSE : KK_SPARSE, st);
 #define SP_LAUNCH(D_, B_)                                                                           \
