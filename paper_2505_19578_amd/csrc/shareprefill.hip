@@ -521,7 +521,7 @@ sp_status launch_vertical_slash(const sp_shape *s, const void *q, const void *k,
 
 // workspace of the token-level vertical-slash attention for n listed heads per batch entry, after the search's own
 struct VsTokLayout {
-  size_t search, bits, cumv, gpos, cumband, bandlist, act, gimg, total;
+  size_t search, bits, cumv, gpos, hdr, act, gimg, total;
 };
 VsTokLayout vs_token_layout(const sp_shape *s, int n) {
   const size_t maps = (size_t)s->batch * n, nqb = s->seq / s->block;
@@ -530,9 +530,8 @@ VsTokLayout vs_token_layout(const sp_shape *s, int n) {
   L.bits = L.search + vs_layout(s, n).total;
   L.cumv = L.bits + align_up(maps * 2 * (s->seq / 64) * sizeof(uint64_t), 256);
   L.gpos = L.cumv + align_up(maps * (nqb + 1) * sizeof(int32_t), 256);
-  L.cumband = L.gpos + align_up(maps * s->seq * sizeof(int32_t), 256);
-  L.bandlist = L.cumband + align_up(maps * nqb * sizeof(int32_t), 256);
-  L.act = L.bandlist + align_up(maps * nqb * sizeof(int32_t), 256);
+  L.hdr = L.gpos + align_up(maps * s->seq * sizeof(int32_t), 256);
+  L.act = L.hdr + 2 * align_up(maps * nqb * sizeof(int32_t), 256);
   L.gimg = L.act + align_up((maps + s->batch) * sizeof(int32_t), 256);
   L.total = L.gimg + align_up(maps * (size_t)s->seq * s->head_dim * 2 * 2, 256);
   return L;
@@ -571,30 +570,51 @@ sp_status launch_vs_token_attn(const sp_shape *s, const void *q, const void *k, 
   tp.bits = bits;
   tp.cumv = (int32_t *)(ws + L.cumv);
   tp.gpos = (int32_t *)(ws + L.gpos);
-  tp.cumband = (int32_t *)(ws + L.cumband);
-  tp.bandlist = (int32_t *)(ws + L.bandlist);
+  tp.hdr = (int2 *)(ws + L.hdr);
   tp.gimg = ws + L.gimg;
   tp.act_pos = (int32_t *)(ws + L.act);
   tp.act_n = tp.act_pos + (size_t)s->batch * n;
-  tp.nch8 = ((tp.nqb + VST_TASK_ROWS - 1) / VST_TASK_ROWS + 7) / 8;
   tp.pairs = pairs;
   tp.role = role;
   for (int a = 0; a < n; ++a) tp.head_ids[a] = heads[a];
+  // The bands and items lie where the search had its statistics, in the room that is kept for it (4 seq block bytes per
+  // head).  The items of all rows take at most 8 (seq/64) (nqb + 1) bytes: where that is more (lengths above 32 block^2),
+  // the rows are walked in several launches, each with the items of its own rows.
+  const size_t maps = (size_t)s->batch * n, band_words = (s->seq / KT + 63) / 64;
+  const size_t band_bytes = align_up(maps * 2 * band_words * sizeof(uint64_t), 256);
+  const VsLayout VL = vs_layout(s, n);
+  tp.bandbits = (uint64_t *)(ws + L.search + VL.part);
+  tp.items = (VsItem *)(ws + L.search + VL.part + band_bytes);
+  tp.item_stride = (int64_t)((VL.sums - VL.part - band_bytes) / sizeof(VsItem) / maps);
   ProfScope prof(KK_VS, st);
   hipLaunchKernelGGL(vs_token_prep_kernel, dim3(n, s->batch), dim3(1024), 0, st, tp);
-  const dim3 ggather(s->seq / KT, n, s->batch), gattn((unsigned)((int64_t)s->batch * 8 * n * tp.nch8 * VST_TASK_ROWS));
-  if (s->head_dim == 128)
-    hipLaunchKernelGGL(vs_gather_kernel<128>, ggather, dim3(256), 0, st, tp);
-  else
-    hipLaunchKernelGGL(vs_gather_kernel<64>, ggather, dim3(256), 0, st, tp);
-  if (s->head_dim == 128 && s->block == 128)
-    hipLaunchKernelGGL((vs_token_attn_kernel<128, 128>), gattn, dim3(256), 0, st, tp);
-  else if (s->head_dim == 128 && s->block == 64)
-    hipLaunchKernelGGL((vs_token_attn_kernel<128, 64>), gattn, dim3(128), 0, st, tp);
-  else if (s->head_dim == 64 && s->block == 128)
-    hipLaunchKernelGGL((vs_token_attn_kernel<64, 128>), gattn, dim3(256), 0, st, tp);
-  else
-    hipLaunchKernelGGL((vs_token_attn_kernel<64, 64>), gattn, dim3(128), 0, st, tp);
+  const int64_t spb = s->block / KT;
+  for (tp.row1 = tp.nqb; tp.row1 > 0; tp.row1 = tp.row0) {
+    const int64_t fits = tp.item_stride / spb;  // sum of i + 1 over the rows
+    int64_t rows = 0;
+    tp.row0 = tp.row1;
+    while (tp.row0 > 0 && rows + tp.row0 <= fits) rows += tp.row0--;
+    if (tp.row0 == tp.row1) {
+      set_err("no room for the items of one row");
+      return SP_ERR_WORKSPACE;
+    }
+    tp.n_gather = tp.row1 == tp.nqb ? s->seq / KT : 0;
+    tp.nch8 = ((tp.row1 - tp.row0 + VST_TASK_ROWS - 1) / VST_TASK_ROWS + 7) / 8;
+    const dim3 gitems(tp.n_gather + tp.row1 - tp.row0, n, s->batch);
+    const dim3 gattn((unsigned)((int64_t)s->batch * 8 * n * tp.nch8 * VST_TASK_ROWS));
+    if (s->head_dim == 128)
+      hipLaunchKernelGGL(vs_gather_items_kernel<128>, gitems, dim3(256), 0, st, tp);
+    else
+      hipLaunchKernelGGL(vs_gather_items_kernel<64>, gitems, dim3(256), 0, st, tp);
+    if (s->head_dim == 128 && s->block == 128)
+      hipLaunchKernelGGL((vs_token_attn_kernel<128, 128>), gattn, dim3(256), 0, st, tp);
+    else if (s->head_dim == 128 && s->block == 64)
+      hipLaunchKernelGGL((vs_token_attn_kernel<128, 64>), gattn, dim3(128), 0, st, tp);
+    else if (s->head_dim == 64 && s->block == 128)
+      hipLaunchKernelGGL((vs_token_attn_kernel<64, 128>), gattn, dim3(256), 0, st, tp);
+    else
+      hipLaunchKernelGGL((vs_token_attn_kernel<64, 64>), gattn, dim3(128), 0, st, tp);
+  }
   return hip_check(hipGetLastError(), "token-level vertical-slash kernels launch");
 }
 

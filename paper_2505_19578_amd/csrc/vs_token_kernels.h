@@ -9,15 +9,24 @@
 
 namespace {
 
-// Per listed head (hb = b * n_heads + n), all in the caller's workspace:
+// Per listed head (hb = b * n_heads + n), all in the caller's workspace (the items in the room of the search, which is done):
 //   bits     [hb][2][seq/64] u64   kept keys (bit s) then kept offsets (bit o), written by the vector selection
 //   cumv     [hb][nqb+1]           gathered keys with s < x*block (gathered = kept keys outside the forced sink block)
 //   gpos     [hb][seq]             token index of gathered key g, ascending
-//   cumband  [hb][nqb]             kept bands among 1 .. x (band d = the offsets (d-1)B+1 .. (d+1)B-1 a key block d
-//                                  blocks below the diagonal can realise)
-//   bandlist [hb][nqb]             the kept bands, ascending
+//   bandbits [hb][2][words of 64]  bit x: a kept offset exists / every offset is kept among those that a 64-key tile x tiles
+//                              below the row's first can realise (64x - 63 .. 64x + B - 1)
+//   hdr      [hb][nqb]         items of row i: how many without a mask (they come first), and all
+//   items    [hb][..]          the items of rows row0 .. row1 - 1, VsItem each; row i's start at SPB (i (i+1) - row0 (row0+1)) / 2
 //   gimg     [hb][seq/64][2][64*D] packed K and V images of the gathered keys, 64 keys each, zero padded
 //   act_pos  [b][n_heads], act_n [b]  the listed positions that take part (role -1, or all without roles), ascending
+// One item of a row's work list: 64 keys, a packed K image followed by the V image.  code: the 64-key tile of the sequence,
+// or with VS_GATHERED the gathered image; v: keys of the item that every query of the row may attend to, whatever its
+// offsets (kept keys of a tile; of a gathered image those that no band holds; all of the sink and, forced, the diagonal).
+struct alignas(16) VsItem {
+  uint32_t code, unused;
+  uint64_t v;
+};
+constexpr uint32_t VS_GATHERED = 1u << 31;
 constexpr int VST_TASK_ROWS = 16;  // consecutive query blocks of a head that one XCD runs side by side
 struct VsTokParams {
   const uint16_t *q, *k, *v;
@@ -27,7 +36,13 @@ struct VsTokParams {
   int seq, nqb, block, n_kv_heads, group, n_heads, n_q_heads, forced;
   float c;  // softmax scale * log2(e)
   uint64_t *bits;
-  int32_t *cumv, *gpos, *cumband, *bandlist, *act_pos, *act_n;
+  int32_t *cumv, *gpos, *act_pos, *act_n;
+  uint64_t *bandbits;
+  int2 *hdr;
+  VsItem *items;
+  int64_t item_stride;  // items per listed head
+  int row0, row1;       // the query blocks of this launch
+  int n_gather;         // 64-key sub-tiles that the gathering launch packs (all, or 0 after the first launch of a call)
   char *gimg;
   int nch8;  // chunks of VST_TASK_ROWS query blocks per head and XCD: ceil(ceil(nqb / VST_TASK_ROWS) / 8)
   int64_t *pairs;        // optional [b][n]: number of (query, key) pairs of the pattern (statistics)
@@ -78,7 +93,6 @@ __global__ __launch_bounds__(1024) void vs_token_prep_kernel(VsTokParams p) {
   const int nw = p.seq / 64, B = p.block, wpb = B / 64;
   const uint64_t *bv = p.bits + hb * 2 * nw, *bs = bv + nw;
   int32_t *cumv = p.cumv + hb * (p.nqb + 1), *gpos = p.gpos + hb * (int64_t)p.seq;
-  int32_t *cumband = p.cumband + hb * p.nqb, *bandlist = p.bandlist + hb * p.nqb;
   const int w_lo = p.forced ? wpb : 0;  // the forced sink block is walked as a block: its keys are not gathered
   int carry = 0;
   for (int w0 = 0; w0 < nw; w0 += 1024) {
@@ -98,37 +112,157 @@ __global__ __launch_bounds__(1024) void vs_token_prep_kernel(VsTokParams p) {
     cumv[p.nqb] = carry;
     if (p.pairs) p.pairs[hb] = 0;
   }
-  // band d >= 1 is kept iff an offset in [(d-1)B + 1, (d+1)B - 1] is kept
-  carry = 0;
-  for (int d0 = 0; d0 < p.nqb; d0 += 1024) {
-    const int d = d0 + threadIdx.x;
-    int on = 0;
-    if (d >= 1 && d < p.nqb) {
-      const int lo = (d - 1) * B + 1, hi = min((d + 1) * B - 1, p.seq - 1);
-      for (int wd = lo / 64; wd <= hi / 64; ++wd) {
-        uint64_t word = bs[wd];
-        if (wd == lo / 64) word &= ~0ull << (lo % 64);
-        if (wd == hi / 64 && hi % 64 != 63) word &= (2ull << (hi % 64)) - 1;
-        on |= word != 0ull;
-      }
+  // tiles x >= 1 below a row's first: is any / every offset of theirs kept?
+  uint64_t *any = p.bandbits + hb * 2 * ((nw + 63) / 64), *all = any + (nw + 63) / 64;
+  for (int x0 = 0; x0 < nw; x0 += 1024) {
+    const int x = x0 + threadIdx.x;
+    bool some = false, every = false;
+    if (x >= 1 && x < nw) {
+      const uint64_t lo = bs[x - 1], mid = bs[x], hi = (wpb == 2 && x + 1 < nw) ? bs[x + 1] : 0ull;
+      some = ((lo & ~1ull) | mid | hi) != 0ull;
+      every = (lo | 1ull) == ~0ull && mid == ~0ull && (wpb == 1 || hi == ~0ull);
     }
-    int total;
-    const int rank = carry + block_scan_1024(on, sh, total);
-    if (d < p.nqb) cumband[d] = rank + on;
-    if (on) bandlist[rank] = d;
-    carry += total;
+    const uint64_t some64 = __ballot(some), every64 = __ballot(every);
+    if ((threadIdx.x & 63) == 0 && x < nw) any[x / 64] = some64, all[x / 64] = every64;
   }
 }
 
-// One workgroup per (gathered 64-key sub-tile, head): K image then V image in the operand order of pack_kv_kernel,
-// rows taken at the gathered keys' positions (zero rows beyond the last gathered key).
+// The items of one row (query block i of a listed head), by a workgroup of four wavefronts.
+// Tiles of 64 keys below the row are either bands, which hold a kept offset of the row's and are walked whole (mask: kept
+// offsets | kept keys), or their kept keys are taken from the gathered images; so every allowed pair belongs to one
+// item.  A gathered image whose keys all lie in bands is left out.  Items whose masks are all ones come first: they are
+// walked without masks.  A row with more items than it has tiles walks all of its tiles as bands.
+// With bands of whole key blocks, whose kept keys were taken from the gathered images all the same, the rows of timed
+// prompts had 12 % (128K tokens) and 10 % (8K) more items, none of the bands without masks: 32 heads of 128K 44.1 -> 39.0
+// ms, of 8K 496 -> 442 us, of 64 heads in dictionary layers of 28K 12.5 -> 10.7 ms (all of it with the scalar reads of
+// the offsets in the kernel below).
+__device__ void vs_row_items(const VsTokParams &p, int i, int b, int n) {
+  __shared__ int cnt_sh[4][2];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t hb = (int64_t)b * p.n_heads + n;
+  const int spb = p.block / KT, nw = p.seq / KT, nx = (nw + 63) / 64;
+  const uint64_t *__restrict__ bv = p.bits + hb * 2 * nw;
+  const uint64_t *__restrict__ any = p.bandbits + hb * 2 * nx, *__restrict__ all = any + nx;
+  const int32_t *__restrict__ gpos = p.gpos + hb * (int64_t)p.seq;
+  const int first = i * spb;                          // the row's first tile; tile kt lies first - kt below it
+  const int n_sink = (p.forced && i > 0) ? spb : 0;
+  const int below = first - n_sink;                   // tiles 1 .. below below the row that are neither sink nor diagonal
+  const int G = p.cumv[hb * (p.nqb + 1) + i], ng = (G + KT - 1) / KT;
+  const int per = (ng + 2) / 3, g0 = (w - 1) * per, g1 = min(w * per, ng);  // gathered images of wavefronts 1 .. 3
+  const uint64_t below_lane = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+  // keys of gathered images g .. g + 3 that lie in no band
+  auto gathered = [&](int g, uint64_t(&m)[4]) {
+    int key[4];
+    uint64_t word[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) key[e] = gpos[min((g + e) * KT + lane, G - 1)];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) word[e] = any[(first - key[e] / KT) / 64];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      m[e] = __ballot(g + e < g1 && (g + e) * KT + lane < G && !((word[e] >> ((first - key[e] / KT) & 63)) & 1));
+  };
+  // tiles 64c .. 64c + 63 below the row: bands, and those of them whose offsets are all kept
+  auto bands = [&](int c, bool walk_all, uint64_t &full) -> uint64_t {
+    uint64_t in = ~0ull;  // tiles 1 .. below of this word
+    if (c == 0) in &= ~1ull;
+    if (below - 64 * c < 63) in &= (2ull << (below - 64 * c)) - 1;
+    const uint64_t band = walk_all ? in : any[c] & in;
+    full = all[c] & band;
+    return band;
+  };
+  int n_full = 0, n_part = 0;
+  if (w == 0) {
+    for (int c = lane; 64 * c <= below; c += 64) {
+      uint64_t full;
+      const uint64_t band = bands(c, false, full);
+      n_full += __popcll(full);
+      n_part += __popcll(band & ~full);
+    }
+    n_full = wave_sum_u32(n_full);
+    n_part = wave_sum_u32(n_part);
+  } else {
+    for (int g = g0; g < g1; g += 4) {
+      uint64_t m[4];
+      gathered(g, m);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n_full += m[e] == ~0ull, n_part += m[e] != 0ull && m[e] != ~0ull;
+    }
+  }
+  if (lane == 0) cnt_sh[w][0] = n_full, cnt_sh[w][1] = n_part;
+  __syncthreads();
+  int all_items = 0;
+  for (int x = 0; x < 4; ++x) all_items += cnt_sh[x][0] + cnt_sh[x][1];
+  const bool walk_all = all_items > below;
+  if (walk_all) {  // rare: bands only, counted again
+    if (w == 0) {
+      n_full = 0;
+      for (int c = lane; 64 * c <= below; c += 64) {
+        uint64_t full;
+        bands(c, true, full);
+        n_full += __popcll(full);
+      }
+      n_full = wave_sum_u32(n_full);
+    }
+    __syncthreads();
+    if (lane == 0) cnt_sh[w][0] = w == 0 ? n_full : 0, cnt_sh[w][1] = w == 0 ? below - n_full : 0;
+    __syncthreads();
+  }
+  // order: sink, full gathered images, full bands | masked gathered images, masked bands, diagonal
+  int U = n_sink, M = 0, at_full = n_sink, at_part = 0;
+  for (int x = 1; x <= 4; ++x) {
+    if (x == (w == 0 ? 4 : w)) at_full = U, at_part = M;
+    U += cnt_sh[x & 3][0];
+    M += cnt_sh[x & 3][1];
+  }
+  at_part += U;
+  const int T = U + M + spb;
+  VsItem *__restrict__ out =
+      p.items + hb * p.item_stride + ((int64_t)i * (i + 1) - (int64_t)p.row0 * (p.row0 + 1)) / 2 * spb;
+  if (w == 0) {
+    if (lane == 0) p.hdr[hb * p.nqb + i] = make_int2(U, T);
+    if (lane < n_sink) out[lane] = VsItem{(uint32_t)lane, 0, ~0ull};
+    if (lane < spb) out[U + M + lane] = VsItem{(uint32_t)(first + lane), 0, p.forced ? ~0ull : bv[first + lane]};
+    for (int c = 0; 64 * c <= below; ++c) {
+      uint64_t full;
+      const uint64_t band = bands(c, walk_all, full), part = band & ~full;
+      const int kt = first - 64 * c - lane;
+      if ((band >> lane) & 1) {
+        const bool f = (full >> lane) & 1;
+        out[f ? at_full + __popcll(full & below_lane) : at_part + __popcll(part & below_lane)] =
+            VsItem{(uint32_t)kt, 0, f ? ~0ull : bv[kt]};
+      }
+      at_full += __popcll(full);
+      at_part += __popcll(part);
+    }
+  } else if (!walk_all) {
+    for (int g = g0; g < g1; g += 4) {
+      uint64_t m[4];
+      gathered(g, m);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (m[e] == 0ull) continue;
+        const int at = m[e] == ~0ull ? at_full++ : at_part++;
+        if (lane == 0) out[at] = VsItem{VS_GATHERED | (uint32_t)(g + e), 0, m[e]};
+      }
+    }
+  }
+}
+
+// Workgroups 0 .. n_gather - 1 of a head pack one gathered 64-key sub-tile each: K image then V image in the operand order
+// of pack_kv_kernel, rows taken at the gathered keys' positions (zero rows beyond the last gathered key).  The others make
+// the items of one row each.
 template <int D>
-__global__ __launch_bounds__(256) void vs_gather_kernel(VsTokParams p) {
+__global__ __launch_bounds__(256) void vs_gather_items_kernel(VsTokParams p) {
   constexpr int IMG = KT * D * 2, NCH = IMG / 16, DS = D / 16, VROW = D + 8;
   __shared__ __attribute__((aligned(16))) uint16_t vs[KT * VROW];
   __shared__ int32_t pos[KT];
   const int mt = blockIdx.x, n = blockIdx.y, b = blockIdx.z;
   if (vst_skip(p, b, n)) return;
+  if (mt >= p.n_gather) {
+    vs_row_items(p, p.row1 - 1 - (mt - p.n_gather), b, n);
+    return;
+  }
   const int64_t hb = (int64_t)b * p.n_heads + n;
   const int nv = p.cumv[hb * (p.nqb + 1) + p.nqb];
   if (mt * KT >= nv) return;
@@ -168,25 +302,18 @@ __global__ __launch_bounds__(256) void vs_gather_kernel(VsTokParams p) {
   }
 }
 
-// One item of a row's work list: a packed K image followed by the V image of the same 64 keys.
-// kind 0 sink block, 1 gathered keys, 2 band, 3 diagonal; j = key block (kinds 0, 2, 3), sub = 64-key sub-tile
-struct VsItem {
-  const char *src;
-  int kind, j, sub;
-};
-// Wave-uniform part of an item's mask: three words of the kept-offset bitmap around the window the wavefront's 32
-// queries see (word wi0 holds offset position start0 of the first query's window), the kept-key word of the item's
-// 64 keys, and the geometry.
+// Wave-uniform part of an item's mask: two words of the kept-offset bitmap around the window the wavefront's 32
+// queries see (word wi0 holds offset position start0 of the first query's window; none for gathered keys), the item's own
+// keys and, for a diagonal tile, the position of the first query.
 struct VsMaskPre {
-  uint64_t w0, w1, w2, v;
-  int start0, kind, nvalid, top0;
-  bool restricted, live;
+  uint64_t w0, w1, v;
+  int start0, top0;
+  bool diag, live;
 };
 
-// One workgroup per (query block, listed head): B/32 wavefronts of 32 queries.  The row's work is a list of 64-key
-// items, each a packed K/V image pair plus a 64-bit mask per query: the sink block (forced), the gathered kept keys
-// below the query block, the kept bands (mask = kept offsets, minus the kept keys already gathered) and the
-// diagonal block (causal; without forced blocks also restricted to kept keys / offsets).
+// One workgroup per (query block, listed head): B/32 wavefronts of 32 queries.  The row's work is the list of 64-key items
+// that vs_row_items made, each a packed K/V image pair plus a 64-bit mask per query: kept offsets | the item's own keys,
+// causal on the diagonal.
 // Same software pipeline as attn_kernel: K and V images ride in LDS rings filled two items ahead, one barrier per
 // item; while the matrix pipe runs S[t+1] = K[t+1] Q^T and O += V[t]^T P[t]^T the VALU computes P[t], then masks
 // S[t+1] and takes its row max (hand-laid groups).  The masks are built one item ahead from wave-uniform words of
@@ -219,14 +346,17 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   const int rr = rest % VST_TASK_ROWS, u = rest / VST_TASK_ROWS;
   const int a = u % n_act, c = 8 * (u / n_act) + ((xcd - a) & 7);
   const int n = __builtin_amdgcn_readfirstlane(p.act_pos[(int64_t)b * p.n_heads + a]);
-  const int i = p.nqb - 1 - (c * VST_TASK_ROWS + rr);
-  if (i < 0) return;  // the last chunks of a head may be short or empty
+  const int i = p.row1 - 1 - (c * VST_TASK_ROWS + rr);
+  if (i < p.row0) return;  // the last chunks of a head may be short or empty
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int head = p.head_ids[n], kvh = head / p.group;
   const int64_t hb = (int64_t)b * p.n_heads + n;
   const int nwords = p.seq / 64;
-  const uint64_t *__restrict__ bv = p.bits + hb * 2 * nwords, *__restrict__ bs = bv + nwords;
+  // The kept offsets, read as constant memory: scalar loads, counted apart from the ring refills.  As ordinary global loads
+  // (which they became beside the kernel's hand-issued ones) every masked step waited for all refills.
+  typedef const __attribute__((address_space(4))) uint64_t *ConstWords;
+  const ConstWords bs = (ConstWords)(uintptr_t)(p.bits + (hb * 2 + 1) * nwords);
   const int tq = 32 * w + c32;
   bf16x8 qf[DS];
   {
@@ -244,71 +374,64 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   float m = -INFINITY, mref = 0.f, l = 0.f, lc = 0.f;
   bool care = true;
 
-  // the row's items
-  const int jmin = p.forced ? 1 : 0;
-  const int n0 = (p.forced && i > 0) ? SPB : 0;
-  const int G = __builtin_amdgcn_readfirstlane(p.cumv[hb * (p.nqb + 1) + i]);
-  // A row whose gathered items and kept bands together outnumber the key blocks below it walks all of those
-  // blocks instead, each with the mask kept offsets | kept keys (a head that keeps nearly everything would
-  // otherwise visit its kept keys twice: in the gathered images and, masked out, in the bands).
-  const int ng_list = (G + KT - 1) / KT;
-  const int nb_list = (i - jmin >= 1) ? __builtin_amdgcn_readfirstlane(p.cumband[hb * p.nqb + (i - jmin)]) : 0;
-  const int nbelow = (i - jmin > 0) ? i - jmin : 0;  // key blocks strictly between the forced sink block and the diagonal
-  const bool walk_all = ng_list + nb_list * SPB > nbelow * SPB;
-  const int ng = walk_all ? 0 : ng_list;
-  const int nb = walk_all ? nbelow : nb_list;
-  const int T = n0 + ng + nb * SPB + SPB;
+  // the row's items, 64 at a time in registers (item t = lane t % 64 of chunk t / 64), the next chunk ahead
+  const VsItem *__restrict__ list =
+      p.items + hb * p.item_stride + ((int64_t)i * (i + 1) - (int64_t)p.row0 * (p.row0 + 1)) / 2 * SPB;
+  const int2 row_hdr = p.hdr[hb * p.nqb + i];
+  const int U = __builtin_amdgcn_readfirstlane(row_hdr.x), T = __builtin_amdgcn_readfirstlane(row_hdr.y);
   const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * STAGE;
   const char *gbase = p.gimg + hb * (int64_t)(p.seq / KT) * STAGE;
-  const int32_t *__restrict__ bandlist = p.bandlist + hb * p.nqb;
-  auto item = [&](int t) -> VsItem {  // t beyond the list: the last item again (loaded, never used)
+  auto load_chunk = [&](int chunk) -> u32x4 {
+    const int t = chunk * 64 + lane;
+    return *reinterpret_cast<const u32x4 *>(list + (t < T ? t : T - 1));
+  };
+  u32x4 it_lane = load_chunk(0), it_next = it_lane;
+  int it_chunk = 0;
+  if (T > 64) it_next = load_chunk(1);
+  auto item = [&](int t) -> VsItem {  // asked for in ascending order; beyond the list: the last item again (never used)
     t = t < T ? t : T - 1;
-    if (t < n0) return VsItem{kvbase + (int64_t)t * STAGE, 0, 0, t};
-    t -= n0;
-    if (t < ng) return VsItem{gbase + (int64_t)t * STAGE, 1, 0, t};
-    t -= ng;
-    if (t < nb * SPB) {
-      const int d = walk_all ? 1 + t / SPB : __builtin_amdgcn_readfirstlane(bandlist[t / SPB]);
-      const int j = i - d, sub = t % SPB;
-      return VsItem{kvbase + (int64_t)(j * SPB + sub) * STAGE, 2, j, sub};
+    if (t >= 64 && (t >> 6) != it_chunk) {
+      it_lane = it_next;
+      ++it_chunk;
+      if (T > (it_chunk + 1) * 64) it_next = load_chunk(it_chunk + 1);
     }
-    t -= nb * SPB;
-    return VsItem{kvbase + (int64_t)(i * SPB + t) * STAGE, 3, i, t};
+    VsItem it;
+    it.code = __builtin_amdgcn_readlane(it_lane[0], t & 63);
+    it.v = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(it_lane[3], t & 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane(it_lane[2], t & 63);
+    return it;
+  };
+  auto item_src = [&](const VsItem &it) -> const char * {
+    return ((it.code & VS_GATHERED) ? gbase : kvbase) + (int64_t)(it.code & ~VS_GATHERED) * STAGE;
   };
   // word idx of a bitmap, 0 outside it (idx is wave-uniform)
-  auto uword = [&](const uint64_t *__restrict__ bits, int idx) -> uint64_t {
+  auto uword = [&](int idx) -> uint64_t {
     const int ic = idx < 0 ? 0 : (idx >= nwords ? nwords - 1 : idx);
-    const uint64_t x = bits[ic];
+    const uint64_t x = bs[ic];
     return ic == idx ? x : 0ull;
   };
   // The mask of item t for this lane's query: bit kk = key kk of the item is allowed.
-  // Offsets of keys kk = 0 .. 63 of a band / diagonal item: o0 - kk with o0 = (i - j) B + tq - 64 sub, so the
-  // window W[x] = kept(o0 - 63 + x), reversed, is the mask in key order; the window of the wavefront's first
+  // Offsets of keys kk = 0 .. 63 of a tile x tiles below the row's first: o0 - kk with o0 = 64 x + tq, so the
+  // window W[y] = kept(o0 - 63 + y), reversed, is the mask in key order; the window of the wavefront's first
   // query starts at bit start0, query c32's window c32 bits further.
   auto mask_pre = [&](const VsItem &it, int t) -> VsMaskPre {
     VsMaskPre pre;
+    const int x = i * SPB - (int)it.code;  // tile: 1 and more below the row, 0 and -1 on the diagonal
     pre.live = t < T;
-    pre.kind = it.kind;
-    pre.nvalid = G - KT * it.sub;
-    pre.restricted = it.kind == 2 || (it.kind == 3 && !p.forced);
-    pre.start0 = (i - it.j) * B + 32 * w - KT * it.sub - 63;
-    pre.top0 = 32 * w - KT * it.sub;
-    const int wi0 = pre.start0 >> 6;  // floor, also for negative positions
-    pre.w0 = uword(bs, wi0);
-    pre.w1 = uword(bs, wi0 + 1);
-    pre.w2 = uword(bs, wi0 + 2);
-    pre.v = it.kind == 1 ? 0ull : bv[(it.j * B + KT * it.sub) >> 6];
+    pre.diag = t >= T - SPB;
+    pre.start0 = 64 * x + 32 * w - 63;
+    pre.top0 = 32 * w + 64 * x;
+    pre.v = it.v;
+    const int wi0 = (it.code & VS_GATHERED) ? -2 : pre.start0 >> 6;  // floor, also for negative positions
+    pre.w0 = uword(wi0);
+    pre.w1 = uword(wi0 + 1);
     return pre;
   };
   auto mask_lane = [&](const VsMaskPre &pre) -> uint64_t {
-    const int x = (pre.start0 & 63) + c32, sh = x & 63;
-    const bool rel = x >= 64;
-    const uint64_t lo = rel ? pre.w1 : pre.w0, hi = rel ? pre.w2 : pre.w1;
-    const uint64_t win = (lo >> sh) | ((hi << 1) << (63 - sh));
-    const uint64_t R = __builtin_bitreverse64(win);
-    uint64_t M = pre.restricted ? ((pre.kind == 2 && !walk_all) ? (R & ~pre.v) : (R | pre.v)) : ~0ull;
-    if (pre.kind == 1) M = pre.nvalid >= KT ? ~0ull : (pre.nvalid <= 0 ? 0ull : ((1ull << pre.nvalid) - 1));
-    if (pre.kind == 3) {  // causal: key 64 sub + kk <= tq
+    const int x = (pre.start0 & 63) + c32;  // 1 or 33, + c32: at most 64
+    const uint64_t win = x >= 64 ? pre.w1 : (pre.w0 >> x) | ((pre.w1 << 1) << (63 - x));
+    uint64_t M = __builtin_bitreverse64(win) | pre.v;
+    if (pre.diag) {  // causal: key 64 sub + kk <= tq
       const int top = pre.top0 + c32;
       M &= top >= 63 ? ~0ull : (top < 0 ? 0ull : ((2ull << top) - 1));
     }
@@ -321,7 +444,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     lds_dma16<OFF - HI>(src + HI, lane * 16, slot_base + w * CH * 1024 + HI);
   };
   auto issue_img = [&](const VsItem &it, bool is_v, uint32_t slot_base) __attribute__((always_inline)) {
-    const char *src = it.src + (is_v ? IMG : 0) + (w * CH) * 1024;
+    const char *src = item_src(it) + (is_v ? IMG : 0) + (w * CH) * 1024;
     static_for<0, CH>([&](auto nc) __attribute__((always_inline)) { issue_chunk(src, slot_base, nc); });
   };
   auto qk = [&](const char *kbuf, f32x16(&s)[2]) {
@@ -421,7 +544,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     wait_vm<VM_KEEP>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const char *ksrc = it2.src + (w * CH) * 1024, *vsrc = ksrc + IMG;
+    const char *ksrc = item_src(it2) + (w * CH) * 1024, *vsrc = ksrc + IMG;
     const uint32_t kslot = lds_k + ((t + 2) % RK) * IMG, vslot = lds_v + ((t + 2) % RV) * IMG;
     const char *kb = smem + ((t + 1) % RK) * IMG + lane * 16;
     const char *vb = smem + (RK + t % RV) * IMG + lane * 16;
@@ -549,10 +672,10 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   int npairs = 0;  // at most 64 per item
   {
     f32x16 s_a[2], s_b[2];
-    const int U = n0 + (walk_all ? 0 : G / KT);     // items 0 .. U-1 have all-ones masks
     const int nfu = (U > 1) ? ((U - 1) & ~1) : 0;   // steps t < nfu: item t+1 is unmasked
     const int nfm = (T - 1 - nfu) & ~1;             // steps nfu <= t < nfu + nfm: the masked step (item t+1 exists)
-    const VsItem it0 = item(0), it1 = item(1);
+    const VsItem it0 = item(0);
+    VsItem it1 = item(1);
     const uint64_t M0 = mask_lane(mask_pre(it0, 0));
     npairs += __popcll(M0) + KT * nfu;  // items 1 .. nfu are full; the later ones are counted as their masks are built
     // prologue: K and V images of items 0 and 1
@@ -567,23 +690,22 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     if (!__all(M0 == ~0ull)) apply_mask(s_a, M0);
     tile_max(s_a);  // O is still zero: nothing to rescale
     int t = 0;
+    VsItem it2 = item(2), it3 = item(3);  // it1, it2, it3: items t + 1, t + 2, t + 3
     {
-      VsItem it2 = item(2), it3 = item(3);
       const VsMaskPre nopre{};
       for (; t < nfu; t += 2) {
         const VsItem it4 = item(t + 4), it5 = item(t + 5);
         fast_step(t, it2, nopre, s_a, s_b, 0ull, std::false_type{});
         fast_step(t + 1, it3, nopre, s_b, s_a, 0ull, std::false_type{});
+        it1 = it3;
         it2 = it4;
         it3 = it5;
       }
     }
-    VsItem it2 = item(t + 2);
-    uint64_t Mn = mask_lane(mask_pre(item(t + 1), t + 1));
+    uint64_t Mn = mask_lane(mask_pre(it1, t + 1));
     npairs += __popcll(Mn);
     {
       VsMaskPre pre2 = mask_pre(it2, t + 2);
-      VsItem it3 = item(t + 3);
       for (const int tend = t + nfm; t < tend; t += 2) {
         const VsMaskPre pre3 = mask_pre(it3, t + 3);
         const VsItem it4 = item(t + 4);

@@ -243,3 +243,31 @@ def test_dictionary_fallback_above_16k_tokens(token_level):
         torch.cuda.synchronize()
         assert torch.equal(vi[:, fb], idx) and torch.equal(vc[:, fb], cnt)
     assert torch.equal(o[:, :, fb].view(torch.int16), alone[:, :, fb].view(torch.int16))
+
+
+def test_token_attention_rows_in_two_launches():
+    """A length at which the items of all rows do not fit their room (more than 32 block^2 tokens): rows on both sides of
+    the cut, and at the ends, against the oracle with the kept sets that the call reports."""
+    import torch
+    import oracle
+    import paper_2505_19578_amd as sp
+    from synth import random_qkv, bf16_bits_to_f32
+    from tests.gpu_util import to_dev, err_stats
+    d, B, nqb = 64, 64, 3000
+    N = nqb * B
+    qb, kb, _ = random_qkv(75, N, 1, 1, d, 2.0)
+    _, _, vb = random_qkv(76, N, 1, 1, d, 1.0)
+    q, k, v = to_dev(qb), to_dev(kb), to_dev(vb)
+    print(f"[vs token] d{d} B{B} N{N}", flush=True)
+    _, o, bits, _ = _run(sp, q, k, v, B, [0], 0.9, True)
+    keep_v, keep_s = _bits_to_keep(bits[0, 0], N), _bits_to_keep(bits[0, 1], N)
+    # the first launch takes the last rows, as many as fit: 16 bytes an item, i + 1 items for row i
+    room = (4 * N * B) // 16
+    cut = next(r for r in range(nqb) if nqb * (nqb + 1) // 2 - r * (r + 1) // 2 <= room)
+    assert 1000 < cut < 2000
+    rows = np.asarray([0, 1, 500, cut - 3, cut - 2, cut - 1, cut, cut + 1, cut + 2, 2500, nqb - 1], dtype=np.int32)
+    at = np.concatenate([np.arange(i * B, (i + 1) * B) for i in rows])
+    hq, hk, hv = (bf16_bits_to_f32(x)[:, 0] for x in (qb, kb, vb))
+    ref = oracle.vs_token_rows(hq, hk, hv, B, keep_v, keep_s, True, rows)
+    emax, emean = err_stats(o.float().cpu().numpy()[0, at, 0], ref)
+    assert emax <= OUT_MAX and emean <= OUT_MEAN, (emax, emean)
