@@ -28,6 +28,7 @@ struct alignas(16) VsItem {
 };
 constexpr uint32_t VS_GATHERED = 1u << 31;
 constexpr int VST_TASK_ROWS = 16;  // consecutive query blocks of a head that one XCD runs side by side
+constexpr int VST_BY_LENGTH = 3;   // most groups of 8 chunks a head that run chunk by chunk
 struct VsTokParams {
   const uint16_t *q, *k, *v;
   const char *kvp;   // packed K/V images of the whole sequence (pack_kv_kernel)
@@ -331,26 +332,41 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   const uint32_t lds_k = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
   const uint32_t lds_v = lds_k + RK * IMG;
   // workgroup -> (XCD, head, query block, batch).  Workgroups are dealt round-robin to the 8 XCDs by the hardware.
-  // A task is VST_TASK_ROWS consecutive query blocks of one head; task (head a, chunk c) belongs to XCD
-  // (a + c) % 8, so every XCD gets an eighth of every head (heads differ widely in how much they keep) and runs
-  // its tasks from long rows to short.  The workgroups resident on an XCD at one time are then a few runs of
-  // neighbouring rows, which walk nearly the same items at nearly the same time and find each other's images in
-  // the XCD's L2.
-  const int xcd = blockIdx.x & 7;
-  int rest = blockIdx.x >> 3;
-  const int per_batch = p.n_heads * p.nch8 * VST_TASK_ROWS;
-  const int b = rest / per_batch;
-  rest %= per_batch;
+  // A task is VST_TASK_ROWS consecutive query blocks of one head, chunk c of its rows from the longest; every XCD gets an
+  // eighth of every head's chunks (heads differ widely in how much they keep).  The workgroups resident on an XCD at one
+  // time are then a few runs of neighbouring rows, which walk nearly the same items at nearly the same time and find each
+  // other's images in the XCD's L2.
+  // Up to VST_BY_LENGTH groups of 8 chunks, chunk c of listed head a belongs to XCD (a + c) % 8, which runs them chunk by
+  // chunk, all heads: what is dispatched last is short.  (Head by head, a long row of the last head ended alone: 32 heads of
+  // 8K 438 -> 411 us, 16 heads d 64 of 2 x 10K 496 -> 456, dictionary layers of 40K 33.0 -> 32.6 ms.)  Beyond, chunk c
+  // belongs to XCD (KV head + c) % 8, head by head: heads of one KV head run the same rows side by side, whose bands are the
+  // same images (128K: 38.8 -> 38.3 ms, chunk by chunk 39.0).
+  const int xcd = blockIdx.x & 7, b = blockIdx.y;
   const int n_act = __builtin_amdgcn_readfirstlane(p.act_n[b]);
-  if (n_act <= 0 || rest >= n_act * p.nch8 * VST_TASK_ROWS) return;
-  const int rr = rest % VST_TASK_ROWS, u = rest / VST_TASK_ROWS;
-  const int a = u % n_act, c = 8 * (u / n_act) + ((xcd - a) & 7);
-  const int n = __builtin_amdgcn_readfirstlane(p.act_pos[(int64_t)b * p.n_heads + a]);
+  const int rr = (blockIdx.x >> 3) % VST_TASK_ROWS, u = (blockIdx.x >> 3) / VST_TASK_ROWS;
+  if (n_act <= 0 || u >= n_act * p.nch8) return;
+  const int k = (int)((uint32_t)u / (uint32_t)n_act);
+  int at = u - k * n_act;  // position among the chunks 8k .. 8k + 7 of this XCD, one of each head
+  int r = 0;
+  if (p.nch8 <= VST_BY_LENGTH) {
+    for (;; ++r) {
+      const int a0 = (xcd - r) & 7;  // a0, + 8, ..: the heads whose chunk 8k + r is this XCD's
+      const int cnt = (n_act >> 3) + (a0 < (n_act & 7) ? 1 : 0);
+      if (at < cnt || r == 7) {
+        at = a0 + 8 * at;
+        break;
+      }
+      at -= cnt;
+    }
+  }
+  const int n = __builtin_amdgcn_readfirstlane(p.act_pos[(int64_t)b * p.n_heads + at]);
+  const int head = p.head_ids[n], kvh = head / p.group;
+  if (p.nch8 > VST_BY_LENGTH) r = (xcd - kvh) & 7;
+  const int c = 8 * k + r;
   const int i = p.row1 - 1 - (c * VST_TASK_ROWS + rr);
   if (i < p.row0) return;  // the last chunks of a head may be short or empty
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int head = p.head_ids[n], kvh = head / p.group;
   const int64_t hb = (int64_t)b * p.n_heads + n;
   const int nwords = p.seq / 64;
   // The kept offsets, read as constant memory: scalar loads, counted apart from the ring refills.  As ordinary global loads
