@@ -16,7 +16,7 @@ struct AttnParams {
   int64_t q_sb, q_st, q_sh, o_sb, o_st, o_sh;
   int seq, nqb, n_kv_heads, n_heads, n_maps;
   float inv_group;  // 1 / query heads per KV head
-  int rgroups;  // ceil(nqb / 8): query-block rows per strand (see the workgroup mapping in attn_kernel)
+  int rgroups;  // ceil(nqb / (8 QB)): workgroups' rows per strand (see the workgroup mapping in attn_kernel)
   float c;    // softmax scale * log2(e)
   float *lws;     // dense: block-local log2-sum-exp [b][n][nqb(nqb+1)/2][B] (row i, key block j <= i), or null
   float *scores;  // dense: [b][n][nqb][nkb], or null
@@ -144,10 +144,10 @@ __device__ __forceinline__ void products_read_ahead(Read &&read, Use &&use) {
 //   shadow of the matrix pipe.  Steps near the diagonal take a general path (causal mask / skip).
 // K and V images ride in LDS rings (RK, RV slots) filled by LDS-direct loads issued DK resp. DV
 // steps ahead, one chunk at a time from inside the MFMA groups; one workgroup barrier per step.
-// One query block per workgroup (B/32 wavefronts); two wavefronts per SIMD, of different workgroups, so that one's
-// barrier / load-issue time is covered by the other: two workgroups per CU at block 128 (80 KiB of LDS each at d 128, 40
-// KiB at d 64), four at block 64 (40 KiB each).
-// At most 256 registers per lane (two wavefronts per SIMD) for every block size: without the bound the block 64
+// One or two query blocks per workgroup (QB B/32 wavefronts); two or three wavefronts per SIMD, of different workgroups, so
+// that one's barrier / load-issue time is covered by the others: workgroups of four wavefronts take 80 KiB of LDS at d 128
+// (two per CU) and 40 KiB at d 64 (three), those of two wavefronts 40 KiB (four).
+// The registers are bounded accordingly (256 or 168 per lane): without a bound the block 64
 // kernels spread over accumulation registers and paid moves for it (tiny layer 53.1 -> 50.0 us).
 //
 // SK: keys of a ring image.  64, except for d 128 / block 64: a workgroup is two wavefronts there and its rings of 64-key
@@ -160,13 +160,28 @@ __device__ __forceinline__ void products_read_ahead(Read &&read, Use &&use) {
 // One workgroup walks the whole row, whatever else the launch holds: groups of wavefronts that walked a part of the row
 // each and were joined at the end (for launches of at most one wavefront per SIMD: 45 -> 35.5 us of a tiny layer) had
 // references of their own, so that a head's output depended on how many heads and batch entries were in the call.
-template <int D, int B>
-constexpr int attn_image_keys() { return (D == 128 && B == 64) ? 32 : 64; }
-template <int D, int B, bool DENSE, bool SCORES>
-__global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
-  constexpr int SK = attn_image_keys<D, B>();
+//
+// QB: query blocks of a workgroup.  Two where a row is walked densely in blocks of 64: neighbouring rows walk the same
+// tiles, so a workgroup of four wavefronts moves every image once for both (the steps of block 128; the block of a wavefront
+// decides where its diagonal lies).  Score maps of 2 x 12352 tokens, 16 heads of d 64: 832 -> 788 us; gated layer of 2 x 8128
+// tokens, d 128: 794 -> 770.
+//
+// d 64 with four wavefronts to a workgroup: three wavefronts per SIMD.  A step there is bound by its VALU work (exponentials,
+// sums, row maxima), and a third wavefront fills what two leave.  168 registers are enough with two LDS fragments ahead
+// instead of four (four: 12 to 20 bytes of scratch, up to 30 % slower on short rows).  The same score maps 788 -> 740 us;
+// blocks of 128, score maps of 2 x 12288: 805 -> 752; lists of 2 x 15488: 1143 -> 1098.
+template <int D, int B, int QB>
+constexpr int attn_image_keys() { return (D == 128 && QB * B == 64) ? 32 : 64; }
+// wavefronts per SIMD that the registers are kept to
+template <int D, int B, int QB>
+constexpr int attn_waves() { return (D == 64 && QB * B == 128) ? 3 : 2; }
+template <int D, int B, bool DENSE, bool SCORES, int QB>
+__global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_kernel(AttnParams p) {
+  static_assert(QB == 1 || (DENSE && B == KT), "rows share their tiles where every key block is walked");
+  constexpr int SK = attn_image_keys<D, B, QB>(), WAVES = attn_waves<D, B, QB>();
   constexpr int KH = KT / SK;       // ring images, and steps, per 64-key tile
-  constexpr int NW = B / 32;        // wavefronts per workgroup, 32 queries each
+  constexpr int WB = B / 32;        // wavefronts per query block, 32 queries each
+  constexpr int NW = QB * WB;       // wavefronts per workgroup
   constexpr int SPB = B / KT;       // tiles per key block
   constexpr int NR = SK / 32;       // 32-key row blocks of S^T per step
   constexpr int NKS = SK / 16;      // 16-key parts of the PV product per step
@@ -215,8 +230,12 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   }
   int slot = strand >> 3;
   if (p.act_pos) slot = __builtin_amdgcn_readfirstlane(p.act_pos[(int64_t)b * p.n_heads + slot]);
-  const int i = p.nqb - 1 - (rest * 8 + (strand & 7));
-  if (i < 0) return;  // nqb is not a multiple of 8: this strand has one row fewer
+  // the (last) query block of the workgroup, and this wavefront's own (negative: none, the workgroup's first block is 0)
+  const int i = p.nqb - 1 - QB * (rest * 8 + (strand & 7));
+  if (i < 0) return;  // nqb is not a multiple of 8 QB: this strand has one row fewer
+  const int wb = QB > 1 ? w / WB : 0;  // which block is the wavefront's
+  const int iw = i - (QB - 1) + wb;
+  const bool idle = QB > 1 && iw < 0;
   int head = p.head_ids[slot];
   const int nkb = p.nqb;
   const int hpos = p.head_pos[slot];
@@ -226,7 +245,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   }
   const int kvh = __builtin_amdgcn_readfirstlane((int)((head + 0.5f) * p.inv_group));  // exact: head < 128
 
-  const int tq = 32 * w + c32;  // this lane's query inside the block
+  const int wr = QB > 1 ? w % WB : w, wq = 32 * wr, tq = wq + c32;  // first query of the wavefront, this lane's, inside the block
   f32x16 oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -277,7 +296,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   bf16x8 qf[DS];
   {
     const uint16_t *qp =
-        p.q + (int64_t)b * p.q_sb + ((int64_t)i * B + tq) * p.q_st + (int64_t)head * p.q_sh + 8 * h;
+        p.q + (int64_t)b * p.q_sb + ((int64_t)(idle ? 0 : iw) * B + tq) * p.q_st + (int64_t)head * p.q_sh + 8 * h;
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds) qf[ds] = *reinterpret_cast<const bf16x8 *>(qp + 16 * ds);
   }
@@ -291,7 +310,8 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * (2 * PACKED);
   float *lrow = nullptr;
   // block log-sum-exps: causal half, row i of a (batch entry, head) starts at i(i+1)/2 key-block slots
-  const int64_t lws_row = ((int64_t)b * p.n_heads + hpos) * ((int64_t)p.nqb * (p.nqb + 1) / 2) + (int64_t)i * (i + 1) / 2;
+  const int64_t lws_row =
+      ((int64_t)b * p.n_heads + hpos) * ((int64_t)p.nqb * (p.nqb + 1) / 2) + (int64_t)iw * (iw + 1) / 2;
   if (SCORES) lrow = p.lws + lws_row * B + tq;
 
   // key block of tile t (t clamped to the sequence; list entries clamped into [0, i]: memory-safe
@@ -299,7 +319,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   auto block_of = [&](int t) -> int {
     const int e = (t < nsub ? t : nsub - 1) / SPB;
     if (DENSE || list == nullptr) return e;
-    if (t >= 6 && (e >> 6) != lst_chunk) {
+    if (__builtin_expect(t >= 6 && (e >> 6) != lst_chunk, 0)) {
       lst = lst_next;
       ++lst_chunk;
       if (nblk > (lst_chunk + 1) * 64) lst_next = load_chunk(lst_chunk + 1);
@@ -309,8 +329,9 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   };
   // what this wavefront has to do for tile `sub` of key block j: 0 all of it, 1 causal mask, 2 nothing
   auto mode_of = [&](int j, int sub) -> int {
-    if (j != i) return 0;
-    const int klo = KT * sub, qlo = 32 * w;
+    if (QB > 1 ? (idle || j > iw) : false) return 2;
+    if (j != iw) return 0;
+    const int klo = KT * sub, qlo = wq;
     return (klo > qlo + 31) ? 2 : ((klo + KT - 1 <= qlo) ? 0 : 1);
   };
   // every wavefront moves CH chunks of image `part` of tile t (clamped) into ring slot `slot_base`; a half image is one
@@ -390,6 +411,10 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   // what a tile's steps hand on to one another: two halves of its row sum, the row max of the next tile, the sum of the
   // weights as PV sees them
   float rs0, rs1, mx, psum;
+  // QB > 1: the general steps of a workgroup begin at its first block's diagonal.  A wavefront's tiles before twice_from,
+  // which it would take by fast steps in a workgroup of its own, are summed as those do: the same bits either way.
+  int twice_from = 0;
+  float lc_later = 0.f;
   auto add_p = [&](auto part, const bf16x8(&pb)[NKS]) {
     psum = decltype(part)::value == 0 ? sum_bf16x8(pb[0]) : psum + sum_bf16x8(pb[0]);
 #pragma unroll
@@ -397,7 +422,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   };
   // tile_exp: P = 2^(S*c - m) for image `part` of a tile whose max is already folded into m, left rounded to bf16 in pb
   // (the B operand of the PV product); the last one adds the tile's row sums
-  auto tile_exp = [&](auto part, f32x16(&s)[2], bf16x8(&pb)[NKS]) {
+  auto tile_exp = [&](auto part, int t, f32x16(&s)[2], bf16x8(&pb)[NKS]) {
     constexpr int P = decltype(part)::value;
     if (P == 0) rs0 = rs1 = 0.f;
 #pragma unroll
@@ -419,7 +444,10 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       const float rs = sum_xor32(rs0 + rs1);
       l += rs;
       bs += rs;
-      lc += sum_xor32(psum) - rs;
+      const float d = sum_xor32(psum) - rs;
+      const bool early = QB > 1 && t < twice_from;
+      lc += early ? 0.f : d;
+      lc_later = early && __any(care) ? d : 0.f;
     }
   };
   auto rescale = [&](float alpha) {
@@ -471,7 +499,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // a run-time loop over register arrays, i.e. 320 B of scratch per lane (a gated layer of 2 x 8128 tokens, 32
     // heads: 49.2 ms with the loop, 1.07 ms without).
     constexpr int NQ = NR * DS, NP = NKS * DB, NM = NQ + NP, NU = SK / 4;  // NU: exp units (2 scores each)
-    constexpr int PF = 4;       // LDS fragments read ahead of the MFMA that uses them
+    constexpr int PF = (WAVES == 3) ? 2 : 4;  // LDS fragments read ahead of the MFMA that uses them
     constexpr int MAXTAIL = LAST ? 4 : 0;  // the running-max update sits this many groups before the end
     auto frag = [&](int n) -> bf16x8 {
       if (n < NQ) return *reinterpret_cast<const bf16x8 *>(kb + ((n % NR) * DS + n / NR) * 1024);
@@ -582,7 +610,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     if (mode1 != 2) qk(part, k_next, s_next);
     if (mode0 != 2) {
       bf16x8 pb[NKS];
-      tile_exp(part, s_cur, pb);
+      tile_exp(part, t, s_cur, pb);
       pv(v_cur, pb);
     }
     if (P < KH - 1) return;
@@ -590,7 +618,11 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       if (h == 0) lrow[(int64_t)jt[0] * B] = m + fast_log2(bs);
       bs = 0.f;
     }
-    if (mode1 != 2) rescale(tile_max(s_next, mode1, sub1));
+    if (mode1 != 2) {
+      const float alpha = tile_max(s_next, mode1, sub1);
+      rescale(alpha);
+      if (QB > 1) lc += lc_later * alpha;
+    }
   };
   auto fast_tile = [&](int t, int j0, int j1, int j2, f32x16(&s_cur)[2], f32x16(&s_next)[2]) {
     const int jt[3] = {j0, j1, j2};
@@ -620,7 +652,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     // leading run of tiles that lie before the first diagonal entry of the list
     int nfast;
     if (DENSE || list == nullptr) {
-      nfast = i * SPB;
+      nfast = (i - (QB - 1)) * SPB;
     } else {
       int first = nblk;
       for (int e0 = 0; e0 < nblk && first == nblk; e0 += 256) {
@@ -639,6 +671,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       }
       nfast = first * SPB;
     }
+    if (QB > 1) twice_from = (iw * SPB - 1) & ~1;
     // fast steps need tile t+1 off the diagonal too; keep their count even (tail starts on even parity)
     nfast = nfast > 0 ? ((nfast - 1) & ~1) : 0;
 
@@ -678,9 +711,9 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
   }
 
   // ---- output: O = O^T accumulators / l, rounded to bf16 ----
-  {
+  if (!idle) {
     const float inv = (l > 0.f) ? 1.f / (l + lc) : 0.f;
-    uint16_t *op = p.o + (int64_t)b * p.o_sb + ((int64_t)i * B + tq) * p.o_st + (int64_t)head * p.o_sh;
+    uint16_t *op = p.o + (int64_t)b * p.o_sb + ((int64_t)iw * B + tq) * p.o_st + (int64_t)head * p.o_sh;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -705,7 +738,7 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
     constexpr int JB = (1024 + NW * 32 * PST * 4 <= (RK + RV) * IMG) ? 32 : 16;  // key blocks per tile
     constexpr int NPART = 64 / JB, PLEN = 64 / NPART;  // stage 2: NPART lanes share a key block, PLEN entries each
     static_assert(1024 + NW * JB * PST * 4 <= (RK + RV) * IMG, "score epilogue tiles must fit the idle rings");
-    float *lse_sh = reinterpret_cast<float *>(smem);  // [B]; the rings are idle now
+    float *lse_sh = reinterpret_cast<float *>(smem) + wb * B;  // [QB][B]; the rings are idle now
     float *part = reinterpret_cast<float *>(smem + 1024) + w * (JB * PST);
     __syncthreads();
     if (h == 0) lse_sh[tq] = m + fast_log2(l);
@@ -714,15 +747,15 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
 #pragma unroll
     for (int tt = 0; tt < TPL; ++tt) lt[tt] = lse_sh[lane + 64 * tt];
     const float *lblk = p.lws + lws_row * B;
-    float *srow = p.scores + (((int64_t)b * p.n_heads + hpos) * p.nqb + i) * nkb;
+    float *srow = p.scores + (((int64_t)b * p.n_heads + hpos) * p.nqb + iw) * nkb;
     const int jr = lane % JB, jp = lane / JB;
-    for (int j0 = w * JB; j0 <= i; j0 += NW * JB) {
+    for (int j0 = wr * JB; j0 <= iw; j0 += WB * JB) {  // (iw < 0: nothing)
 #pragma unroll
       for (int u0 = 0; u0 < JB; u0 += JU) {
         float x[JU][TPL];
 #pragma unroll
         for (int u = 0; u < JU; ++u) {
-          const int j = (j0 + u0 + u <= i) ? j0 + u0 + u : i;
+          const int j = (j0 + u0 + u <= iw) ? j0 + u0 + u : iw;
 #pragma unroll
           for (int tt = 0; tt < TPL; ++tt) x[u][tt] = lblk[(int64_t)j * B + lane + 64 * tt];
         }
@@ -743,12 +776,13 @@ __global__ __launch_bounds__(B * 2, 2) void attn_kernel(AttnParams p) {
       for (int kq = 0; kq < PLEN; ++kq) acc += part[jr * PST + jp * PLEN + kq];
       acc = sum_xor32(acc);
       if (NPART == 4) acc += __shfl_xor(acc, 16, 64);
-      if (jp == 0 && j0 + jr <= i) srow[j0 + jr] = acc * (1.f / B);
+      if (jp == 0 && j0 + jr <= iw) srow[j0 + jr] = acc * (1.f / B);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    for (int j = i + 1 + w * 64 + lane; j < nkb; j += NW * 64) srow[j] = 0.f;
+    if (!idle)
+      for (int j = iw + 1 + wr * 64 + lane; j < nkb; j += WB * 64) srow[j] = 0.f;
   }
 }
 

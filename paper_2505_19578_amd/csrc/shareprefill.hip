@@ -249,19 +249,26 @@ void sort_head_list(HeadList &hl, int group, bool dense) {
 // cut into 8 strands each and dealt to the 8 XCDs in contiguous runs, so heads that read the same K/V images
 // (and, for the sparse kernel, walk the same list) run on one XCD together and meet in its L2.
 template <bool DENSE>
-sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipStream_t st) {
+sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipStream_t st,
+                      KernelKind kind = DENSE ? KK_DENSE : KK_SPARSE) {
   const int n = hl.n, group = s->n_q_heads / s->n_kv_heads;
   struct Ent {
     int kvh, map, head, pos;
   } ent[SP_MAX_HEADS];
   for (int a = 0; a < n; ++a) ent[a] = {hl.head[a] / group, DENSE ? 0 : hl.map[a], hl.head[a], a};
-  std::stable_sort(ent, ent + n, [](const Ent &x, const Ent &y) {
-    if (x.kvh != y.kvh) return x.kvh < y.kvh;
-    if (x.map != y.map) return x.map < y.map;
-    return x.head < y.head;
-  });
+  if (!ap.act_pos)  // (positions chosen on the device refer to the caller's order)
+    std::stable_sort(ent, ent + n, [](const Ent &x, const Ent &y) {
+      if (x.kvh != y.kvh) return x.kvh < y.kvh;
+      if (x.map != y.map) return x.map < y.map;
+      return x.head < y.head;
+    });
   ap.n_heads = n;
-  ap.rgroups = (ap.nqb + 7) / 8;
+  // Query blocks of a workgroup (see attn_kernel; the results are the same bits): two where blocks of 64 are walked densely,
+  // for d 64 from 2048 of them on (two rounds of four to a compute unit: below, the chip is not full and a row in a workgroup
+  // of its own ends earlier; with two everywhere 448 blocks took 157.0 us for 154.7, a tiny layer of 32 46.8 for 43.5, and
+  // 1728, of which a gate leaves a part, 255 for 251; 6176 take 744 for 832).
+  const int qb = DENSE && s->block == 64 && (s->head_dim == 128 || (int64_t)s->batch * n * ap.nqb >= 2048) ? 2 : 1;
+  ap.rgroups = (ap.nqb + 8 * qb - 1) / (8 * qb);
   for (int a = 0; a < n; ++a) {
     ap.head_ids[a] = ent[a].head;
     ap.head_map[a] = ent[a].map;
@@ -275,22 +282,25 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
   // a batch entry's workgroups are a multiple of 8, so its first one is again the first XCD's
   dim3 grid((unsigned)(8 * n * ap.rgroups), (unsigned)s->batch);
   const bool sc = DENSE && ap.scores != nullptr;
-  ProfScope prof(DENSE ? KK_DENSE : KK_SPARSE, st);
-#define SP_LAUNCH(D_, B_)                                                                           \
-  do {                                                                                              \
-    if (sc)                                                                                         \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, true, true>), grid, dim3(B_ * 2), 0, st, ap);        \
-    else                                                                                            \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false>), grid, dim3(B_ * 2), 0, st, ap);      \
+  ProfScope prof(kind, st);
+#define SP_LAUNCH(D_, B_, QB_)                                                                                \
+  do {                                                                                                        \
+    if (sc)                                                                                                   \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, DENSE, QB_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);      \
+    else                                                                                                      \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false, QB_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);      \
   } while (0)
+  constexpr int QB = DENSE ? 2 : 1;
   if (s->head_dim == 128 && s->block == 128)
-    SP_LAUNCH(128, 128);
+    SP_LAUNCH(128, 128, 1);
   else if (s->head_dim == 128 && s->block == 64)
-    SP_LAUNCH(128, 64);
+    SP_LAUNCH(128, 64, QB);
   else if (s->head_dim == 64 && s->block == 128)
-    SP_LAUNCH(64, 128);
+    SP_LAUNCH(64, 128, 1);
+  else if (qb == 1)
+    SP_LAUNCH(64, 64, 1);
   else
-    SP_LAUNCH(64, 64);
+    SP_LAUNCH(64, 64, QB);
 #undef SP_LAUNCH
   return hip_check(hipGetLastError(), DENSE ? "dense attn_kernel launch" : "sparse attn_kernel launch");
 }
@@ -1214,7 +1224,8 @@ static sp_status prefill_impl(const sp_shape *shape, const void *q, const void *
       ap.n_q_heads = Hq;
       ap.act_n = cls == 0 ? cp.shared_n : cp.fallback_n;
       ap.act_pos = cls == 0 ? cp.shared_pos : cp.fallback_pos;
-      if ((rc = launch_attn<false>(shape, ap, hl, st))) return rc;
+      if ((rc = cls == 0 ? launch_attn<false>(shape, ap, hl, st) : launch_attn<true>(shape, ap, hl, st, KK_SPARSE)))
+        return rc;
     }
   }
   return SP_OK;
@@ -1438,7 +1449,10 @@ sp_status sp_prefill_layer_dict(const sp_shape *shape, const void *q, const void
         ap.priv_idx = vs_idx;
         ap.priv_cnt = vs_cnt;
       }
-      if ((rc = launch_attn<false>(shape, ap, rl, st))) return rc;
+      // fallback heads without lists of their own walk every key block
+      if ((rc = cls == 0 || vs ? launch_attn<false>(shape, ap, rl, st)
+                               : launch_attn<true>(shape, ap, rl, st, KK_SPARSE)))
+        return rc;
     }
   }
   return SP_OK;

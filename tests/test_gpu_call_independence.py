@@ -94,3 +94,28 @@ def test_search_of_a_head_alone_and_among_others(d, B, nkb):
             for what, a, e in zip(("sums", "lists", "counts"), alone, everything):
                 e = e[b:b + 1, h:h + 1]
                 assert torch.equal(a, e), f"{what}, head {h}, batch entry {b}: {int((a != e).sum())} of {a.numel()} differ"
+
+
+@pytest.mark.parametrize("nqb", [65, 66, 67])
+@pytest.mark.parametrize("scores", [True, False])
+def test_dense_rows_two_to_a_workgroup_and_alone(nqb, scores):
+    """d 64, blocks of 64: 2 x 16 heads have their rows walked two to a workgroup (the first workgroup of an odd number has
+    one row), a single head one to a workgroup."""
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, v = _inputs(41, nqb * 64, 64)
+
+    def run(q, k, v, heads):
+        shape = sp.shape_of(q, k, None, 64)
+        ws = torch.empty(sp.sp_workspace_bytes(shape, len(heads)), dtype=torch.uint8, device="cuda")
+        o = torch.zeros_like(q)
+        sc = torch.full((q.shape[0], len(heads), nqb, nqb), -1.0, dtype=torch.float32, device="cuda") if scores else None
+        sp.sp_dense_attn_with_block_scores(shape, q, k, v, heads, o, sc, ws)
+        torch.cuda.synchronize()
+        return o[:, :, heads], sc
+
+    o_all, s_all = run(q, k, v, list(range(HQ)))
+    for b, h in ((0, 2), (1, 15)):
+        o, s = run(q[b:b + 1], k[b:b + 1], v[b:b + 1], [h])
+        assert torch.equal(o[0, :, 0], o_all[b, :, h])
+        assert s is None or torch.equal(s[0, 0], s_all[b, h])
