@@ -2,6 +2,7 @@
 #ifndef SP_ATTN_KERNEL_H
 #define SP_ATTN_KERNEL_H
 #include "sp_common.h"
+#include "mask_kernel.h"
 
 namespace {
 
@@ -9,6 +10,7 @@ namespace {
 // attention kernel
 // ---------------------------------------------------------------------------------------------
 constexpr int SP_MAX_SLOTS = SP_MAX_HEADS + 8;
+constexpr int SP_FUSED_MASK_MAX = 256;  // key blocks of a row whose list the dense kernel makes itself
 struct AttnParams {
   const uint16_t *q;
   const char *kvp;  // packed K/V images
@@ -20,6 +22,11 @@ struct AttnParams {
   float c;    // softmax scale * log2(e)
   float *lws;     // dense: block-local log2-sum-exp [b][n][nqb(nqb+1)/2][B] (row i, key block j <= i), or null
   float *scores;  // dense: [b][n][nqb][nkb], or null
+  // dense with scores, nkb <= SP_FUSED_MASK_MAX, optional: the row's list (Alg. 2) is made where its scores are:
+  // [b][n][nqb][nkb] and [b][n][nqb], or the map that route ([b][n], negative = none) names in place of b, n
+  int32_t *mask_idx, *mask_cnt;
+  const int32_t *route;
+  uint32_t mask_gq;  // rint(gamma 2^24)
   const int32_t *kb_idx;  // sparse: [b][n_maps][nqb][nkb]
   const int32_t *kb_cnt;  // sparse: [b][n_maps][nqb]
   // sparse, optional: per (batch entry, query head) pattern chosen on the device (Alg. 3's gate):
@@ -737,12 +744,14 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     constexpr int TPL = B / 64, PST = 65, JU = 8;
     constexpr int JB = (1024 + NW * 32 * PST * 4 <= (RK + RV) * IMG) ? 32 : 16;  // key blocks per tile
     constexpr int NPART = 64 / JB, PLEN = 64 / NPART;  // stage 2: NPART lanes share a key block, PLEN entries each
-    static_assert(1024 + NW * JB * PST * 4 <= (RK + RV) * IMG, "score epilogue tiles must fit the idle rings");
+    static_assert(1024 + NW * JB * PST * 4 + QB * SP_FUSED_MASK_MAX * 4 <= (RK + RV) * IMG,
+                  "score epilogue tiles and rows must fit the idle rings");
     float *lse_sh = reinterpret_cast<float *>(smem) + wb * B;  // [QB][B]; the rings are idle now
     float *part = reinterpret_cast<float *>(smem + 1024) + w * (JB * PST);
     __syncthreads();
     if (h == 0) lse_sh[tq] = m + fast_log2(l);
     __syncthreads();
+    float *row_sh = reinterpret_cast<float *>(smem + 1024 + NW * JB * PST * 4) + wb * SP_FUSED_MASK_MAX;
     float lt[TPL];
 #pragma unroll
     for (int tt = 0; tt < TPL; ++tt) lt[tt] = lse_sh[lane + 64 * tt];
@@ -776,13 +785,28 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       for (int kq = 0; kq < PLEN; ++kq) acc += part[jr * PST + jp * PLEN + kq];
       acc = sum_xor32(acc);
       if (NPART == 4) acc += __shfl_xor(acc, 16, 64);
-      if (jp == 0 && j0 + jr <= iw) srow[j0 + jr] = acc * (1.f / B);
+      if (jp == 0 && j0 + jr <= iw) {
+        srow[j0 + jr] = acc * (1.f / B);
+        if (p.mask_idx) row_sh[j0 + jr] = acc * (1.f / B);
+      }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (!idle)
       for (int j = iw + 1 + wr * 64 + lane; j < nkb; j += WB * 64) srow[j] = 0.f;
+    // The row's list, by one wavefront, from the scores in LDS: the same row of mask_kernel, without its launch (5 us behind
+    // the sweep of a short prompt, hidden behind other rows' steps here).
+    if (p.mask_idx) {
+      __syncthreads();
+      if (!idle && wr == 0) {
+        int64_t map = (int64_t)b * p.n_heads + hpos;
+        if (p.route) map = p.route[map];
+        if (map >= 0)
+          mask_row<SP_FUSED_MASK_MAX / 64>(row_sh, lane, iw, nkb, p.mask_gq, p.mask_idx + (map * p.nqb + iw) * nkb,
+                                           p.mask_cnt + map * p.nqb + iw, nullptr);
+      }
+    }
   }
 }
 

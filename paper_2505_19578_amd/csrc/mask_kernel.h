@@ -39,25 +39,11 @@ __device__ __forceinline__ uint32_t quantise24(float s) {
   return (uint32_t)rintf(s * 16777216.f);
 }
 
-// One wavefront per (map, row).  EPL > 0: the row lives in registers (nkb <= 64*EPL);
-// EPL == 0: any nkb, the row is re-read from memory in every pass.
-template <int EPL>
-__global__ __launch_bounds__(256) void mask_kernel(const float *__restrict__ scores, int n_rows_total, int nqb,
-                                                   int nkb, uint32_t gq, int32_t *__restrict__ kb_idx,
-                                                   int32_t *__restrict__ kb_cnt, uint64_t *__restrict__ bitmask,
-                                                   const int32_t *__restrict__ route) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n_rows_total) return;
-  const int i = row % nqb;
-  // route (optional, [n_maps]): the map whose lists this map's rows become, negative = leave this map out
-  int64_t orow = row;
-  if (route) {
-    const int dst = route[row / nqb];
-    if (dst < 0) return;
-    orow = (int64_t)dst * nqb + i;
-  }
-  const float *src = scores + (int64_t)row * nkb;
+// The list of row i from its scores src[0 .. i], by one wavefront: out[nkb], *cnt, optionally bits[ceil(nkb / 64)].
+// EPL > 0: the row lives in registers (nkb <= 64*EPL); EPL == 0: any nkb, the row is re-read in every pass.
+template <int EPL, class Src>
+__device__ __forceinline__ void mask_row(Src src, int lane, int i, int nkb, uint32_t gq, int32_t *__restrict__ out,
+                                         int32_t *__restrict__ cnt, uint64_t *__restrict__ bits) {
   const int nchunk = (i >> 6) + 1;  // 64-wide chunks that hold valid key blocks
   uint32_t u[EPL > 0 ? EPL : 1];
   auto get = [&](int e) -> uint32_t {
@@ -102,7 +88,6 @@ __global__ __launch_bounds__(256) void mask_kernel(const float *__restrict__ sco
     const uint64_t above = sum_ge(vstar + 1u);
     need = (T - above + vstar - 1) / vstar;  // ties taken, lowest key block first
   }
-  int32_t *out = kb_idx + orow * nkb;
   const int nwords = (nkb + 63) >> 6;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t ties_before = 0, n_out = 0;
@@ -126,10 +111,32 @@ __global__ __launch_bounds__(256) void mask_kernel(const float *__restrict__ sco
     const uint64_t smask = __ballot(sel);
     if (sel) out[n_out + __popcll(smask & lt)] = j;
     n_out += __popcll(smask);
-    if (bitmask && lane == 0) bitmask[orow * nwords + e] = smask;
+    if (bits && lane == 0) bits[e] = smask;
   }
   for (int pos = n_out + lane; pos < nkb; pos += 64) out[pos] = -1;
-  if (lane == 0) kb_cnt[orow] = (int32_t)n_out;
+  if (lane == 0) *cnt = (int32_t)n_out;
+}
+
+// One wavefront per (map, row).
+template <int EPL>
+__global__ __launch_bounds__(256) void mask_kernel(const float *__restrict__ scores, int n_rows_total, int nqb,
+                                                   int nkb, uint32_t gq, int32_t *__restrict__ kb_idx,
+                                                   int32_t *__restrict__ kb_cnt, uint64_t *__restrict__ bitmask,
+                                                   const int32_t *__restrict__ route) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= n_rows_total) return;
+  const int i = row % nqb;
+  // route (optional, [n_maps]): the map whose lists this map's rows become, negative = leave this map out
+  int64_t orow = row;
+  if (route) {
+    const int dst = route[row / nqb];
+    if (dst < 0) return;
+    orow = (int64_t)dst * nqb + i;
+  }
+  const int nwords = (nkb + 63) >> 6;
+  mask_row<EPL>(scores + (int64_t)row * nkb, lane, i, nkb, gq, kb_idx + orow * nkb, kb_cnt + orow,
+                bitmask ? bitmask + orow * nwords : nullptr);
 }
 
 }  // namespace

@@ -305,6 +305,17 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
   return hip_check(hipGetLastError(), DENSE ? "dense attn_kernel launch" : "sparse attn_kernel launch");
 }
 
+// Has the dense sweep `ap` make the lists of its scored rows, where their rows are short enough to do so at once (up to 256
+// key blocks: the launch saved is 5 us of 44 of a tiny layer, and nothing at 32K tokens).
+bool fuse_mask(AttnParams &ap, float gamma, int32_t *kb_idx, int32_t *kb_cnt, const int32_t *route = nullptr) {
+  if (!ap.scores || ap.nqb > SP_FUSED_MASK_MAX) return false;
+  ap.mask_idx = kb_idx;
+  ap.mask_cnt = kb_cnt;
+  ap.route = route;
+  ap.mask_gq = (uint32_t)rintf(gamma * 16777216.f);
+  return true;
+}
+
 sp_status launch_mask(const float *scores, int n_maps, int nqb, int nkb, float gamma, int32_t *kb_idx,
                       int32_t *kb_cnt, uint64_t *bitmask, hipStream_t st, const int32_t *route = nullptr) {
   const uint32_t gq = (uint32_t)rintf(gamma * 16777216.f);
@@ -1153,6 +1164,7 @@ static sp_status prefill_impl(const sp_shape *shape, const void *q, const void *
     ap.lws = (float *)(ws + off_lws);
     ap.scores = block_scores;
   }
+  const bool masked = select_mode == SP_SELECT_PER_ROW && fuse_mask(ap, gamma, kb_idx, kb_cnt);
   if ((rc = launch_attn<true>(shape, ap, hl, st))) return rc;
   if (!mass && (rc = launch_mean_logit_scores(shape, q, k, pivot_heads, n_clusters, 0, nqb, block_scores, ws + off_pat, st)))
     return rc;
@@ -1177,7 +1189,9 @@ static sp_status prefill_impl(const sp_shape *shape, const void *q, const void *
       return rc;
   }
   // 3. one pattern per (batch, cluster) (Alg. 2: per query-block row, or over the flattened map)
-  if (select_mode == SP_SELECT_PER_ROW)
+  if (masked)
+    rc = SP_OK;
+  else if (select_mode == SP_SELECT_PER_ROW)
     rc = launch_mask(block_scores, shape->batch * n_clusters, nqb, nqb, gamma, kb_idx, kb_cnt, nullptr, st);
   else
     rc = launch_mask_global(block_scores, shape->batch * n_clusters, nqb, gamma, 1, kb_idx, kb_cnt,
@@ -1400,12 +1414,15 @@ sp_status sp_prefill_layer_dict(const sp_shape *shape, const void *q, const void
       ap.lws = (float *)(ws + off_lws);
       ap.scores = block_scores;
     }
+    const bool masked = select_mode == SP_SELECT_PER_ROW && fuse_mask(ap, gamma, dict->kb_idx, dict->kb_cnt, route);
     if ((rc = launch_attn<true>(shape, ap, hl, st))) return rc;
     if (!mass && (rc = launch_mean_logit_scores(shape, q, k, nullptr, n_slots, 0, nqb, block_scores, ws + off_pat, st,
                                                 pivot_head)))
       return rc;
     // 3. Alg. 2 for the elected slots, written straight into the dictionary
-    if (select_mode == SP_SELECT_PER_ROW)
+    if (masked)
+      rc = SP_OK;
+    else if (select_mode == SP_SELECT_PER_ROW)
       rc = launch_mask(block_scores, shape->batch * n_slots, nqb, nqb, gamma, dict->kb_idx, dict->kb_cnt, nullptr, st,
                        route);
     else
