@@ -24,6 +24,19 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
   add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // lane 31 to rows 2 and 3
   return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  auto join = [&](auto ctrl, auto rows) {
+    x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+  };
+  using std::integral_constant;
+  join(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+  join(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  join(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  join(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  join(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+  join(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
 // Every lane's x below 2^50 (24-bit scores: a lane would have to add 2^26 of them): two halves that cannot overflow.
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
   const uint32_t lo = wave_sum_u32((uint32_t)x & 0xFFFFFFu), hi = wave_sum_u32((uint32_t)(x >> 24));
@@ -79,12 +92,31 @@ __device__ __forceinline__ void mask_row(Src src, int lane, int i, int nkb, uint
   if (tot > 0) {
     uint64_t T = ((uint64_t)gq * tot + 16777215ull) >> 24;  // least integer prefix sum that reaches gamma
     if (T < 1) T = 1;
-    uint32_t lo = 1u, hi = 16777217u;  // sum_ge(lo) >= T > sum_ge(hi)
-    while (hi - lo > 1u) {
-      const uint32_t mid = lo + ((hi - lo) >> 1);
-      if (sum_ge(mid) >= T) lo = mid; else hi = mid;
+    // v* = the largest value with sum_ge(v*) >= T.  It is one of the scores, so a row of up to 128 blocks takes sum_ge of
+    // each of its scores, side by side in the lanes (one pass over the row), and the largest that reaches T.  A longer row
+    // halves an interval 24 times: a chain of wave sums, 3 us (a tiny layer 41.1 -> 38.8 us with the pass).
+    if (EPL > 0 && i < 128) {
+      uint32_t s0 = 0, s1 = 0;  // at most 128 scores of at most 2^24
+      const uint32_t u0 = u[0], u1 = EPL > 1 ? u[EPL > 1 ? 1 : 0] : 0u;
+      for (int j0 = 0; j0 <= i; j0 += 8) {
+        const uint32_t from = j0 < 64 ? u0 : u1;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {  // (scores beyond the row are zero)
+          const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)from, (j0 + x) & 63);
+          s0 += (u0 <= y) ? y : 0u;
+          s1 += (u1 <= y) ? y : 0u;
+        }
+      }
+      const uint32_t t32 = (uint32_t)T;  // T <= tot < 2^32
+      vstar = wave_max_u32(max(s0 >= t32 ? u0 : 0u, s1 >= t32 ? u1 : 0u));
+    } else {
+      uint32_t lo = 1u, hi = 16777217u;  // sum_ge(lo) >= T > sum_ge(hi)
+      while (hi - lo > 1u) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (sum_ge(mid) >= T) lo = mid; else hi = mid;
+      }
+      vstar = lo;
     }
-    vstar = lo;
     const uint64_t above = sum_ge(vstar + 1u);
     need = (T - above + vstar - 1) / vstar;  // ties taken, lowest key block first
   }

@@ -321,3 +321,24 @@ def test_fused_layer_without_returned_scores():
     torch.cuda.synchronize()
     assert torch.equal(idx2, kb_idx) and torch.equal(cnt2, kb_cnt)
     assert torch.equal(o2.view(torch.int16), o.view(torch.int16))
+
+
+@pytest.mark.parametrize("nqb", [1, 2, 63, 65, 127, 128, 129, 255, 256, 257])
+@pytest.mark.parametrize("d,B", [(64, 64), (128, 64), (64, 128)])
+def test_lists_of_a_layer_are_the_selection_over_its_score_maps(nqb, d, B):
+    """The lists come from the sweep itself up to 256 key blocks and from a launch of their own beyond: the same bits as the
+    stand-alone selection over the returned score maps."""
+    import torch
+    import paper_2505_19578_amd as sp
+    from synth import random_qkv
+    from tests.gpu_util import to_dev
+    q, k, v = (to_dev(x) for x in random_qkv(61 + nqb, nqb * B, 2, 1, d, 1.5))
+    shape = sp.shape_of(q, k, None, B)
+    ws = torch.empty(sp.sp_workspace_bytes(shape, 1), dtype=torch.uint8, device="cuda")
+    sc = torch.empty((1, 1, nqb, nqb), dtype=torch.float32, device="cuda")
+    idx, idx2 = (torch.full((1, 1, nqb, nqb), -9, dtype=torch.int32, device="cuda") for _ in range(2))
+    cnt, cnt2 = (torch.full((1, 1, nqb), -9, dtype=torch.int32, device="cuda") for _ in range(2))
+    sp.sp_prefill_layer(shape, q, k, v, [0, 0], [1], 0.9, torch.empty_like(q), sc, idx, cnt, ws)
+    sp.sp_build_block_mask(sc, 1, nqb, nqb, 0.9, idx2, cnt2)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx2) and torch.equal(cnt, cnt2)
