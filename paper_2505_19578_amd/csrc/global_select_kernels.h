@@ -303,57 +303,35 @@ __global__ __launch_bounds__(256) void gsel_emit_flags_kernel(const float *__res
   if (lane == 0) flags[(int64_t)map * g.n_rows + row] = any | (any_after_first << 1);
 }
 
-// The whole selection over plain vectors of at most GSEL_VECTOR_MAX entries, rows of NC * 64, in one launch: a
-// workgroup per vector, histogram, tie counts and threshold in LDS, the vector read four times (from L2 after the
-// first).  It first adds up the borders of the search's slash sums.  Same integers as the eight launches above, which are latency alone on short vectors: the vertical-slash
-// attention of 32 heads (64 vectors) of 8K tokens takes 597 us with them and 578 us with this.
-constexpr int GSEL_VECTOR_MAX = 16384;
-template <int NC>
-__global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeom g, uint32_t gq,
-                                                           int32_t *__restrict__ flags, uint64_t *__restrict__ bits) {
+// The whole selection over one map in one launch, by a workgroup of 1024 threads: rows of at most NC * 64 entries, at most
+// GSEL_ROWS of them, histogram, tie counts and threshold in LDS.  load(row, k) gives entry 64 k + lane of a row (any in-range
+// entry beyond the map), width(row) how many entries it has; emit(row, u, rank, vstar, need) takes its quantised entries (0
+// beyond the row) and the number of ties before it.  The map is read four times (from L2 after the first).  Same integers as
+// the launches above, which are latency alone on a small map.
+constexpr int GSEL_ROWS = 256;
+template <int NC, class Load, class Width, class Emit>
+__device__ __forceinline__ void gsel_whole(int n_rows, uint32_t gq, Load load, Width width, Emit emit) {
   __shared__ unsigned long long hist[GS_BINS];
   __shared__ unsigned long long wt[16];
   __shared__ GselState st;
-  __shared__ uint32_t ties[GSEL_VECTOR_MAX / 64];  // at least as many as there are rows
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, map = blockIdx.x;
-  if (gsel_skip(g, map)) return;
-  float *const vec = vs.sums + (int64_t)map * vs.seq;
-  constexpr int BL = NC * 64, NB = ((VS_PARTS - 1) * BL + 1023) / 1024;
-  const int nb = (vs.n_chunks - 1) * BL;
-  if ((map & 1) && nb > 0) {  // all loads in flight at once
-    const float *low = vs.low + (int64_t)(map >> 1) * vs.n_chunks * BL;
-    float a[NB], b[NB];
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int x = min(tid + 1024 * k, nb - 1);
-      a[k] = low[x];
-      b[k] = vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL];
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int x = tid + 1024 * k;
-      if (x < nb) vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL] = (a[k] + b[k]) * (1.f / BL);
-    }
-  }
-  const float *src = vec + lane;
+  __shared__ uint32_t ties[GSEL_ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // f(row, the row's quantised entries), four rows of a wavefront in flight
   auto each_row = [&](auto f) {
-    for (int r0 = w; r0 < g.n_rows; r0 += 64) {
+    for (int r0 = w; r0 < n_rows; r0 += 64) {
       float x[4][NC];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int e = 0; e < NC; ++e) {
-          const int row = min(r0 + 16 * k, g.n_rows - 1);
-          x[k][e] = src[(int64_t)row * (NC * 64) + e * 64];
-        }
+        for (int e = 0; e < NC; ++e) x[k][e] = load(min(r0 + 16 * k, n_rows - 1), e);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        if (r0 + 16 * k >= g.n_rows) break;
+        const int row = r0 + 16 * k;
+        if (row >= n_rows) break;
         uint32_t u[NC];
 #pragma unroll
-        for (int e = 0; e < NC; ++e) u[e] = quantise24(x[k][e]);
-        f(r0 + 16 * k, u);
+        for (int e = 0; e < NC; ++e) u[e] = e * 64 + lane < width(row) ? quantise24(x[k][e]) : 0u;
+        f(row, u);
       }
     }
   };
@@ -385,7 +363,7 @@ __global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeo
   __syncthreads();
   gsel_scan<2>(hist, &st, wt, gq);
   __syncthreads();
-  const uint32_t vstar = st.vstar;
+  const uint32_t vstar = st.vstar;  // never 0
   const uint64_t need = st.need;
   each_row([&](int row, const uint32_t(&u)[NC]) {
     uint32_t n = 0;
@@ -394,7 +372,7 @@ __global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeo
     if (lane == 0) ties[row] = n;
   });
   __syncthreads();
-  const uint32_t own = tid < g.n_rows ? ties[tid] : 0u;
+  const uint32_t own = tid < n_rows ? ties[tid] : 0u;
   uint32_t incl = own;  // sum over lanes <= this one
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -405,25 +383,93 @@ __global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeo
   __syncthreads();
   uint32_t before_wave = 0;
   for (int x = 0; x < w; ++x) before_wave += (uint32_t)wt[x];
-  if (tid < g.n_rows) ties[tid] = before_wave + incl - own;
+  if (tid < n_rows) ties[tid] = before_wave + incl - own;
   __syncthreads();
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  each_row([&](int row, const uint32_t(&u)[NC]) {
-    uint64_t rank = ties[row];
-    int any = 0, any_after_first = 0;
+  each_row([&](int row, const uint32_t(&u)[NC]) { emit(row, u, (uint64_t)ties[row], vstar, need); });
+}
+
+// Plain vectors of at most GSEL_VECTOR_MAX entries, rows of NC * 64.  The borders of the search's slash sums are added up
+// first.  The vertical-slash attention of 32 heads (64 vectors) of 8K tokens took 597 us with the launches above, 578 with
+// this.
+constexpr int GSEL_VECTOR_MAX = 16384;  // (of rows of 64: GSEL_ROWS)
+template <int NC>
+__global__ __launch_bounds__(1024) void gsel_vector_kernel(VsBorders vs, GselGeom g, uint32_t gq,
+                                                           int32_t *__restrict__ flags, uint64_t *__restrict__ bits) {
+  const int tid = threadIdx.x, lane = tid & 63, map = blockIdx.x;
+  if (gsel_skip(g, map)) return;
+  float *const vec = vs.sums + (int64_t)map * vs.seq;
+  constexpr int BL = NC * 64, NB = ((VS_PARTS - 1) * BL + 1023) / 1024;
+  const int nb = (vs.n_chunks - 1) * BL;
+  if ((map & 1) && nb > 0) {  // all loads in flight at once
+    const float *low = vs.low + (int64_t)(map >> 1) * vs.n_chunks * BL;
+    float a[NB], b[NB];
 #pragma unroll
-    for (int e = 0; e < NC; ++e) {
-      const bool tie = u[e] == vstar;
-      const uint64_t tmask = __ballot(tie);
-      const bool sel = (u[e] > vstar && vstar != 0xFFFFFFFFu) || (tie && rank + __popcll(tmask & lt) < need);
-      rank += __popcll(tmask);
-      const uint64_t smask = __ballot(sel);
-      any |= smask != 0ull;
-      any_after_first |= (e == 0 ? (smask & ~1ull) : smask) != 0ull;
-      if (bits && lane == 0) bits[((int64_t)map * g.n_rows + row) * NC + e] = smask;
+    for (int k = 0; k < NB; ++k) {
+      const int x = min(tid + 1024 * k, nb - 1);
+      a[k] = low[x];
+      b[k] = vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL];
     }
-    if (lane == 0) flags[(int64_t)map * g.n_rows + row] = any | (any_after_first << 1);
-  });
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int x = tid + 1024 * k;
+      if (x < nb) vec[vs.seq - (x / BL + 1) * vs.chunk_keys - x % BL] = (a[k] + b[k]) * (1.f / BL);
+    }
+  }
+  const float *src = vec + lane;
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  gsel_whole<NC>(
+      g.n_rows, gq, [&](int row, int e) { return src[(int64_t)row * (NC * 64) + e * 64]; }, [](int) { return NC * 64; },
+      [&](int row, const uint32_t(&u)[NC], uint64_t rank, uint32_t vstar, uint64_t need) {
+        int any = 0, any_after_first = 0;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+          const bool tie = u[e] == vstar;
+          const uint64_t tmask = __ballot(tie);
+          const bool sel = (u[e] > vstar && vstar != 0xFFFFFFFFu) || (tie && rank + __popcll(tmask & lt) < need);
+          rank += __popcll(tmask);
+          const uint64_t smask = __ballot(sel);
+          any |= smask != 0ull;
+          any_after_first |= (e == 0 ? (smask & ~1ull) : smask) != 0ull;
+          if (bits && lane == 0) bits[((int64_t)map * g.n_rows + row) * NC + e] = smask;
+        }
+        if (lane == 0) flags[(int64_t)map * g.n_rows + row] = any | (any_after_first << 1);
+      });
+}
+
+// Causal maps of at most GSEL_MAP_ROWS rows, lists as gsel_emit_kernel writes them.  A layer with the printed pattern:
+// 9 blocks 99.9 -> 84.2 us, 31 blocks 86.1 -> 71.8, 75 blocks 303 -> 293, 108 blocks 487 -> 477; a workgroup per map is too
+// few beyond (165 blocks 1246 -> 1248, 168 blocks 268 -> 273, 193 blocks 1529 -> 1539).
+constexpr int GSEL_MAP_ROWS = 128;
+template <int NC>
+__global__ __launch_bounds__(1024) void gsel_map_kernel(const float *__restrict__ scores, int nqb, uint32_t gq, int forced,
+                                                        int32_t *__restrict__ kb_idx, int32_t *__restrict__ kb_cnt,
+                                                        const int32_t *__restrict__ route) {
+  const int lane = threadIdx.x & 63, map = blockIdx.x;
+  const int omap = route ? route[map] : map;
+  if (omap < 0) return;
+  const float *src = scores + (int64_t)map * nqb * nqb;
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  gsel_whole<NC>(
+      nqb, gq, [&](int row, int e) { return src[(int64_t)row * nqb + min(e * 64 + lane, row)]; },
+      [](int row) { return row + 1; },
+      [&](int i, const uint32_t(&u)[NC], uint64_t rank, uint32_t vstar, uint64_t need) {
+        int32_t *out = kb_idx + ((int64_t)omap * nqb + i) * nqb;
+        uint32_t n_out = 0;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+          const int j = e * 64 + lane;
+          const bool tie = u[e] == vstar;
+          const uint64_t tmask = __ballot(tie);
+          const bool sel = (j <= i) && ((u[e] > vstar && vstar != 0xFFFFFFFFu) ||
+                                        (tie && rank + __popcll(tmask & lt) < need) || (forced && (j == 0 || j == i)));
+          rank += __popcll(tmask);
+          const uint64_t smask = __ballot(sel);
+          if (sel) out[n_out + __popcll(smask & lt)] = j;
+          n_out += __popcll(smask);
+        }
+        for (int pos = n_out + lane; pos < nqb; pos += 64) out[pos] = -1;
+        if (lane == 0) kb_cnt[(int64_t)omap * nqb + i] = (int32_t)n_out;
+      });
 }
 
 }  // namespace

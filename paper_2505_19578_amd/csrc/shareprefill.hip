@@ -674,6 +674,15 @@ sp_status launch_mask_global(const float *scores, int n_maps, int nqb, float gam
   const int row_groups = (nqb + 3) / 4;
   const dim3 ghist(std::min(row_groups, 64), n_maps), grows(row_groups, n_maps);
   ProfScope prof(KK_MASK, st);
+  if (nqb <= GSEL_MAP_ROWS) {  // one launch instead of eight (the scratch is not used)
+    if (nqb <= 64)
+      hipLaunchKernelGGL(gsel_map_kernel<1>, dim3(n_maps), dim3(1024), 0, st, scores, nqb, gq, forced, kb_idx, kb_cnt,
+                         route);
+    else
+      hipLaunchKernelGGL(gsel_map_kernel<2>, dim3(n_maps), dim3(1024), 0, st, scores, nqb, gq, forced, kb_idx, kb_cnt,
+                         route);
+    return hip_check(hipGetLastError(), "global selection kernel launch");
+  }
   GselGeom g;
   g.n_rows = nqb;
   g.n_cols = nqb;

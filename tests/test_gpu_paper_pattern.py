@@ -218,3 +218,9 @@ def test_llama8b_128k_paper_modes_full_size_and_coverage():
           f"{d_pap:.4f}, covered mass mean {float(cov_pap.mean()):.4f} min {float(cov_pap.min()):.4f}", flush=True)
     assert float(cov_row.min()) >= cfg.gamma - 2e-3         # what the per-row reading guarantees by construction
     assert 0.0 < d_pap < 1.0
+
+
+@pytest.mark.parametrize("n", [63, 127, 128, 129])
+def test_global_mask_builder_at_the_edges_of_the_single_launch(n):
+    """Maps of up to 128 rows are selected over in one launch, two register chunks per row above 64."""
+    test_global_mask_builder_bit_exact(n)
