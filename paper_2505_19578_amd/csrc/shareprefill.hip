@@ -15,7 +15,7 @@
 //                    DENSE=false walks a per-row key-block index list (Sec. 5.1 A(Q,K,V,M)).
 //   mask_kernel      Alg. 2 per query-block row in exact integer arithmetic, one wavefront
 //                    per row: threshold search + ballot/popcount prefix sums.
-//   key_pool_kernel, query_pool_kernel, mean_logit_softmax_kernel, gsel_*_kernel
+//   pool_kernel, mean_logit_softmax_kernel, gsel_*_kernel
 //                    the pattern construction as the paper prints it: row softmax of the
 //                    block-mean QK logits (Sec. 5.2) and Alg. 2 over the flattened map.
 //
@@ -382,11 +382,10 @@ sp_status launch_mean_logit_scores(const sp_shape *s, const void *q, const void 
   pp.c_full = scale / (B * B);
   pp.c_diag = scale / (B * (B + 1.f) * 0.5f);
   ProfScope prof(KK_SCORE, st);
-  dim3 gk(nqb, s->n_kv_heads, s->batch), gq(n_rows, n, s->batch), glog((n_rows + 3) / 4, s->batch * n);
+  const dim3 gpool(nqb * s->n_kv_heads + n_rows * n, s->batch), glog((n_rows + 3) / 4, s->batch * n);
 #define SP_POOL(D_, B_)                                                              \
   do {                                                                               \
-    hipLaunchKernelGGL((key_pool_kernel<D_, B_>), gk, dim3(D_), 0, st, pp);          \
-    hipLaunchKernelGGL((query_pool_kernel<D_, B_>), gq, dim3(D_), 0, st, pp);        \
+    hipLaunchKernelGGL((pool_kernel<D_, B_>), gpool, dim3(D_), 0, st, pp);           \
     hipLaunchKernelGGL((mean_logit_softmax_kernel<D_>), glog, dim3(256), 0, st, pp); \
   } while (0)
   if (s->head_dim == 128 && s->block == 128)
