@@ -98,11 +98,9 @@ __device__ __forceinline__ float sum_bf16x8(bf16x8 v) {
   }
   return a + b;
 }
-__device__ __forceinline__ float max3f(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
+// one v_max3_f32 (as inline assembly it was followed by a wait state wherever its result is used)
+__device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+__device__ __forceinline__ bool any_lane(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
 
 // One wavefront-wide 1 KiB copy HBM/L2 -> LDS without passing through registers: lane l moves the
 // 16 bytes at g_uniform + lane_off to LDS byte address lds_base + 16 l (g_uniform and lds_base are
@@ -343,10 +341,14 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
   };
   // every wavefront moves CH chunks of image `part` of tile t (clamped) into ring slot `slot_base`; a half image is one
   // half of a packed K image, and of every 4 KiB (one 32-dim block) of a packed V image
-  auto img_src = [&](int t, int part, int j, bool is_v) -> const char * {
+  const char *const k_mine = kvbase + w * CH * 1024;  // the wavefront's share of K and V image 0
+  const char *const v_mine = kvbase + PACKED + (KH > 1 ? w * (CH / NKS) * 4096 : w * CH * 1024);
+  auto img_src = [&](int t, int part, int j, auto is_v) __attribute__((always_inline)) -> const char * {
+    constexpr bool V = decltype(is_v)::value;
     const int tt = t < nsub ? t : nsub - 1;
-    const char *src = kvbase + (int64_t)(j * SPB + tt % SPB) * (2 * PACKED) + (is_v ? PACKED : 0);
-    return KH == 1 ? src : src + part * (is_v ? NKS * 1024 : IMG);
+    // (the compiler loses sight of it being uniform; at most 2^16 tiles, 2^31 bytes)
+    const uint32_t tile = __builtin_amdgcn_readfirstlane(DENSE ? tt : j * SPB + tt % SPB);
+    return (V ? v_mine : k_mine) + tile * (uint32_t)(2 * PACKED) + (KH == 1 ? 0 : part * (V ? NKS * 1024 : IMG));
   };
   // chunk n (0 .. CH-1) of this wavefront's share of an image.  The chunk number goes into the instruction's offset: with
   // an address computed per chunk, a step of d 128 had 14 scalar instructions more.  That shows where a wavefront is alone
@@ -356,11 +358,10 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     constexpr int n = decltype(nc)::value;
     constexpr bool HALF_V = KH > 1 && decltype(is_v)::value;  // NKS KiB of every 4 KiB of the packed image
     static_assert(!HALF_V || CH % NKS == 0, "a wavefront's share of a half V image starts at a 4 KiB piece");
-    lds_dma16<n * 1024>(src + (HALF_V ? w * (CH / NKS) * 4096 + n / NKS * (4096 - NKS * 1024) : w * CH * 1024), lane * 16,
-                        slot_base + w * CH * 1024);
+    lds_dma16<n * 1024>(src + (HALF_V ? n / NKS * (4096 - NKS * 1024) : 0), lane * 16, slot_base + w * CH * 1024);
   };
   auto issue_img = [&](int t, int part, int j, auto is_v, uint32_t slot_base) __attribute__((always_inline)) {
-    const char *src = img_src(t, part, j, decltype(is_v)::value);
+    const char *src = img_src(t, part, j, is_v);
     static_for<0, CH>([&](auto nc) __attribute__((always_inline)) { issue_chunk(src, slot_base, nc, is_v); });
   };
   using IsK = std::false_type;
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
   };
   // what a tile's steps hand on to one another: two halves of its row sum, the row max of the next tile, the sum of the
   // weights as PV sees them
-  float rs0, rs1, mx, psum;
+  float rs0, rs1, mx, mx_odd, psum;
   // QB > 1: the general steps of a workgroup begin at its first block's diagonal.  A wavefront's tiles before twice_from,
   // which it would take by fast steps in a workgroup of its own, are summed as those do: the same bits either way.
   int twice_from = 0;
@@ -454,11 +455,11 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       const float d = sum_xor32(psum) - rs;
       const bool early = QB > 1 && t < twice_from;
       lc += early ? 0.f : d;
-      lc_later = early && __any(care) ? d : 0.f;
+      lc_later = early && any_lane(care) ? d : 0.f;
     }
   };
   auto rescale = [&](float alpha) {
-    if (__any(alpha != 1.f)) {
+    if (any_lane(alpha != 1.f)) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -475,6 +476,16 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
         });
   };
 
+  // Byte offsets of the V slots: of the image that this step reads, and of the one before it, which is refilled (DV = RV - 1).
+  // Carried along: a remainder by three is eight scalar instructions.  With the image addresses in 32 bits, the row max as
+  // fmaxf in two chains and the tests of a lane mask as scalar compares, a step of d 128 went from 378 to 358 instructions
+  // (128K layer 52.2 -> 51.4 ms, 32K 3428 -> 3369 us, tiny 38.8 -> 37.7).
+  static_assert(DV == RV - 1, "the slot to refill is the previous step's");
+  uint32_t v_now = 0, v_old = (RV - 1) * IMG;
+  auto next_v = [&]() {
+    v_old = v_now;
+    v_now = v_now == (RV - 1) * IMG ? 0 : v_now + IMG;
+  };
   // On entry to the steps of tile t: s_cur = raw S[t] (masked where needed), m / l / bs / O already moved to the
   // running max that includes tile t.  jt[x] = key block of tile t + x.
   // sync: wait until the images this step reads have landed for every wavefront; the ring slots that the previous step
@@ -492,12 +503,13 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     // the ring refills (K, then V) are dropped one chunk at a time into the MFMA groups below instead of going out in a
     // burst after the barrier
     sync();
-    const char *ksrc = img_src(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], false);
+    const char *ksrc = img_src(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], IsK{});
     const uint32_t kslot = lds_k + ((u0 + DK) % RK) * IMG;
-    const char *vsrc = img_src(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], true);
-    const uint32_t vslot = lds_v + ((u0 + DV) % RV) * IMG;
+    const char *vsrc = img_src(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], IsV{});
+    const uint32_t vslot = lds_v + v_old;
     const char *kb = smem + ((u0 + KH) % RK) * IMG + lane * 16;
-    const char *vb = smem + (RK + u0 % RV) * IMG + lane * 16;
+    const char *vb = smem + RK * IMG + v_now + lane * 16;
+    next_v();
     // Hand-laid schedule: NM groups, each = one MFMA + one LDS read (PF fragments ahead) + a slice
     // of the VALU work; nothing may cross a group boundary (sched_barrier).
     //   groups 0 .. NQ-1   : S[t+1] += K frag * Q frag ; exp / row-sum / bf16 pack of S[t]
@@ -585,13 +597,14 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
           if (2 + u * (NP - 2 - MAXTAIL) / NU != np) continue;
           const f32x16 &s = s_next[P * NR + u / 8];
           const float a0 = s[2 * (u % 8)], a1 = s[2 * (u % 8) + 1];
-          mx = (P == 0 && u == 0) ? fmaxf(a0, a1) : max3f(mx, a0, a1);
+          float &m2 = u % 2 ? mx_odd : mx;  // two chains
+          m2 = (P == 0 && u < 2) ? fmaxf(a0, a1) : max3f(m2, a0, a1);
         }
-        if (LAST && np == NP - MAXTAIL) alpha = move_reference(max_xor32(mx));
+        if (LAST && np == NP - MAXTAIL) alpha = move_reference(max_xor32(fmaxf(mx, mx_odd)));
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (__any(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
+    if (any_lane(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
       add_p(part, pb);
       if (LAST) lc += (sum_xor32(psum) - rs_tile) * alpha;
     }
@@ -608,9 +621,10 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     sync();
     issue_img(t + (P + DK) / KH, (P + DK) % KH, jt[(P + DK) / KH], IsK{}, lds_k + ((u0 + DK) % RK) * IMG);
-    issue_img(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], IsV{}, lds_v + ((u0 + DV) % RV) * IMG);
+    issue_img(t + (P + DV) / KH, (P + DV) % KH, jt[(P + DV) / KH], IsV{}, lds_v + v_old);
     const char *k_next = smem + ((u0 + KH) % RK) * IMG;
-    const char *v_cur = smem + (RK + u0 % RV) * IMG;
+    const char *v_cur = smem + RK * IMG + v_now;
+    next_v();
     const int sub = t % SPB, sub1 = (t + 1) % SPB;
     const int mode0 = mode_of(jt[0], sub);
     const int mode1 = (t + 1 < nsub) ? mode_of(jt[1], sub1) : 2;

@@ -533,7 +533,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     lc += sum_xor32(sum_bf16x8(pb[0]) + sum_bf16x8(pb[1]) + sum_bf16x8(pb[2]) + sum_bf16x8(pb[3])) - rs;
   };
   auto rescale = [&](float alpha) {
-    if (__any(alpha != 1.f)) {
+    if (any_lane(alpha != 1.f)) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     bf16x8 fr[PF + 1];
     bf16x8 pb[4];
     u32x4 pt;
-    float rs0 = 0.f, rs1 = 0.f, mx = 0.f, alpha = 1.f, rs_tile = 0.f;
+    float rs0 = 0.f, rs1 = 0.f, mx = 0.f, mx_odd = 0.f, alpha = 1.f, rs_tile = 0.f;
     const bool care_t = care;  // set when this tile's max was taken
     float xa[16], xb[16];
     uint64_t Mnn = 0ull;
@@ -644,15 +644,16 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
           }
           if (gm == np) {
             const float a0 = s_next[rb][r], a1 = s_next[rb][r + 1];
-            mx = (u == 0) ? fmaxf(a0, a1) : max3f(mx, a0, a1);
+            float &m2 = u % 2 ? mx_odd : mx;  // two chains
+            m2 = (u < 2) ? fmaxf(a0, a1) : max3f(m2, a0, a1);
           }
         }
-        if (np == NP - MAXTAIL) alpha = move_reference(max_xor32(mx));
+        if (np == NP - MAXTAIL) alpha = move_reference(max_xor32(fmaxf(mx, mx_odd)));
         if (MASKED && np == NP - 2) Mnn = mask_lane(pre2);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (__any(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
+    if (any_lane(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
       asm volatile("" ::: "memory");  // a real branch: not to be evaluated on every step
       lc += (sum_xor32(sum_bf16x8(pb[0]) + sum_bf16x8(pb[1]) + sum_bf16x8(pb[2]) + sum_bf16x8(pb[3])) - rs_tile) * alpha;
     }
@@ -668,7 +669,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     asm volatile("" ::: "memory");
     issue_img(it2, false, lds_k + ((t + 2) % RK) * IMG);
     issue_img(it2, true, lds_v + ((t + 2) % RV) * IMG);
-    const bool act_next = __any(Mn != 0ull);
+    const bool act_next = any_lane(Mn != 0ull);
     if (act_next) qk(smem + ((t + 1) % RK) * IMG, s_next);
     if (act_cur) {
       bf16x8 pb[4];
