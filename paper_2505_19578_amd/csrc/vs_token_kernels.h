@@ -417,8 +417,10 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
            (uint32_t)__builtin_amdgcn_readlane(it_lane[2], t & 63);
     return it;
   };
+  // this wavefront's share of an item's K image (at most 2^16 images, 2^31 bytes)
+  const char *const kv_mine = kvbase + w * CH * 1024, *const g_mine = gbase + w * CH * 1024;
   auto item_src = [&](const VsItem &it) -> const char * {
-    return ((it.code & VS_GATHERED) ? gbase : kvbase) + (int64_t)(it.code & ~VS_GATHERED) * STAGE;
+    return ((it.code & VS_GATHERED) ? g_mine : kv_mine) + (it.code & ~VS_GATHERED) * (uint32_t)STAGE;
   };
   // word idx of a bitmap, 0 outside it (idx is wave-uniform)
   auto uword = [&](int idx) -> uint64_t {
@@ -438,9 +440,14 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     pre.start0 = 64 * x + 32 * w - 63;
     pre.top0 = 32 * w + 64 * x;
     pre.v = it.v;
-    const int wi0 = (it.code & VS_GATHERED) ? -2 : pre.start0 >> 6;  // floor, also for negative positions
-    pre.w0 = uword(wi0);
-    pre.w1 = uword(wi0 + 1);
+    if (it.code < (uint32_t)(i * SPB)) {  // a tile below the row: x >= 1, both words lie in the bitmap
+      pre.w0 = bs[pre.start0 >> 6];
+      pre.w1 = bs[(pre.start0 >> 6) + 1];
+    } else {
+      const int wi0 = (it.code & VS_GATHERED) ? -2 : pre.start0 >> 6;  // floor, also for negative positions
+      pre.w0 = uword(wi0);
+      pre.w1 = uword(wi0 + 1);
+    }
     return pre;
   };
   auto mask_lane = [&](const VsMaskPre &pre) -> uint64_t {
@@ -460,7 +467,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     lds_dma16<OFF - HI>(src + HI, lane * 16, slot_base + w * CH * 1024 + HI);
   };
   auto issue_img = [&](const VsItem &it, bool is_v, uint32_t slot_base) __attribute__((always_inline)) {
-    const char *src = item_src(it) + (is_v ? IMG : 0) + (w * CH) * 1024;
+    const char *src = item_src(it) + (is_v ? IMG : 0);
     static_for<0, CH>([&](auto nc) __attribute__((always_inline)) { issue_chunk(src, slot_base, nc); });
   };
   auto qk = [&](const char *kbuf, f32x16(&s)[2]) {
@@ -550,6 +557,12 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
         });
   };
 
+  // byte offsets of the V slots: of item t's image and of the one before it, which item t + 2 refills (as in attn_kernel)
+  uint32_t v_now = 0, v_old = (RV - 1) * IMG;
+  auto next_v = [&]() {
+    v_old = v_now;
+    v_now = v_now == (RV - 1) * IMG ? 0 : v_now + IMG;
+  };
   // On entry to step t: s_cur = masked raw S[t] with its max folded into m / l / O (if this wavefront has anything
   // in item t), Mn = the mask of item t+1, it2 / pre2 = item t+2 and the uniform part of its mask.  Every step
   // returns the mask of item t+2.
@@ -560,10 +573,11 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     wait_vm<VM_KEEP>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const char *ksrc = item_src(it2) + (w * CH) * 1024, *vsrc = ksrc + IMG;
-    const uint32_t kslot = lds_k + ((t + 2) % RK) * IMG, vslot = lds_v + ((t + 2) % RV) * IMG;
+    const char *ksrc = item_src(it2), *vsrc = ksrc + IMG;
+    const uint32_t kslot = lds_k + ((t + 2) % RK) * IMG, vslot = lds_v + v_old;
     const char *kb = smem + ((t + 1) % RK) * IMG + lane * 16;
-    const char *vb = smem + (RK + t % RV) * IMG + lane * 16;
+    const char *vb = smem + RK * IMG + v_now + lane * 16;
+    next_v();
     const uint32_t mw0 = (uint32_t)Mn >> (4 * h), mw1 = (uint32_t)(Mn >> 32) >> (4 * h);
     // NM groups, each = one MFMA + one LDS read (PF fragments ahead) + a slice of the VALU work:
     //   groups 0 .. NQ-1   : S[t+1] += K frag * Q frag ; exp / row-sum / bf16 pack of S[t]
@@ -668,13 +682,15 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     issue_img(it2, false, lds_k + ((t + 2) % RK) * IMG);
-    issue_img(it2, true, lds_v + ((t + 2) % RV) * IMG);
+    issue_img(it2, true, lds_v + v_old);
+    const char *v_cur = smem + RK * IMG + v_now;
+    next_v();
     const bool act_next = any_lane(Mn != 0ull);
     if (act_next) qk(smem + ((t + 1) % RK) * IMG, s_next);
     if (act_cur) {
       bf16x8 pb[4];
       tile_exp(s_cur, pb);
-      pv(smem + (RK + t % RV) * IMG, pb);
+      pv(v_cur, pb);
     }
     if (act_next) {
       if (!__all(Mn == ~0ull)) apply_mask(s_next, Mn);
