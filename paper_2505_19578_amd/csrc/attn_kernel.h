@@ -114,6 +114,22 @@ __device__ __forceinline__ void lds_dma16(const void *g_uniform, uint32_t lane_o
                "v"(lane_off), "s"(g_uniform), "n"(OFF)
                : "memory", "m0");
 }
+// The chunks at OFF and OFF + 1024, for one setting of M0.
+template <int OFF>
+__device__ __forceinline__ void lds_dma16_pair(const void *g_uniform, uint32_t lane_off, uint32_t lds_base) {
+  static_assert(OFF >= 0 && OFF + 1024 < 4096, "13-bit signed immediate");
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3\n\tglobal_load_lds_dwordx4 %1, %2 offset:%4" ::
+          "s"(lds_base),
+      "v"(lane_off), "s"(g_uniform), "n"(OFF), "n"(OFF + 1024)
+      : "memory", "m0");
+}
+// wait until at most N LDS reads are in flight (the compiler takes it into account)
+template <int N>
+__device__ __forceinline__ void wait_lds() {
+  static_assert(N >= 0 && N < 16, "4-bit counter");
+  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -525,7 +541,13 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       const int np = n - NQ;
       return *reinterpret_cast<const bf16x8 *>(vb + ((np % DB) * NKS + np / DB) * 1024);
     };
-    bf16x8 fr[PF + 1];
+    // Whole images: LDS reads and ring refills two at a time, with one wait and one setting of M0 for both.  Bound by the
+    // instructions it issues, a wavefront alone on its SIMD gains (tiny layer 37.6 -> 36.4 us, 7K d 64 145.0 -> 139.8, 4K
+    // 135.8 -> 134.8); two on one SIMD do not lose.  Half images: the reads' wait comes too early (gated 776 -> 779).  Three
+    // wavefronts per SIMD have no registers for a further fragment.
+    constexpr bool READ2 = KH == 1 && WAVES == 2, REFILL2 = KH == 1;
+    constexpr int NF = PF + (READ2 ? 2 : 1);
+    bf16x8 fr[NF];
     bf16x8 pb[NKS];
     u32x4 pt;
     if (P == 0) rs0 = rs1 = 0.f;
@@ -537,16 +559,25 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     __builtin_amdgcn_sched_barrier(0);  // all PF reads in flight before the first MFMA waits for one of them
     static_for<0, NM>([&](auto nc) __attribute__((always_inline)) {
       constexpr int n = decltype(nc)::value;
-      if (n + PF < NM) fr[(n + PF) % (PF + 1)] = frag(n + PF);
+      if constexpr (!READ2) {
+        if (n + PF < NM) fr[(n + PF) % NF] = frag(n + PF);
+      } else if constexpr (n % 2 == 0) {
+        static_assert(NM % 2 == 0 && PF % 2 == 0, "fragments come in pairs");
+        if constexpr (n + PF < NM) {
+          fr[(n + PF) % NF] = frag(n + PF);
+          fr[(n + PF + 1) % NF] = frag(n + PF + 1);
+        }
+        wait_lds<(n + PF < NM ? PF : NM - 2 - n)>();  // fragments n and n + 1 are there
+      }
       if (n < NQ) {
         if (n < NR) {
           f32x16 z;
 #pragma unroll
           for (int r = 0; r < 16; ++r) z[r] = 0.f;
-          s_next[P * NR + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[0], z, 0, 0, 0);
+          s_next[P * NR + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % NF], qf[0], z, 0, 0, 0);
         } else {
           f32x16 &s = s_next[P * NR + n % NR];
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], qf[n / NR], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % NF], qf[n / NR], s, 0, 0, 0);
         }
       }
       // exp units u (2 scores each), three stages in consecutive groups so that no instruction waits
@@ -583,13 +614,20 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       {
         constexpr int GAP = NM / (2 * CH);  // groups between two chunk loads
         constexpr int x = n / GAP;
-        if constexpr (n % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{}, IsK{});
-        if constexpr (n % GAP == 1 && x >= CH && x < 2 * CH)
-          issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{}, IsV{});
+        if constexpr (REFILL2) {
+          static_assert(CH % 2 == 0, "a wavefront's share of an image is pairs of chunks");
+          if constexpr (n % (2 * GAP) == 1 && x < CH) lds_dma16_pair<x * 1024>(ksrc, lane * 16, kslot + w * CH * 1024);
+          if constexpr (n % (2 * GAP) == 1 && x >= CH && x < 2 * CH)
+            lds_dma16_pair<(x - CH) * 1024>(vsrc, lane * 16, vslot + w * CH * 1024);
+        } else {
+          if constexpr (n % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{}, IsK{});
+          if constexpr (n % GAP == 1 && x >= CH && x < 2 * CH)
+            issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{}, IsV{});
+        }
       }
       if (n >= NQ) {
         const int np = n - NQ;
-        oacc[np % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % (PF + 1)], pb[np / DB], oacc[np % DB], 0, 0, 0);
+        oacc[np % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % NF], pb[np / DB], oacc[np % DB], 0, 0, 0);
         // row max of S[t+1]: NU max3 units spread over groups 2 .. NP-1-MAXTAIL, then the running-max
         // update MAXTAIL groups before the end (its dependent chain hides under the last MFMAs)
 #pragma unroll
