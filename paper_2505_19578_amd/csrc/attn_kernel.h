@@ -274,7 +274,7 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
   float m = -INFINITY, l = 0.f, bs = 0.f;
   float lc = 0.f;     // sum of bf16(p) - p over the tiles summed twice (see SP_CARE)
-  bool care = true;   // the tile whose max was taken last may hold a weight that matters
+  bool care = true;   // the tile whose max was taken last may hold a weight that matters, for any lane
 
   // A list is read 64 entries at a time into registers, a chunk ahead (entry e of the row = lane e % 64 of chunk e / 64); its
   // first chunk goes out together with the number of entries.  A load per entry inside the loop had every second step wait
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     l *= alpha;
     bs *= alpha;
     lc *= alpha;
-    care = fast_exp2(__builtin_fmaf(mx, p.c, -m_new)) * SP_CARE > l;
+    care = any_lane(fast_exp2(__builtin_fmaf(mx, p.c, -m_new)) * SP_CARE > l);
     return alpha;
   };
   // Online softmax, split in two halves that sit in different pipeline steps.
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       const float d = sum_xor32(psum) - rs;
       const bool early = QB > 1 && t < twice_from;
       lc += early ? 0.f : d;
-      lc_later = early && any_lane(care) ? d : 0.f;
+      lc_later = early && care ? d : 0.f;
     }
   };
   auto rescale = [&](float alpha) {
@@ -543,8 +543,9 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     };
     // Whole images: LDS reads and ring refills two at a time, with one wait and one setting of M0 for both.  Bound by the
     // instructions it issues, a wavefront alone on its SIMD gains (tiny layer 37.6 -> 36.4 us, 7K d 64 145.0 -> 139.8, 4K
-    // 135.8 -> 134.8); two on one SIMD do not lose.  Half images: the reads' wait comes too early (gated 776 -> 779).  Three
-    // wavefronts per SIMD have no registers for a further fragment.
+    // 135.8 -> 134.8); two on one SIMD do not lose.  The wait is fenced from the products behind it, which otherwise get waits
+    // of their own again (4K 134.2 -> 132.0, lists of 98K 19.50 -> 19.24 ms).  Half images: the reads' wait comes too early
+    // (gated 776 -> 779).  Three wavefronts per SIMD have no registers for a further fragment.
     constexpr bool READ2 = KH == 1 && WAVES == 2, REFILL2 = KH == 1;
     constexpr int NF = PF + (READ2 ? 2 : 1);
     bf16x8 fr[NF];
@@ -563,11 +564,12 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
         if (n + PF < NM) fr[(n + PF) % NF] = frag(n + PF);
       } else if constexpr (n % 2 == 0) {
         static_assert(NM % 2 == 0 && PF % 2 == 0, "fragments come in pairs");
+        wait_lds<(n + PF <= NM ? PF : NM - n) - 2>();  // fragments n and n + 1 are there
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (n + PF < NM) {
           fr[(n + PF) % NF] = frag(n + PF);
           fr[(n + PF + 1) % NF] = frag(n + PF + 1);
         }
-        wait_lds<(n + PF < NM ? PF : NM - 2 - n)>();  // fragments n and n + 1 are there
       }
       if (n < NQ) {
         if (n < NR) {
@@ -642,7 +644,7 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (any_lane(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
+    if (care_t) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
       add_p(part, pb);
       if (LAST) lc += (sum_xor32(psum) - rs_tile) * alpha;
     }

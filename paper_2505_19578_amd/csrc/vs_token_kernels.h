@@ -508,7 +508,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     mref = mref_new;
     l *= alpha;
     lc *= alpha;
-    care = fast_exp2(__builtin_fmaf(mx, p.c, -mref_new)) * SP_CARE > l;
+    care = any_lane(fast_exp2(__builtin_fmaf(mx, p.c, -mref_new)) * SP_CARE > l);
     return alpha;
   };
   auto tile_max = [&](f32x16(&s)[2]) -> float {
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if (any_lane(care_t)) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
+    if (care_t) {  // rare: the tile summed again as PV saw it (alpha already holds the move after this tile)
       asm volatile("" ::: "memory");  // a real branch: not to be evaluated on every step
       lc += (sum_xor32(sum_bf16x8(pb[0]) + sum_bf16x8(pb[1]) + sum_bf16x8(pb[2]) + sum_bf16x8(pb[3])) - rs_tile) * alpha;
     }
