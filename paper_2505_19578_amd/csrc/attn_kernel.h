@@ -551,7 +551,6 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
     bf16x8 fr[NF];
     bf16x8 pb[NKS];
     u32x4 pt;
-    if (P == 0) rs0 = rs1 = 0.f;
     float lval = 0.f, alpha = 1.f, rs_tile = 0.f;
     const bool care_t = care;  // set when this tile's max was taken
     float xa[NU], xb[NU];
@@ -597,8 +596,8 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
           xb[u] = fast_exp2(xb[u]);
         }
         if (gu + 2 == n) {
-          rs0 += xa[u];
-          rs1 += xb[u];
+          rs0 = (P == 0 && u == 0) ? xa[u] : rs0 + xa[u];
+          rs1 = (P == 0 && u == 0) ? xb[u] : rs1 + xb[u];
           pt[e2] = pack_bf16(xa[u], xb[u]);
           if (e2 == 3) pb[ks] = __builtin_bit_cast(bf16x8, pt);
         }

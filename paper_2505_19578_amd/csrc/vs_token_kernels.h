@@ -579,18 +579,22 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     const char *vb = smem + RK * IMG + v_now + lane * 16;
     next_v();
     const uint32_t mw0 = (uint32_t)Mn >> (4 * h), mw1 = (uint32_t)(Mn >> 32) >> (4 * h);
-    // NM groups, each = one MFMA + one LDS read (PF fragments ahead) + a slice of the VALU work:
+    // NM groups, each = one MFMA + half of two LDS reads (PF fragments ahead) + a slice of the VALU work:
     //   groups 0 .. NQ-1   : S[t+1] += K frag * Q frag ; exp / row-sum / bf16 pack of S[t]
     //   groups NQ .. NM-1  : O += V frag * P frag       ; mask and row max of S[t+1], reference update,
     //                                                     the mask of item t+2
     constexpr int NQ = 2 * DS, NP = 4 * DB, NM = NQ + NP;
-    constexpr int PF = 3, MAXTAIL = 4;
+    // Reads and refills go two at a time with one wait a pair, as in attn_kernel (with three fragments ahead and each wait left
+    // to the compiler: n = 3904 d128 block 64 220.8 -> 216.2 us, 40K dictionary layers 31.56 -> 31.29 ms, 8K 412.1 -> 409.5 us,
+    // 128K 38.18 -> 37.97 ms).  A wavefront that issues all eight chunks (d128, block 64) keeps single refills.
+    constexpr int PF = 4, MAXTAIL = 4;
+    constexpr int NF = PF + 2;
     auto frag = [&](int g) -> bf16x8 {
       if (g < NQ) return *reinterpret_cast<const bf16x8 *>(kb + ((g % 2) * DS + g / 2) * 1024);
       const int np = g - NQ;
       return *reinterpret_cast<const bf16x8 *>(vb + ((np % DB) * 4 + np / DB) * 1024);
     };
-    bf16x8 fr[PF + 1];
+    bf16x8 fr[NF];
     bf16x8 pb[4];
     u32x4 pt;
     float rs0 = 0.f, rs1 = 0.f, mx = 0.f, mx_odd = 0.f, alpha = 1.f, rs_tile = 0.f;
@@ -602,15 +606,22 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NM>([&](auto gc) __attribute__((always_inline)) {
       constexpr int g = decltype(gc)::value;
-      if (g + PF < NM) fr[(g + PF) % (PF + 1)] = frag(g + PF);
+      if constexpr (g % 2 == 0) {
+        wait_lds<(g + PF <= NM ? PF : NM - g) - 2>();  // fragments g and g + 1 are there
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (g + PF < NM) {
+          fr[(g + PF) % NF] = frag(g + PF);
+          fr[(g + PF + 1) % NF] = frag(g + PF + 1);
+        }
+      }
       if (g < NQ) {
         if (g < 2) {
           f32x16 z;
 #pragma unroll
           for (int r = 0; r < 16; ++r) z[r] = 0.f;
-          s_next[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % (PF + 1)], qf[0], z, 0, 0, 0);
+          s_next[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % NF], qf[0], z, 0, 0, 0);
         } else {
-          s_next[g % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % (PF + 1)], qf[g / 2], s_next[g % 2], 0, 0, 0);
+          s_next[g % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % NF], qf[g / 2], s_next[g % 2], 0, 0, 0);
         }
       }
       // exp units u (2 scores each), three stages in consecutive groups
@@ -627,8 +638,8 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
           xb[u] = fast_exp2(xb[u]);
         }
         if (gu + 2 == g) {
-          rs0 += xa[u];
-          rs1 += xb[u];
+          rs0 = u == 0 ? xa[u] : rs0 + xa[u];
+          rs1 = u == 0 ? xb[u] : rs1 + xb[u];
           pt[e2] = pack_bf16(xa[u], xb[u]);
           if (e2 == 3) pb[ks] = __builtin_bit_cast(bf16x8, pt);
         }
@@ -640,12 +651,18 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
       {
         constexpr int GAP = NM / (2 * CH);  // groups between two chunk loads
         constexpr int x = g / GAP;
-        if constexpr (g % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{});
-        if constexpr (g % GAP == 1 && x >= CH && x < 2 * CH) issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{});
+        if constexpr (CH <= 4) {
+          if constexpr (g % (2 * GAP) == 1 && x < CH) lds_dma16_pair<x * 1024>(ksrc, lane * 16, kslot + w * CH * 1024);
+          if constexpr (g % (2 * GAP) == 1 && x >= CH && x < 2 * CH)
+            lds_dma16_pair<(x - CH) * 1024>(vsrc, lane * 16, vslot + w * CH * 1024);
+        } else {
+          if constexpr (g % GAP == 1 && x < CH) issue_chunk(ksrc, kslot, std::integral_constant<int, x>{});
+          if constexpr (g % GAP == 1 && x >= CH && x < 2 * CH) issue_chunk(vsrc, vslot, std::integral_constant<int, x - CH>{});
+        }
       }
       if (g >= NQ) {
         const int np = g - NQ;
-        oacc[np % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % (PF + 1)], pb[np / DB], oacc[np % DB], 0, 0, 0);
+        oacc[np % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g % NF], pb[np / DB], oacc[np % DB], 0, 0, 0);
         // S[t+1]: 16 units of two scores, masked one group before they enter the row max; the reference update
         // MAXTAIL groups before the end
 #pragma unroll
