@@ -1235,7 +1235,7 @@ static sp_status prefill_impl(const sp_shape *shape, const void *q, const void *
     cp.n_q_heads = Hq;
     cp.n_launch = hl.n;
     for (int a = 0; a < hl.n; ++a) cp.launch_head[a] = hl.head[a];
-    hipLaunchKernelGGL(classify_heads_kernel, dim3(shape->batch), dim3(64), 0, st, cp);
+    hipLaunchKernelGGL(classify_heads_kernel, dim3(shape->batch), dim3(128), 0, st, cp);
     if ((rc = hip_check(hipGetLastError(), "classify_heads_kernel launch"))) return rc;
     for (int cls = 0; cls < 2; ++cls) {
       fill_attn(ap, shape, q, workspace, o);

@@ -294,3 +294,86 @@ def test_dict_paper_thresholds_on_the_spread_workload():
     assert (roles[1] >= 0).sum() > (roles[1] == -1).sum() > 0
     ds = g[0]["dist"][:, 0]
     assert ds.min() < 0.3 < ds.max(), "the workload must straddle the sparsity threshold"
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(63, 9), (64, 8), (65, 13), (128, 16)])
+def test_elections_and_head_lists_at_the_edges_of_a_wavefront(Hq, Hkv):
+    """Elections and the lists of sharing and falling-back heads are made 64 at a time: the roles against a walk of Alg. 1
+    over the distances reported, and, with gamma = 1 (every list is whole), each head's output against dense attention, for
+    the dictionary layer and the gated layer.  Two prompts in a batch, clusters and heads without one in random order."""
+    import torch
+    import paper_2505_19578_amd as sp
+    n, d, B, nb, C = 512, 64, 64, 2, 40
+    nqb = n // B
+    rng = np.random.default_rng(Hq)
+    gen = torch.Generator(device="cuda").manual_seed(Hq)
+    h2c = [int(x) for x in rng.integers(-1, C, Hq)]
+    D = _Dict(sp, nb, C, nqb)
+    clusters = sorted({c for c in h2c if c >= 0})
+
+    def dense(q, k, v):
+        qf, kf, vf = q.float(), k.float().repeat_interleave(Hq // Hkv, 2), v.float().repeat_interleave(Hq // Hkv, 2)
+        causal = torch.ones((n, n), dtype=torch.bool, device="cuda").tril()
+        o = torch.empty_like(qf)
+        for b in range(nb):
+            for h in range(Hq):
+                s = (qf[b, :, h] @ kf[b, :, h].T) / d ** 0.5
+                o[b, :, h] = torch.softmax(s.masked_fill(~causal, float("-inf")), -1) @ vf[b, :, h]
+        return o
+
+    def close(o, want):
+        e = (o.float() - want).abs()
+        assert not torch.isnan(e).any() and float(e.max()) <= OUT_MAX and float(e.mean()) <= OUT_MEAN
+
+    delta = tau = None
+    for layer in range(2):
+        amp = torch.linspace(0.2, 3.0, Hq, device="cuda")[torch.randperm(Hq, device="cuda", generator=gen)]
+        q = (torch.randn((nb, n, Hq, d), device="cuda", generator=gen) * amp[None, None, :, None]).bfloat16()
+        k, v = (torch.randn((nb, n, Hkv, d), device="cuda", generator=gen).bfloat16() for _ in range(2))
+        want = dense(q, k, v)
+        shape = sp.shape_of(q, k, None, B)
+        ws = torch.empty(sp.sp_workspace_bytes(shape, C), dtype=torch.uint8, device="cuda")
+        a_hat = torch.empty((nb, Hq, nqb), dtype=torch.float32, device="cuda")
+        dist = torch.empty((nb, Hq, 2), dtype=torch.float32, device="cuda")
+        role = torch.full((nb, Hq), -7, dtype=torch.int32, device="cuda")
+        scores = torch.empty((nb, C, nqb, nqb), dtype=torch.float32, device="cuda")
+        if delta is None:  # thresholds in the middle of the distances, from a dictionary that is thrown away
+            sp.sp_prefill_layer_dict(shape, q, k, v, h2c, 1.0, 10.0, 10.0, 0, 0, _Dict(sp, nb, C, nqb).c, torch.zeros_like(q),
+                                     scores, role, a_hat, dist, ws)
+            ds = dist.cpu().numpy()
+            delta, tau = float(np.quantile(ds[..., 0], 0.6)), float(np.quantile(ds[..., 1][ds[..., 1] > 0], 0.6))
+            delta, tau = delta * 1.0001, tau * 1.0001
+        o = torch.full_like(q, float("nan"))
+        valid = D.valid.cpu().numpy()
+        sp.sp_prefill_layer_dict(shape, q, k, v, h2c, 1.0, delta, tau, 0, 0, D.c, o, scores, role, a_hat, dist, ws)
+        got, dd = role.cpu().numpy(), dist.cpu().numpy()
+        kinds = set()
+        for b in range(nb):
+            has = {c: bool(valid[b, c]) for c in range(C)}
+            for h in range(Hq):
+                c, r = h2c[h], -1
+                if c >= 0:
+                    assert abs(dd[b, h, 0] - delta) > 1e-7 and abs(dd[b, h, 1] - tau) > 1e-7
+                    if not has[c]:
+                        if dd[b, h, 0] < delta:
+                            r, has[c] = -2, True
+                    elif dd[b, h, 0] < delta and dd[b, h, 1] < tau:
+                        r = c
+                assert got[b, h] == r, (layer, b, h)
+                kinds.add(min(r, 0))
+            assert [bool(x) for x in D.valid[b].cpu()] == [has[c] for c in range(C)]
+        assert kinds == {-2, -1, 0}
+        close(o, want)
+    pivots = [h2c.index(c) for c in clusters]
+    h2g = [clusters.index(c) if c >= 0 else -1 for c in h2c]
+    G = len(clusters)
+    ws = torch.empty(sp.sp_workspace_bytes(shape, G), dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, float("nan"))
+    hp = torch.full((nb, Hq), -9, dtype=torch.int32, device="cuda")
+    scores = torch.empty((nb, G, nqb, nqb), dtype=torch.float32, device="cuda")
+    idx = torch.empty((nb, G, nqb, nqb), dtype=torch.int32, device="cuda")
+    cnt = torch.empty((nb, G, nqb), dtype=torch.int32, device="cuda")
+    sp.sp_prefill_layer_gated(shape, q, k, v, h2g, pivots, 1.0, delta, tau, 0, 0, o, scores, idx, cnt, a_hat, dist, hp, ws)
+    shared = [int(hp[0, h]) for h in range(Hq) if h2g[h] >= 0 and h not in pivots]
+    assert any(x >= 0 for x in shared) and any(x < 0 for x in shared)
+    close(o, want)
