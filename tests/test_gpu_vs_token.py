@@ -271,3 +271,41 @@ def test_token_attention_rows_in_two_launches():
     ref = oracle.vs_token_rows(hq, hk, hv, B, keep_v, keep_s, True, rows)
     emax, emean = err_stats(o.float().cpu().numpy()[0, at, 0], ref)
     assert emax <= OUT_MAX and emean <= OUT_MEAN, (emax, emean)
+
+
+@pytest.mark.parametrize("d,B", [(128, 128), (128, 64), (64, 128), (64, 64)])
+def test_weight_that_rules_a_row_is_not_rounded(d, B):
+    """One kept key has about half of every row's weight, the sink block's keys, which a row meets first, have the rest, each
+    a factor 30 to 110 below it.  Dimension x has 1 at the one key and -g_x at the others, so outputs near 0 show their
+    weights' rounding: of the one key's weight s (1 - s) (1 + g) 2^-9 at most, 5e-4 to 1e-3 rms over the queries, if it is
+    rounded; of B independent others sqrt(sum r^2) g 2^-9, 1e-4 to 2e-4 rms with the output's own rounding, if it is exactly 1."""
+    import torch
+    import paper_2505_19578_amd as sp
+    rng = np.random.default_rng([d, B])
+    nqb, one = 6, 2 * B + 5
+    N = nqb * B
+    bf16 = lambda x: torch.from_numpy(np.asarray(x, np.float32)).to(torch.bfloat16)
+    f64 = lambda x: x.to(torch.float64).numpy()
+    alpha = bf16(rng.uniform(7, 8, N) * np.sqrt(d) / 8)
+    beta = bf16(np.where(np.arange(N) < B, rng.uniform(6, 7, N), -8.0))
+    x = f64(alpha)[:, None] * f64(beta)[None, :B] / np.sqrt(d)
+    beta[one] = bf16((np.log(np.exp(x).sum(1)) / (f64(alpha) / np.sqrt(d))).mean())
+    lead = (f64(alpha) * f64(beta)[one] / np.sqrt(d) - x.max(1)) / np.log(2)
+    assert 4.0 < lead.min() and lead.max() < 7.5
+    g = np.exp(np.linspace(np.log(0.25), np.log(4), d))
+    q, k, v = (torch.zeros((1, N, 1, d), dtype=torch.bfloat16) for _ in range(3))
+    q[0, :, 0, 0], k[0, :, 0, 0] = alpha, beta
+    v[0, :B, 0], v[0, one, 0] = -bf16(g), 1.0
+    print(f"[vs token] one heavy key, d{d} B{B}", flush=True)
+    _, o, bits, _ = _run(sp, q.cuda(), k.cuda(), v.cuda(), B, [0], 0.9, True)
+    keep_v, keep_s = _bits_to_keep(bits[0, 0], N).astype(bool), _bits_to_keep(bits[0, 1], N).astype(bool)
+    assert keep_v[one]
+    t, s = np.arange(3 * B, N)[:, None], np.arange(N)[None, :]
+    allow = (s <= t) & (keep_v[s] | keep_s[np.maximum(t - s, 0)] | (s // B == 0) | (s // B == t // B))
+    w = np.where(allow, np.exp(f64(alpha)[t] * f64(beta)[s] / np.sqrt(d)), 0.0)
+    ref = (w / w.sum(1, keepdims=True)) @ f64(v[0, :, 0])
+    near_0 = np.abs(ref) < 0.05
+    assert near_0.sum() > 4 * B
+    err = np.sqrt(np.mean((f64(o[0, 3 * B:, 0].cpu()) - ref)[near_0] ** 2))
+    print(f"[vs token] rms error of the outputs near 0: {err:.2e}", flush=True)
+    assert err <= 3.5e-4
