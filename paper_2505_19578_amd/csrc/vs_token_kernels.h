@@ -6,6 +6,7 @@
 #include "sp_common.h"
 #include "attn_kernel.h"
 #include "vertical_slash_kernels.h"
+#include "vs_items.h"
 
 namespace {
 
@@ -19,14 +20,6 @@ namespace {
 //   items    [hb][..]          the items of rows row0 .. row1 - 1, VsItem each; row i's start at SPB (i (i+1) - row0 (row0+1)) / 2
 //   gimg     [hb][seq/64][2][64*D] packed K and V images of the gathered keys, 64 keys each, zero padded
 //   act_pos  [b][n_heads], act_n [b]  the listed positions that take part (role -1, or all without roles), ascending
-// One item of a row's work list: 64 keys, a packed K image followed by the V image.  code: the 64-key tile of the sequence,
-// or with VS_GATHERED the gathered image; v: keys of the item that every query of the row may attend to, whatever its
-// offsets (kept keys of a tile; of a gathered image those that no band holds; all of the sink and, forced, the diagonal).
-struct alignas(16) VsItem {
-  uint32_t code, unused;
-  uint64_t v;
-};
-constexpr uint32_t VS_GATHERED = 1u << 31;
 constexpr int VST_TASK_ROWS = 16;  // consecutive query blocks of a head that one XCD runs side by side
 constexpr int VST_BY_LENGTH = 3;   // most groups of 8 chunks a head that run chunk by chunk
 struct VsTokParams {
@@ -434,7 +427,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   // query starts at bit start0, query c32's window c32 bits further.
   auto mask_pre = [&](const VsItem &it, int t) -> VsMaskPre {
     VsMaskPre pre;
-    const int x = i * SPB - (int)it.code;  // tile: 1 and more below the row, 0 and -1 on the diagonal
+    const int x = vs_tiles_below(i * SPB, it.code);
     pre.live = t < T;
     pre.diag = t >= T - SPB;
     pre.start0 = 64 * x + 32 * w - 63;
