@@ -10,6 +10,7 @@ import pytest
 from tests.test_gpu_parity import OUT_MAX, OUT_MEAN, _LazyHost
 
 pytestmark = pytest.mark.gpu
+KT = 64  # keys of a tile
 
 
 def _bits_to_keep(words, N):
@@ -63,8 +64,8 @@ def _pair_count(keep_v, keep_s, B, forced):
 @pytest.mark.parametrize("d,B,N,forced,gamma", [(128, 128, 1024, True, 0.5), (128, 128, 1024, False, 0.5),
                                                 (128, 64, 576, True, 0.5), (64, 128, 768, True, 0.5),
                                                 (64, 64, 448, False, 0.5),
-                                                # nearly everything kept (long runs of full gathered items, every
-                                                # band), and nearly nothing
+                                                # nearly everything kept (every tile a band with a mask), and nearly
+                                                # nothing
                                                 (128, 128, 1536, True, 0.98), (64, 64, 640, False, 0.98),
                                                 (128, 128, 1024, False, 0.02), (128, 64, 576, True, 0.02)])
 def test_token_attention_random_inputs(d, B, N, forced, gamma):
@@ -309,3 +310,125 @@ def test_weight_that_rules_a_row_is_not_rounded(d, B):
     err = np.sqrt(np.mean((f64(o[0, 3 * B:, 0].cpu()) - ref)[near_0] ** 2))
     print(f"[vs token] rms error of the outputs near 0: {err:.2e}", flush=True)
     assert err <= 3.5e-4
+
+
+def _row_items(keep_v, keep_s, B, forced):
+    """The items of every row, as the kernel's rule makes them: [rows] x (gathered images that lie in no band, bands of which
+    every offset is kept, gathered images with a mask, bands with a mask, whether all tiles are walked as bands)."""
+    N, spb = len(keep_v), B // KT
+    kept = np.cumsum(np.concatenate([[0], keep_s]))
+    lo, hi = KT * np.arange(N // KT) - KT + 1, KT * np.arange(N // KT) + B - 1  # the offsets of a tile x below the row's first
+    n = kept[np.minimum(hi, N - 1) + 1] - kept[np.maximum(lo, 0)]
+    band, full = n > 0, n == B + KT - 1
+    keys = np.flatnonzero(keep_v)
+    keys = keys[keys >= (B if forced else 0)]
+    rows = []
+    for i in range(N // B):
+        first, below = i * spb, i * spb - (spb if forced and i > 0 else 0)
+        nb, nf = int(band[1:below + 1].sum()), int((band & full)[1:below + 1].sum())
+        images = np.array_split(keys[keys < i * B], np.arange(KT, max(1, (keys < i * B).sum()), KT))
+        left = [int((~band[first - x // KT]).sum()) for x in images]
+        gf, gp = sum(x == KT for x in left), sum(0 < x < KT for x in left)
+        if nb + gf + gp > below:
+            rows.append((0, int((band & full)[1:below + 1].sum()), 0, below - int((band & full)[1:below + 1].sum()), 1))
+        else:
+            rows.append((gf, nf, gp, nb - nf, 0))
+    return np.asarray(rows)
+
+
+def _weights_by_choice(rng, d, B, N, keys, offsets, share):
+    """q, k of which each query of the last block has `share` of its weight on `keys`, alike, the rest on the keys `offsets`
+    below it, alike; the other queries' weights are random, on few keys each."""
+    h = d // 2
+    q, k = rng.normal(size=(N, d)) * 4, rng.normal(size=(N, d))
+    k[:, :h] = 0
+    code = rng.normal(size=(B, h - 1))
+    code /= np.linalg.norm(code, axis=1, keepdims=True)
+    for o in offsets:
+        k[N - B - o:N - o, 1:h] = 4 * code
+    k[keys, 1:h] = 0
+    k[keys, 0] = (20 + np.log(share / (1 - share) * max(1, len(offsets)) / len(keys))) / 5 if len(offsets) else 4
+    q[N - B:] = 0
+    q[N - B:, 1:h] = code * 5 * np.sqrt(d)
+    q[N - B:, 0] = 5 * np.sqrt(d)
+    return q, k
+
+
+@pytest.mark.parametrize("d,B", [(128, 128), (128, 64), (64, 128), (64, 64)])
+@pytest.mark.parametrize("forced", [True, False])
+@pytest.mark.parametrize("kind", ["runs", "all_tiles"])
+def test_token_attention_every_kind_of_item(d, B, forced, kind):
+    """runs: one run of kept keys and one of kept offsets, which give runs of items without masks of both kinds (the unmasked
+    steps) beside ones with masks.  all_tiles: 20 keys of every tile, single offsets 2 to 4 tiles apart and a run of both, so that
+    rows have more items than tiles and walk all of their tiles as bands, some without masks."""
+    import torch
+    import oracle
+    import paper_2505_19578_amd as sp
+    from tests.gpu_util import err_stats
+    rng = np.random.default_rng([d, B])
+    if kind == "runs":
+        N = 24 * B
+        keys, offsets, share, gamma = np.arange(N // 4, N // 4 + N // 3), [], 1.0, 0.9
+    else:
+        tiles, run, gaps = (24, 6 * B, [2, 3]) if B == 64 else (32, 4 * B, [4])
+        N = tiles * KT
+        keys = (KT * np.arange(tiles)[:, None] + 3 * np.arange(20) + 3).ravel()
+        keys = np.union1d(keys[keys < N - B], np.arange(N - B - run, N - B))
+        offsets, x = [], B // KT + 1 + run // KT
+        while KT * x + 33 < N - B:
+            offsets.append(KT * x + 33)
+            x += gaps[(len(offsets) - 1) % len(gaps)]
+        share = (len(keys) + 0.0) / (2 * len(keys) - run)  # as much on the single keys as on the single offsets
+        gamma = share - 0.05
+    bf16 = lambda x: torch.from_numpy(np.asarray(x, np.float32)).to(torch.bfloat16)
+    q, k = (bf16(x) for x in _weights_by_choice(rng, d, B, N, keys, offsets, share))
+    v = bf16(rng.normal(size=(N, d)))
+    print(f"[vs token] {kind} d{d} B{B} N{N} forced {forced}", flush=True)
+    q4, k4, v4 = (x[None, :, None].contiguous().cuda() for x in (q, k, v))
+    shape, o, bits, pairs = _run(sp, q4, k4, v4, B, [0], gamma, forced)
+    _check_kept_sets(oracle, sp, shape, q4, k4, [0], gamma, bits)
+    keep_v, keep_s = _bits_to_keep(bits[0, 0], N), _bits_to_keep(bits[0, 1], N)
+    items = _row_items(keep_v, keep_s, B, forced)
+    print(f"[vs token] rows with each kind of item: {(items > 0).sum(0)} of {N // B}", flush=True)
+    if kind == "runs":  # (U > 2: the unmasked steps are taken)
+        assert (items[:, :4] > 0).any(0).all() and (items[:, :2].sum(1) > 2).any()
+    else:
+        assert items[:, 4].sum() > 2 and (items[items[:, 4] > 0, 1] > 0).any()
+    f32 = lambda x: x.float().numpy()
+    ref = oracle.vs_token_rows(f32(q), f32(k), f32(v), B, keep_v, keep_s, forced)
+    emax, emean = err_stats(o.float().cpu().numpy()[0, :, 0], ref)
+    assert emax <= OUT_MAX and emean <= OUT_MEAN, (emax, emean)
+    assert int(pairs[0]) == _pair_count(keep_v, keep_s, B, forced)
+
+
+# (a) rows in two launches, more than one head and batch entry: every head's items start at their own place; (b) more than 3
+# groups of 8 chunks (384 rows), heads of several KV heads, more heads than XCDs; (c) up to 3 groups, the same
+@pytest.mark.parametrize("B,nqb,batch,Hq,Hkv", [(64, 2050, 2, 4, 2), (64, 390, 1, 10, 5), (128, 385, 1, 9, 3), (64, 383, 2, 9, 9)])
+def test_a_heads_rows_do_not_depend_on_the_other_heads(B, nqb, batch, Hq, Hkv):
+    import torch
+    import oracle
+    import paper_2505_19578_amd as sp
+    from synth import random_qkv, bf16_bits_to_f32
+    from tests.gpu_util import to_dev, err_stats
+    d, N = 64, nqb * B
+    parts = [random_qkv(180 + b, N, Hq, Hkv, d, 2.0) for b in range(batch)]
+    q, k, v = (torch.cat([to_dev(p[x]) for p in parts]) for x in range(3))
+    print(f"[vs token] B{B} N{N} batch {batch} heads {Hq}/{Hkv}", flush=True)
+    shape = sp.shape_of(q, k, None, B)
+    ws = torch.empty(sp.sp_vs_token_workspace_bytes(shape, Hq), dtype=torch.uint8, device="cuda")
+    o = torch.zeros_like(q)
+    pairs = torch.full((batch, Hq), -1, dtype=torch.int64, device="cuda")
+    sp.sp_vertical_slash_attn(shape, q, k, v, list(range(Hq)), 0.9, True, o, None, pairs, ws)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        for h in range(Hq):
+            _, alone, bits, n = _run(sp, q[b:b + 1], k[b:b + 1], v[b:b + 1], B, [h], 0.9, True)
+            assert torch.equal(o[b, :, h].view(torch.int16), alone[0, :, h].view(torch.int16)), (b, h)
+            assert int(pairs[b, h]) == int(n[0]), (b, h)
+    # the last one is held to the oracle on a few rows: the first and last, and the border (rows 77, 78) of (a)'s launches
+    rows = np.asarray([0, 1, 40, 77, 78, 79, nqb - 1], dtype=np.int32)
+    at = np.concatenate([np.arange(i * B, (i + 1) * B) for i in rows])
+    hq, hk, hv = (bf16_bits_to_f32(parts[-1][x])[:, -1] for x in range(3))
+    ref = oracle.vs_token_rows(hq, hk, hv, B, _bits_to_keep(bits[0, 0], N), _bits_to_keep(bits[0, 1], N), True, rows)
+    emax, emean = err_stats(o[-1, at, Hq - 1].float().cpu().numpy(), ref)
+    assert emax <= OUT_MAX and emean <= OUT_MEAN, (emax, emean)
