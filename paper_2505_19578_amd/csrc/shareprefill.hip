@@ -441,8 +441,7 @@ VsLayout vs_layout(const sp_shape *s, int n) {
   // (the sizes that callers have been told: room for every logit of a query block, of which the partial row statistics
   // take nkb * block * 8 bytes at most and the borders' lower halves nkb * block * 4)
   L.low = L.part + maps * std::min<size_t>(nkb, VS_PARTS) * s->block * sizeof(float2);
-  L.sums = L.part + align_up(maps * s->block * s->seq * sizeof(float), 256) +
-           align_up(maps * s->block * 2 * sizeof(float), 256);
+  L.sums = L.part + vs_statistics_bytes(maps, s->seq, s->block);
   L.flags = L.sums + align_up(maps * 2 * s->seq * sizeof(float), 256);
   L.gsel = L.flags + align_up(maps * 2 * nkb * sizeof(int32_t), 256);
   L.total = L.gsel + align_up(maps * 2 * gsel_map_bytes((int)nkb), 256);
@@ -597,23 +596,18 @@ sp_status launch_vs_token_attn(const sp_shape *s, const void *q, const void *k, 
   tp.pairs = pairs;
   tp.role = role;
   for (int a = 0; a < n; ++a) tp.head_ids[a] = heads[a];
-  // The bands and items lie where the search had its statistics, in the room that is kept for it (4 seq block bytes per
-  // head).  The items of all rows take at most 8 (seq/64) (nqb + 1) bytes: where that is more (lengths above 32 block^2),
-  // the rows are walked in several launches, each with the items of its own rows.
-  const size_t maps = (size_t)s->batch * n, band_words = (s->seq / KT + 63) / 64;
-  const size_t band_bytes = align_up(maps * 2 * band_words * sizeof(uint64_t), 256);
+  // The bands and items lie where the search had its statistics, 4 seq block bytes per head and a little.  The items of all
+  // rows take at most 8 (seq/64) (nqb + 1) bytes: where that is more (32 block^2 tokens and above; for blocks of 128 one block
+  // less already), the rows are walked in several launches, each with the items of its own rows.
+  const size_t maps = (size_t)s->batch * n;
   const VsLayout VL = vs_layout(s, n);
   tp.bandbits = (uint64_t *)(ws + L.search + VL.part);
-  tp.items = (VsItem *)(ws + L.search + VL.part + band_bytes);
-  tp.item_stride = (int64_t)((VL.sums - VL.part - band_bytes) / sizeof(VsItem) / maps);
+  tp.items = (VsItem *)(ws + L.search + VL.part + vs_band_bytes(maps, s->seq));
+  tp.item_stride = vs_item_room(maps, s->seq, s->block);
   ProfScope prof(KK_VS, st);
   hipLaunchKernelGGL(vs_token_prep_kernel, dim3(n, s->batch), dim3(1024), 0, st, tp);
-  const int64_t spb = s->block / KT;
   for (tp.row1 = tp.nqb; tp.row1 > 0; tp.row1 = tp.row0) {
-    const int64_t fits = tp.item_stride / spb;  // sum of i + 1 over the rows
-    int64_t rows = 0;
-    tp.row0 = tp.row1;
-    while (tp.row0 > 0 && rows + tp.row0 <= fits) rows += tp.row0--;
+    tp.row0 = vs_first_row(tp.row1, tp.item_stride, s->block / KT);
     if (tp.row0 == tp.row1) {
       set_err("no room for the items of one row");
       return SP_ERR_WORKSPACE;

@@ -17,7 +17,7 @@ namespace {
 //   bandbits [hb][2][words of 64]  bit x: a kept offset exists / every offset is kept among those that a 64-key tile x tiles
 //                              below the row's first can realise (64x - 63 .. 64x + B - 1)
 //   hdr      [hb][nqb]         items of row i: how many without a mask (they come first), and all
-//   items    [hb][..]          the items of rows row0 .. row1 - 1, VsItem each; row i's start at SPB (i (i+1) - row0 (row0+1)) / 2
+//   items    [hb][..]          the items of rows row0 .. row1 - 1, VsItem each; row i's start at vs_items_before(i, row0)
 //   gimg     [hb][seq/64][2][64*D] packed K and V images of the gathered keys, 64 keys each, zero padded
 //   act_pos  [b][n_heads], act_n [b]  the listed positions that take part (role -1, or all without roles), ascending
 constexpr int VST_TASK_ROWS = 16;  // consecutive query blocks of a head that one XCD runs side by side
@@ -212,7 +212,7 @@ __device__ void vs_row_items(const VsTokParams &p, int i, int b, int n) {
   at_part += U;
   const int T = U + M + spb;
   VsItem *__restrict__ out =
-      p.items + hb * p.item_stride + ((int64_t)i * (i + 1) - (int64_t)p.row0 * (p.row0 + 1)) / 2 * spb;
+      p.items + hb * p.item_stride + vs_items_before(i, p.row0, spb);
   if (w == 0) {
     if (lane == 0) p.hdr[hb * p.nqb + i] = make_int2(U, T);
     if (lane < n_sink) out[lane] = VsItem{(uint32_t)lane, 0, ~0ull};
@@ -384,8 +384,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   bool care = true;
 
   // the row's items, 64 at a time in registers (item t = lane t % 64 of chunk t / 64), the next chunk ahead
-  const VsItem *__restrict__ list =
-      p.items + hb * p.item_stride + ((int64_t)i * (i + 1) - (int64_t)p.row0 * (p.row0 + 1)) / 2 * SPB;
+  const VsItem *__restrict__ list = p.items + hb * p.item_stride + vs_items_before(i, p.row0, SPB);
   const int2 row_hdr = p.hdr[hb * p.nqb + i];
   const int U = __builtin_amdgcn_readfirstlane(row_hdr.x), T = __builtin_amdgcn_readfirstlane(row_hdr.y);
   const char *kvbase = p.kvp + ((int64_t)b * p.n_kv_heads + kvh) * (int64_t)(p.seq / KT) * STAGE;
