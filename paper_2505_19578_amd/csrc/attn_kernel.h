@@ -10,6 +10,7 @@ namespace {
 // attention kernel
 // ---------------------------------------------------------------------------------------------
 constexpr int SP_MAX_SLOTS = SP_MAX_HEADS + 8;
+constexpr int SP_MAX_TOGETHER = 16;     // batch entries of a call whose rows are dispatched in one order
 constexpr int SP_FUSED_MASK_MAX = 256;  // key blocks of a row whose list the dense kernel makes itself
 struct AttnParams {
   const uint16_t *q;
@@ -19,6 +20,7 @@ struct AttnParams {
   int seq, nqb, n_kv_heads, n_heads, n_maps;
   float inv_group;  // 1 / query heads per KV head
   int rgroups;  // ceil(nqb / (8 QB)): workgroups' rows per strand (see the workgroup mapping in attn_kernel)
+  int n_together;  // batch entries whose rows are dispatched in one order (1: one after the other, entry blockIdx.y)
   float c;    // softmax scale * log2(e)
   float *lws;     // dense: block-local log2-sum-exp [b][n][nqb(nqb+1)/2][B] (row i, key block j <= i), or null
   float *scores;  // dense: [b][n][nqb][nkb], or null
@@ -232,21 +234,40 @@ __global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_ker
   // works on at most ceil(n/8)+1 heads (heads that share a KV head sit next to each other and meet in its
   // L2).  Inside an XCD the dispatch order is rows from long to short, then strand number, then head: the
   // heads that walk the same list for the same row are neighbours in time.
-  const int xcd = blockIdx.x & 7, b = blockIdx.y;
-  // number of heads this launch really has for batch entry b (all listed ones unless the device says otherwise)
-  const int n_act = p.act_n ? __builtin_amdgcn_readfirstlane(p.act_n[b]) : p.n_heads;
-  if (n_act <= 0 || (int)(blockIdx.x >> 3) >= n_act * p.rgroups) return;
-  const int rest = (blockIdx.x >> 3) / (uint32_t)n_act;
+  // Up to some size of launch, the rows of several batch entries are dispatched in one order, from long to short over all of
+  // them (n_together): one entry after the other, the long rows of the last entry begin when the chip is half empty, which
+  // costs the more the fewer and longer-lived the workgroups are (two rows to one, three wavefronts per SIMD).
+  const int xcd = blockIdx.x & 7;
+  const uint32_t u = blockIdx.x >> 3;
+  // number of heads this launch really has for batch entry x (all listed ones unless the device says otherwise)
+  auto heads_of = [&](int x) -> int { return p.act_n ? __builtin_amdgcn_readfirstlane(p.act_n[x]) : p.n_heads; };
+  int b = blockIdx.y, n_act = heads_of(b), n_all = n_act;
+  for (int x = 1; x < p.n_together; ++x) n_all += heads_of(x);
+  if (n_all <= 0 || (int)u >= n_all * p.rgroups) return;
+  const int rest = u / (uint32_t)n_all;
   int strand;
   {
-    int kk = (blockIdx.x >> 3) - rest * n_act;  // position inside the XCD's run, enumerated strand number first, head second
-    const int g0 = xcd * n_act;
+    // Position inside the XCD's run, enumerated strand number first, batch entry second, head third; where the device says
+    // which heads there are, entries have runs of their own.
+    int kk = u - rest * n_all;
+    if (p.act_n)
+      while (kk >= n_act && b + 1 < p.n_together) {
+        kk -= n_act;
+        n_act = heads_of(++b);
+      }
+    const int g0 = xcd * n_act, alike = p.act_n ? 1 : p.n_together;
     for (int sn = 0;; ++sn) {
-      const int u = (sn - g0) & 7;  // g0 + u, + 8, ..: the strands of the run whose number is sn
-      const int cnt = (n_act >> 3) + (u < (n_act & 7) ? 1 : 0);
-      strand = g0 + u + 8 * kk;
-      if (kk < cnt || sn == 7) break;
-      kk -= cnt;
+      const int s0 = (sn - g0) & 7;  // g0 + s0, + 8, ..: the strands of the run whose number is sn
+      const int cnt = (n_act >> 3) + (s0 < (n_act & 7) ? 1 : 0);
+      if (kk < cnt * alike || sn == 7) {
+        if (alike > 1) {
+          b = (uint32_t)kk / (uint32_t)cnt;
+          kk -= b * cnt;
+        }
+        strand = g0 + s0 + 8 * kk;
+        break;
+      }
+      kk -= cnt * alike;
     }
   }
   int slot = strand >> 3;

@@ -279,8 +279,16 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
     set_err("grid too large");
     return SP_ERR_UNSUPPORTED;
   }
-  // a batch entry's workgroups are a multiple of 8, so its first one is again the first XCD's
-  dim3 grid((unsigned)(8 * n * ap.rgroups), (unsigned)s->batch);
+  // Batch entries in one order from long rows to short (see attn_kernel's mapping) in dense walks of up to 4096 workgroups, 16
+  // to a compute unit.  One after the other / in one order: d 64, blocks of 64, 3 x 16 heads of 4096 tokens (1536 workgroups)
+  // 172 / 152 us, blocks of 128 169 / 150; 4 x 8 heads of 16K (4096) 1290 / 1257; d 128, 2 x 8 heads of 32K (4096) 3.85 / 3.84
+  // ms.  Beyond, the images of several entries' heads pass through one L2, and the end of the launch hardly counts: 5 x 16
+  // heads of 16K (10240) 3190 / 3389 us, d 128, 4 x 32 heads of 32K (32768) 29.96 / 31.94 ms.  Rows over lists are not as long
+  // as they stand: 2 x 4 heads of 8K over a caller's lists 73.5 / 85.7 us.
+  // (One after the other: an entry's workgroups are a multiple of 8, so its first one is again the first XCD's.)
+  const int64_t rows = (int64_t)s->batch * n * ((ap.nqb + qb - 1) / qb);
+  ap.n_together = DENSE && s->batch <= SP_MAX_TOGETHER && rows <= 4096 ? s->batch : 1;
+  dim3 grid((unsigned)(8 * n * ap.rgroups * ap.n_together), (unsigned)(s->batch / ap.n_together));
   const bool sc = DENSE && ap.scores != nullptr;
   ProfScope prof(kind, st);
 #define SP_LAUNCH(D_, B_, QB_)                                                                                \

@@ -119,3 +119,77 @@ def test_dense_rows_two_to_a_workgroup_and_alone(nqb, scores):
         o, s = run(q[b:b + 1], k[b:b + 1], v[b:b + 1], [h])
         assert torch.equal(o[0, :, 0], o_all[b, :, h])
         assert s is None or torch.equal(s[0, 0], s_all[b, h])
+
+
+# The rows of up to 16 batch entries are dispatched in one order (17: one entry after the other); head counts on both sides of
+# a multiple of 8
+@pytest.mark.parametrize("d,B,nqb,batch,heads", [(128, 128, 9, 3, 5), (64, 64, 17, 16, 3), (64, 64, 17, 17, 3), (128, 64, 7, 2, 16),
+                                                 (64, 128, 11, 16, 1), (64, 64, 43, 3, 16)])
+def test_a_batch_entry_alone_and_among_others(d, B, nqb, batch, heads):
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, v = _inputs(47, nqb * B, d, batch)
+    g = torch.Generator().manual_seed(11)
+    keep = torch.rand((batch, 1, nqb, nqb), generator=g) < 0.5
+    keep |= torch.eye(nqb, dtype=torch.bool)
+    keep &= torch.ones(nqb, nqb, dtype=torch.bool).tril()
+    key = torch.where(keep, torch.arange(nqb), nqb).sort(dim=-1).values
+    idx, cnt = torch.where(key < nqb, key, -1).int().cuda(), keep.sum(-1, dtype=torch.int32).cuda()
+    listed = [(5 * h + 2) % HQ for h in range(heads)]
+
+    def run(q, k, v, idx, cnt):
+        shape = sp.shape_of(q, k, None, B)
+        ws = torch.empty(sp.sp_workspace_bytes(shape, heads), dtype=torch.uint8, device="cuda")
+        o, ol = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+        sc = torch.full((q.shape[0], heads, nqb, nqb), -1.0, dtype=torch.float32, device="cuda")
+        sp.sp_dense_attn_with_block_scores(shape, q, k, v, listed, o, sc, ws)
+        sp.sp_block_sparse_attn(shape, q, k, v, listed, [0] * heads, idx, cnt, 1, ol, ws)
+        torch.cuda.synchronize()
+        return o, sc, ol
+
+    print(f"[batch] d{d} B{B} {nqb} blocks, {batch} x {heads} heads", flush=True)
+    everything = run(q, k, v, idx, cnt)
+    for b in range(batch):
+        alone = run(q[b:b + 1], k[b:b + 1], v[b:b + 1], idx[b:b + 1].contiguous(), cnt[b:b + 1].contiguous())
+        for what, a, e in zip(("dense output", "score map", "output over lists"), alone, everything):
+            assert torch.equal(a[0], e[b]), f"{what}, batch entry {b}: {int((a[0] != e[b]).sum())} of {a.numel()} differ"
+
+
+@pytest.mark.parametrize("d,B,nqb,batch", [(128, 128, 8, 4), (64, 64, 21, 4), (128, 64, 9, 16), (64, 128, 5, 17)])
+def test_a_batch_entry_of_a_gated_layer_alone_and_among_others(d, B, nqb, batch):
+    """Entries whose heads all attend alike (every head shares), entries whose estimates are one-hot (no head passes the sparsity
+    test: all but the pivots fall back) and ordinary ones: the device's lists of heads have other lengths for every entry,
+    none among them."""
+    import torch
+    import paper_2505_19578_amd as sp
+    q, k, v = _inputs(53, nqb * B, d, batch)
+    for b in range(batch):
+        if b % 4 in (1, 2):
+            q[b] = 0  # uniform attention
+        if b % 4 == 2:
+            k[b, :B] = 0
+            k[b, :B, :, 0] = 8.0
+            q[b, :, :, 0] = 8.0  # all on the first block
+    clusters, pivots = [h // 4 for h in range(HQ)], [0, 4, 8, 12]
+
+    def run(q, k, v):
+        shape, b = sp.shape_of(q, k, None, B), q.shape[0]
+        ws = torch.empty(sp.sp_workspace_bytes(shape, 4), dtype=torch.uint8, device="cuda")
+        o = torch.full_like(q, 7.0)
+        idx = torch.empty((b, 4, nqb, nqb), dtype=torch.int32, device="cuda")
+        cnt = torch.empty((b, 4, nqb), dtype=torch.int32, device="cuda")
+        a_hat = torch.empty((b, HQ, nqb), dtype=torch.float32, device="cuda")
+        dist = torch.empty((b, HQ, 2), dtype=torch.float32, device="cuda")
+        role = torch.full((b, HQ), -9, dtype=torch.int32, device="cuda")
+        sp.sp_prefill_layer_gated(shape, q, k, v, clusters, pivots, 0.9, 0.3, 0.2, sp.SP_SCORE_BLOCK_MASS, sp.SP_SELECT_PER_ROW,
+                                  o, None, idx, cnt, a_hat, dist, role, ws)
+        torch.cuda.synchronize()
+        return o, idx, cnt, dist, role
+
+    print(f"[batch] gated d{d} B{B} {nqb} blocks, batch {batch}", flush=True)
+    everything = run(q, k, v)
+    fallback = (everything[4] == -1).sum(1).tolist()
+    assert 0 in fallback and max(fallback) >= 12, fallback
+    for b in range(batch):
+        for what, a, e in zip(("output", "lists", "counts", "distances", "roles"), run(q[b:b + 1], k[b:b + 1], v[b:b + 1]), everything):
+            assert torch.equal(a[0], e[b]), f"{what}, batch entry {b}"
