@@ -189,19 +189,18 @@ __device__ __forceinline__ void products_read_ahead(Read &&read, Use &&use) {
 // decides where its diagonal lies).  Score maps of 2 x 12352 tokens, 16 heads of d 64: 832 -> 788 us; gated layer of 2 x 8128
 // tokens, d 128: 794 -> 770.
 //
-// d 64 with four wavefronts to a workgroup: three wavefronts per SIMD.  A step there is bound by its VALU work (exponentials,
-// sums, row maxima), and a third wavefront fills what two leave.  168 registers are enough with two LDS fragments ahead
-// instead of four (four: 12 to 20 bytes of scratch, up to 30 % slower on short rows).  The same score maps 788 -> 740 us;
-// blocks of 128, score maps of 2 x 12288: 805 -> 752; lists of 2 x 15488: 1143 -> 1098.
+// WAVES: wavefronts per SIMD that the registers are kept to.  Three for d 64 with four wavefronts to a workgroup, where a launch
+// is large enough (the launcher's rule).  A step there is bound by its VALU work (exponentials, sums, row maxima), and a third
+// wavefront fills what two leave.  168 registers are enough with two LDS fragments ahead instead of four (four: 12 to 20 bytes
+// of scratch, up to 30 % slower on short rows).  The same score maps 788 -> 740 us; blocks of 128, score maps of 2 x 12288:
+// 805 -> 752; lists of 2 x 15488: 1143 -> 1098.
 template <int D, int B, int QB>
 constexpr int attn_image_keys() { return (D == 128 && QB * B == 64) ? 32 : 64; }
-// wavefronts per SIMD that the registers are kept to
-template <int D, int B, int QB>
-constexpr int attn_waves() { return (D == 64 && QB * B == 128) ? 3 : 2; }
-template <int D, int B, bool DENSE, bool SCORES, int QB>
-__global__ __launch_bounds__(QB * B * 2, (attn_waves<D, B, QB>())) void attn_kernel(AttnParams p) {
+template <int D, int B, bool DENSE, bool SCORES, int QB, int WAVES>
+__global__ __launch_bounds__(QB * B * 2, WAVES) void attn_kernel(AttnParams p) {
   static_assert(QB == 1 || (DENSE && B == KT), "rows share their tiles where every key block is walked");
-  constexpr int SK = attn_image_keys<D, B, QB>(), WAVES = attn_waves<D, B, QB>();
+  static_assert(WAVES == 2 || (D == 64 && QB * B == 128), "three wavefronts per SIMD: 40 KiB of LDS per four wavefronts");
+  constexpr int SK = attn_image_keys<D, B, QB>();
   constexpr int KH = KT / SK;       // ring images, and steps, per 64-key tile
   constexpr int WB = B / 32;        // wavefronts per query block, 32 queries each
   constexpr int NW = QB * WB;       // wavefronts per workgroup

@@ -264,9 +264,9 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
     });
   ap.n_heads = n;
   // Query blocks of a workgroup (see attn_kernel; the results are the same bits): two where blocks of 64 are walked densely,
-  // for d 64 from 2048 of them on (two rounds of four to a compute unit: below, the chip is not full and a row in a workgroup
-  // of its own ends earlier; with two everywhere 448 blocks took 157.0 us for 154.7, a tiny layer of 32 46.8 for 43.5, and
-  // 1728, of which a gate leaves a part, 255 for 251; 6176 take 744 for 832).
+  // for d 64 from 2048 of them on, listed heads of all batch entries counted.  Time with two (and three wavefronts per SIMD) over
+  // time with one, 2 to 32 heads in up to 8 entries: up to 256 blocks 1.08 to 1.11 (the chip is not full, and a row in a workgroup
+  // of its own ends earlier), 384 to 1536 either way, 0.87 to 1.09, 2048 0.96 to 1.04, from 2304 on 0.89 to 0.95.
   const int qb = DENSE && s->block == 64 && (s->head_dim == 128 || (int64_t)s->batch * n * ap.nqb >= 2048) ? 2 : 1;
   ap.rgroups = (ap.nqb + 8 * qb - 1) / (8 * qb);
   for (int a = 0; a < n; ++a) {
@@ -291,24 +291,33 @@ sp_status launch_attn(const sp_shape *s, AttnParams ap, const HeadList &hl, hipS
   dim3 grid((unsigned)(8 * n * ap.rgroups * ap.n_together), (unsigned)(s->batch / ap.n_together));
   const bool sc = DENSE && ap.scores != nullptr;
   ProfScope prof(kind, st);
-#define SP_LAUNCH(D_, B_, QB_)                                                                                \
-  do {                                                                                                        \
-    if (sc)                                                                                                   \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, DENSE, QB_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);      \
-    else                                                                                                      \
-      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false, QB_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);      \
+#define SP_LAUNCH(D_, B_, QB_, WAVES_)                                                                             \
+  do {                                                                                                             \
+    if (sc)                                                                                                        \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, DENSE, QB_, WAVES_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);   \
+    else                                                                                                           \
+      hipLaunchKernelGGL((attn_kernel<D_, B_, DENSE, false, QB_, WAVES_>), grid, dim3(QB_ * B_ * 2), 0, st, ap);   \
   } while (0)
+  // d 64, blocks of 128: three wavefronts per SIMD (see attn_kernel) from 1024 rows on, which are two rounds of two workgroups to
+  // a compute unit; over lists of several batch entries above 1024.  Below, compute units share three workgroups at the end
+  // where others have none left.  Time with three over time with two, 2 to 32 heads in up to 8 entries: dense up to 384 rows 0.98
+  // to 1.04, 512 0.98 to 1.01, 768 1.04 to 1.07, 1024 0.94 to 1.03, from 1152 on 0.93 to 0.98; lists of one entry up to 768 0.97
+  // to 1.04, from 1024 on 0.93 to 0.99, of several 512 1.01 to 1.02, 768 0.91 to 1.15, 1024 0.93 to 1.10, 1152 0.92 to 0.95, 1536
+  // 0.91 to 1.02, from 2048 on 0.92 to 1.00.
+  const bool three = rows >= (DENSE || s->batch == 1 ? 1024 : 1025);
   constexpr int QB = DENSE ? 2 : 1;
   if (s->head_dim == 128 && s->block == 128)
-    SP_LAUNCH(128, 128, 1);
+    SP_LAUNCH(128, 128, 1, 2);
   else if (s->head_dim == 128 && s->block == 64)
-    SP_LAUNCH(128, 64, QB);
+    SP_LAUNCH(128, 64, QB, 2);
+  else if (s->head_dim == 64 && s->block == 128 && !three)
+    SP_LAUNCH(64, 128, 1, 2);
   else if (s->head_dim == 64 && s->block == 128)
-    SP_LAUNCH(64, 128, 1);
+    SP_LAUNCH(64, 128, 1, 3);
   else if (qb == 1)
-    SP_LAUNCH(64, 64, 1);
+    SP_LAUNCH(64, 64, 1, 2);
   else
-    SP_LAUNCH(64, 64, QB);
+    SP_LAUNCH(64, 64, QB, (DENSE ? 3 : 2));
 #undef SP_LAUNCH
   return hip_check(hipGetLastError(), DENSE ? "dense attn_kernel launch" : "sparse attn_kernel launch");
 }

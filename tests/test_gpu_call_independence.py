@@ -122,9 +122,10 @@ def test_dense_rows_two_to_a_workgroup_and_alone(nqb, scores):
 
 
 # The rows of up to 16 batch entries are dispatched in one order (17: one entry after the other); head counts on both sides of
-# a multiple of 8
+# a multiple of 8; d 64 with blocks of 128: launches with two and with three wavefronts per SIMD (from 1024 rows on, over lists of
+# several entries above 1024)
 @pytest.mark.parametrize("d,B,nqb,batch,heads", [(128, 128, 9, 3, 5), (64, 64, 17, 16, 3), (64, 64, 17, 17, 3), (128, 64, 7, 2, 16),
-                                                 (64, 128, 11, 16, 1), (64, 64, 43, 3, 16)])
+                                                 (64, 128, 11, 16, 1), (64, 128, 32, 2, 16), (64, 128, 33, 2, 16), (64, 64, 43, 3, 16)])
 def test_a_batch_entry_alone_and_among_others(d, B, nqb, batch, heads):
     import torch
     import paper_2505_19578_amd as sp
