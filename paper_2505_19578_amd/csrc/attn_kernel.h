@@ -876,7 +876,7 @@ __global__ __launch_bounds__(QB * B * 2, WAVES) void attn_kernel(AttnParams p) {
         int64_t map = (int64_t)b * p.n_heads + hpos;
         if (p.route) map = p.route[map];
         if (map >= 0)
-          mask_row<SP_FUSED_MASK_MAX / 64>(row_sh, lane, iw, nkb, p.mask_gq, p.mask_idx + (map * p.nqb + iw) * nkb,
+          mask_row<SP_FUSED_MASK_MAX / 64, 128>(row_sh, lane, iw, nkb, p.mask_gq, p.mask_idx + (map * p.nqb + iw) * nkb,
                                            p.mask_cnt + map * p.nqb + iw, nullptr);
       }
     }

@@ -54,7 +54,8 @@ __device__ __forceinline__ uint32_t quantise24(float s) {
 
 // The list of row i from its scores src[0 .. i], by one wavefront: out[nkb], *cnt, optionally bits[ceil(nkb / 64)].
 // EPL > 0: the row lives in registers (nkb <= 64*EPL); EPL == 0: any nkb, the row is re-read in every pass.
-template <int EPL, class Src>
+// PASS: rows of up to PASS (64 or 128) blocks find their threshold in one pass over the row.
+template <int EPL, int PASS, class Src>
 __device__ __forceinline__ void mask_row(Src src, int lane, int i, int nkb, uint32_t gq, int32_t *__restrict__ out,
                                          int32_t *__restrict__ cnt, uint64_t *__restrict__ bits) {
   const int nchunk = (i >> 6) + 1;  // 64-wide chunks that hold valid key blocks
@@ -92,19 +93,22 @@ __device__ __forceinline__ void mask_row(Src src, int lane, int i, int nkb, uint
   if (tot > 0) {
     uint64_t T = ((uint64_t)gq * tot + 16777215ull) >> 24;  // least integer prefix sum that reaches gamma
     if (T < 1) T = 1;
-    // v* = the largest value with sum_ge(v*) >= T.  It is one of the scores, so a row of up to 128 blocks takes sum_ge of
-    // each of its scores, side by side in the lanes (one pass over the row), and the largest that reaches T.  A longer row
-    // halves an interval 24 times: a chain of wave sums, 3 us (a tiny layer 41.1 -> 38.8 us with the pass).
-    if (EPL > 0 && i < 128) {
+    // v* = the largest value with sum_ge(v*) >= T.  It is one of the scores, so a short row takes sum_ge of each of its
+    // scores, side by side in the lanes (one pass over the row), and the largest that reaches T.  A longer row halves an
+    // interval 24 times: a chain of wave sums, 3 us (a tiny layer 41.1 -> 38.8 us with the pass).  Up to 64 blocks the pass has
+    // fewer instructions as well (64 maps of 64 rows 9.0 -> 7.4 us); up to 128 it only has the shorter chain, which counts
+    // where a wavefront is alone (64 maps of 128 rows 14.8 us with the search from 64 blocks on, 19.1 with the pass), or where
+    // the search adds up 16 registers (64 maps of 512 rows 95.7 and 92.2).
+    if (EPL > 0 && i < PASS) {
       uint32_t s0 = 0, s1 = 0;  // at most 128 scores of at most 2^24
-      const uint32_t u0 = u[0], u1 = EPL > 1 ? u[EPL > 1 ? 1 : 0] : 0u;
+      const uint32_t u0 = u[0], u1 = (PASS > 64 && EPL > 1) ? u[EPL > 1 ? 1 : 0] : 0u;
       for (int j0 = 0; j0 <= i; j0 += 8) {
-        const uint32_t from = j0 < 64 ? u0 : u1;
+        const uint32_t from = (PASS <= 64 || j0 < 64) ? u0 : u1;
 #pragma unroll
         for (int x = 0; x < 8; ++x) {  // (scores beyond the row are zero)
           const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)from, (j0 + x) & 63);
           s0 += (u0 <= y) ? y : 0u;
-          s1 += (u1 <= y) ? y : 0u;
+          if (PASS > 64) s1 += (u1 <= y) ? y : 0u;
         }
       }
       const uint32_t t32 = (uint32_t)T;  // T <= tot < 2^32
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(256) void mask_kernel(const float *__restrict__ sco
     orow = (int64_t)dst * nqb + i;
   }
   const int nwords = (nkb + 63) >> 6;
-  mask_row<EPL>(scores + (int64_t)row * nkb, lane, i, nkb, gq, kb_idx + orow * nkb, kb_cnt + orow,
+  mask_row<EPL, EPL <= 4 ? 64 : 128>(scores + (int64_t)row * nkb, lane, i, nkb, gq, kb_idx + orow * nkb, kb_cnt + orow,
                 bitmask ? bitmask + orow * nwords : nullptr);
 }
 
