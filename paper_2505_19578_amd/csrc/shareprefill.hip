@@ -631,6 +631,7 @@ sp_status launch_vs_token_attn(const sp_shape *s, const void *q, const void *k, 
     }
     tp.n_gather = tp.row1 == tp.nqb ? s->seq / KT : 0;
     tp.nch8 = ((tp.row1 - tp.row0 + VST_TASK_ROWS - 1) / VST_TASK_ROWS + 7) / 8;
+    tp.by_length = tp.nch8 <= (s->n_kv_heads % 8 == 0 ? VST_BY_LENGTH : VST_BY_LENGTH_UNEVEN);
     const dim3 gitems(tp.n_gather + tp.row1 - tp.row0, n, s->batch);
     const dim3 gattn((unsigned)(8 * n * tp.nch8 * VST_TASK_ROWS), (unsigned)s->batch);
     if (s->head_dim == 128)

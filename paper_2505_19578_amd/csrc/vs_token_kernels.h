@@ -1,6 +1,6 @@
 // Attention over the vertical-slash pattern of Alg. 5 at token granularity (Sec. 5.1 A(Q,K,V,M) with the mask M
 // built from S = S_v U S_s): the kept keys of a head are gathered into packed images of their own, the kept
-// offsets are walked as bands of key blocks with a bit mask inside every tile.
+// offsets are walked as bands of 64-key tiles with a bit mask inside every tile.
 #ifndef SP_VS_TOKEN_KERNELS_H
 #define SP_VS_TOKEN_KERNELS_H
 #include "sp_common.h"
@@ -21,7 +21,9 @@ namespace {
 //   gimg     [hb][seq/64][2][64*D] packed K and V images of the gathered keys, 64 keys each, zero padded
 //   act_pos  [b][n_heads], act_n [b]  the listed positions that take part (role -1, or all without roles), ascending
 constexpr int VST_TASK_ROWS = 16;  // consecutive query blocks of a head that one XCD runs side by side
-constexpr int VST_BY_LENGTH = 3;   // most groups of 8 chunks a head that run chunk by chunk
+// Most groups of 8 chunks a head that run chunk by chunk: 384 query blocks of a launch, or 768 where the KV heads are not a
+// multiple of 8 (see the mapping in vs_token_attn_kernel).
+constexpr int VST_BY_LENGTH = 3, VST_BY_LENGTH_UNEVEN = 6;
 struct VsTokParams {
   const uint16_t *q, *k, *v;
   const char *kvp;   // packed K/V images of the whole sequence (pack_kv_kernel)
@@ -38,7 +40,8 @@ struct VsTokParams {
   int row0, row1;       // the query blocks of this launch
   int n_gather;         // 64-key sub-tiles that the gathering launch packs (all, or 0 after the first launch of a call)
   char *gimg;
-  int nch8;  // chunks of VST_TASK_ROWS query blocks per head and XCD: ceil(ceil(nqb / VST_TASK_ROWS) / 8)
+  int nch8;  // chunks of VST_TASK_ROWS query blocks per head and XCD: ceil(ceil((row1 - row0) / VST_TASK_ROWS) / 8)
+  int by_length;  // the chunks run chunk by chunk
   int64_t *pairs;        // optional [b][n]: number of (query, key) pairs of the pattern (statistics)
   const int32_t *role;   // optional [b][n_q_heads]: only heads whose entry is -1 are processed
   int32_t head_ids[SP_MAX_HEADS];
@@ -329,11 +332,18 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   // eighth of every head's chunks (heads differ widely in how much they keep).  The workgroups resident on an XCD at one
   // time are then a few runs of neighbouring rows, which walk nearly the same items at nearly the same time and find each
   // other's images in the XCD's L2.
-  // Up to VST_BY_LENGTH groups of 8 chunks, chunk c of listed head a belongs to XCD (a + c) % 8, which runs them chunk by
-  // chunk, all heads: what is dispatched last is short.  (Head by head, a long row of the last head ended alone: 32 heads of
-  // 8K 438 -> 411 us, 16 heads d 64 of 2 x 10K 496 -> 456, dictionary layers of 40K 33.0 -> 32.6 ms.)  Beyond, chunk c
-  // belongs to XCD (KV head + c) % 8, head by head: heads of one KV head run the same rows side by side, whose bands are the
-  // same images (128K: 38.8 -> 38.3 ms, chunk by chunk 39.0).
+  // by_length: chunk c of listed head a belongs to XCD (a + c) % 8, which runs them chunk by chunk, all heads: what is
+  // dispatched last is short.  (Head by head, a long row of the last head ended alone: 32 heads of 8K 438 -> 411 us, 16 heads
+  // d 64 of 2 x 10K 496 -> 456, dictionary layers of 40K 33.0 -> 32.6 ms.)  In launches of more rows chunk c belongs to XCD (KV
+  // head + c) % 8, head by head: heads of one KV head run the same rows side by side, whose bands are the same images.  That
+  // shares the rows evenly only over KV heads that are a multiple of 8.  Head by head over chunk by chunk, two prompts each:
+  //   query / KV heads    256 rows     384 to 400   448 to 512   640 to 768   1024
+  //   32 / 8, blocks 128  1.02         1.00 - 1.02  0.98 - 1.00  0.96 - 0.99  0.97 - 0.98
+  //   32 / 8, blocks 64   0.99 - 1.03  0.97 - 1.00  0.99         0.97 - 0.99  0.97 - 0.99
+  //   24 to 64 / 8 to 32                            0.97 - 1.00  0.96 - 0.99  0.96 - 0.99
+  //   28 / 4, both        1.08 - 1.16  1.04 - 1.12  1.04 - 1.09  1.02 - 1.07  0.99 - 1.04
+  //   32 / 4                                        1.04 - 1.07  0.98 - 0.99  0.95 - 0.98
+  //   8 / 2, both         1.16 - 1.21  1.03 - 1.15  1.05 - 1.13  1.00 - 1.11  1.04 - 1.05
   const int xcd = blockIdx.x & 7, b = blockIdx.y;
   const int n_act = __builtin_amdgcn_readfirstlane(p.act_n[b]);
   const int rr = (blockIdx.x >> 3) % VST_TASK_ROWS, u = (blockIdx.x >> 3) / VST_TASK_ROWS;
@@ -341,7 +351,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   const int k = (int)((uint32_t)u / (uint32_t)n_act);
   int at = u - k * n_act;  // position among the chunks 8k .. 8k + 7 of this XCD, one of each head
   int r = 0;
-  if (p.nch8 <= VST_BY_LENGTH) {
+  if (p.by_length) {
     for (;; ++r) {
       const int a0 = (xcd - r) & 7;  // a0, + 8, ..: the heads whose chunk 8k + r is this XCD's
       const int cnt = (n_act >> 3) + (a0 < (n_act & 7) ? 1 : 0);
@@ -354,7 +364,7 @@ __global__ __launch_bounds__(B * 2, 2) void vs_token_attn_kernel(VsTokParams p) 
   }
   const int n = __builtin_amdgcn_readfirstlane(p.act_pos[(int64_t)b * p.n_heads + at]);
   const int head = p.head_ids[n], kvh = head / p.group;
-  if (p.nch8 > VST_BY_LENGTH) r = (xcd - kvh) & 7;
+  if (!p.by_length) r = (xcd - kvh) & 7;
   const int c = 8 * k + r;
   const int i = p.row1 - 1 - (c * VST_TASK_ROWS + rr);
   if (i < p.row0) return;  // the last chunks of a head may be short or empty

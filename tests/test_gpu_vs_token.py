@@ -402,8 +402,10 @@ def test_token_attention_every_kind_of_item(d, B, forced, kind):
 
 
 # (a) rows in two launches, more than one head and batch entry: every head's items start at their own place; (b) more than 3
-# groups of 8 chunks (384 rows), heads of several KV heads, more heads than XCDs; (c) up to 3 groups, the same
-@pytest.mark.parametrize("B,nqb,batch,Hq,Hkv", [(64, 2050, 2, 4, 2), (64, 390, 1, 10, 5), (128, 385, 1, 9, 3), (64, 383, 2, 9, 9)])
+# groups of 8 chunks (384 rows) of heads of 8 KV heads, and more than 6 (768) of heads of 5, which run head by head; (c) fewer of
+# them, more heads than XCDs
+@pytest.mark.parametrize("B,nqb,batch,Hq,Hkv", [(64, 2050, 2, 4, 2), (128, 385, 1, 16, 8), (64, 770, 1, 10, 5), (64, 390, 1, 10, 5),
+                                                (128, 385, 1, 9, 3), (64, 383, 2, 9, 9)])
 def test_a_heads_rows_do_not_depend_on_the_other_heads(B, nqb, batch, Hq, Hkv):
     import torch
     import oracle
