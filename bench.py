@@ -38,13 +38,17 @@ MEASURED_TRAFFIC = {
 }
 
 
+# the files that define the two attention kernels (with what they include), their K/V images and their launch
+TRAFFIC_SOURCES = ["attn_kernel.h", "mask_kernel.h", "pack_kernel.h", "sp_common.h", "shareprefill.hip",
+                   "../../include/shareprefill.h"]
+
+
 def kernel_source_digest() -> str:
     """sha256 (first 16 hex digits) over the library's sources: names the build a counter figure belongs to."""
     import hashlib
     h = hashlib.sha256()
     src = os.path.join(ROOT, "paper_2505_19578_amd", "csrc")
-    # the files that define the two attention kernels, their K/V images and their launch
-    for name in ["attn_kernel.h", "pack_kernel.h", "sp_common.h", "shareprefill.hip", "../../include/shareprefill.h"]:
+    for name in TRAFFIC_SOURCES:
         with open(os.path.join(src, name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()[:16]

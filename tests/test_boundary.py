@@ -255,3 +255,22 @@ def test_bench_refuses_more_than_one_gpu():
                          text=True, timeout=120)
     assert res.returncode != 0
     assert "single-GPU" in res.stderr and res.stdout.strip() == ""
+
+
+def test_traffic_digest_covers_what_the_attention_kernels_are_built_from():
+    """bench.py reports recorded HBM traffic only while the digest of its sources is the recorded one, so every file that the
+    attention and packing kernels include has to be in it."""
+    import re
+    import bench
+    csrc = os.path.join(ROOT, "paper_2505_19578_amd", "csrc")
+    todo, need = ["attn_kernel.h", "pack_kernel.h"], {"shareprefill.hip"}
+    while todo:
+        name = todo.pop()
+        if not os.path.exists(os.path.join(csrc, name)):
+            name = "../../include/" + name
+        if name in need:
+            continue
+        need.add(name)
+        with open(os.path.join(csrc, name)) as f:
+            todo += re.findall(r'#include "([^"]+)"', f.read())
+    assert need <= set(bench.TRAFFIC_SOURCES), need - set(bench.TRAFFIC_SOURCES)
