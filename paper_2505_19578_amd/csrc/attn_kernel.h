@@ -20,7 +20,7 @@ struct AttnParams {
   int seq, nqb, n_kv_heads, n_heads, n_maps;
   float inv_group;  // 1 / query heads per KV head
   int rgroups;  // ceil(nqb / (8 QB)): workgroups' rows per strand (see the workgroup mapping in attn_kernel)
-  int n_together;  // batch entries whose rows are dispatched in one order (1: one after the other, entry blockIdx.y)
+  int n_together;  // dense: batch entries whose rows are dispatched in one order (1: one after the other, entry blockIdx.y)
   float c;    // softmax scale * log2(e)
   float *lws;     // dense: block-local log2-sum-exp [b][n][nqb(nqb+1)/2][B] (row i, key block j <= i), or null
   float *scores;  // dense: [b][n][nqb][nkb], or null
@@ -240,8 +240,9 @@ __global__ __launch_bounds__(QB * B * 2, WAVES) void attn_kernel(AttnParams p) {
   const uint32_t u = blockIdx.x >> 3;
   // number of heads this launch really has for batch entry x (all listed ones unless the device says otherwise)
   auto heads_of = [&](int x) -> int { return p.act_n ? __builtin_amdgcn_readfirstlane(p.act_n[x]) : p.n_heads; };
+  const int together = DENSE ? p.n_together : 1;
   int b = blockIdx.y, n_act = heads_of(b), n_all = n_act;
-  for (int x = 1; x < p.n_together; ++x) n_all += heads_of(x);
+  for (int x = 1; x < together; ++x) n_all += heads_of(x);
   if (n_all <= 0 || (int)u >= n_all * p.rgroups) return;
   const int rest = u / (uint32_t)n_all;
   int strand;
@@ -250,11 +251,11 @@ __global__ __launch_bounds__(QB * B * 2, WAVES) void attn_kernel(AttnParams p) {
     // which heads there are, entries have runs of their own.
     int kk = u - rest * n_all;
     if (p.act_n)
-      while (kk >= n_act && b + 1 < p.n_together) {
+      while (kk >= n_act && b + 1 < together) {
         kk -= n_act;
         n_act = heads_of(++b);
       }
-    const int g0 = xcd * n_act, alike = p.act_n ? 1 : p.n_together;
+    const int g0 = xcd * n_act, alike = p.act_n ? 1 : together;
     for (int sn = 0;; ++sn) {
       const int s0 = (sn - g0) & 7;  // g0 + s0, + 8, ..: the strands of the run whose number is sn
       const int cnt = (n_act >> 3) + (s0 < (n_act & 7) ? 1 : 0);
